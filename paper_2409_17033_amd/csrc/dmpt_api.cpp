@@ -113,6 +113,7 @@ dmpt_status normalise(const dmpt_opts* o, Opts* r) {
 // Workspace plan.  All offsets are from the workspace base.
 struct Plan {
   int n, n_pad, nobs, prec, tile, ntile, nb64, nparts_step;
+  int ts;                          // tile edge of the small-size kernels (0: the large-size ones)
   int xslots;
   int ckpt, nckpt;                 // adjoint checkpoint interval (0: every X_n kept) and slot count
   size_t mat_f32, mat_op, mat_op2, mat_meta; // bytes per matrix: master, operand copy (and the
@@ -153,16 +154,45 @@ int flush_interval(int prec, int n_pad) {
   return std::max(1, (int)std::lround(f));
 }
 
-void make_plan(const Opts& o, int nobs, Plan* p) {
+// Tile edge of the small-size kernels (dmpt_small.hip) for a problem with z
+// sweep products a launch and with_p = 1 if the launch forms X^2 too; 0: the
+// large-size kernels.  All times are whole solves in ms, small / large.
+//  * The large tiles win once they fill the chip: FP16 split, z = 1: n = 2400
+//    6.0 / 6.7, n = 2600 7.27 / 7.68, n = 2800 8.41 / 7.90; z = 4: n = 2048
+//    10.1 / 10.7, n = 2400 16.8 / 15.6; z = 16: n = 1400 12.9 / 13.9, n = 2048
+//    36 / 29; the BF16 splits likewise.  FP32 products are bound by their MFMAs
+//    much longer: z = 1: n = 4600 83 / 91, n = 5000 111 / 103; z = 4: n = 2400
+//    37 / 43; z = 16: n = 1400 28 / 41, n = 2048 90 / 89.
+//  * Corrected runs of the three-term-X^2 option have wide sweep tiles and
+//    K-split tails in the large-size lists: those take over at n = 2048
+//    already (6.1 / 8.3; z = 4: 15.0 / 14.6).
+//  * 32 x 32 tiles while all of them are resident at once (two workgroups a
+//    CU), where the K loop of one tile is what a launch takes: z = 1, FP16
+//    split: n = 700 1.04 against 1.15 with 64 x 64 tiles, n = 850 1.47 against
+//    1.32.  FP32 tiles have four times the MFMA time, and the finer grain
+//    balances it up to five rounds: n = 700 1.27 against 1.61, z = 4 2.15
+//    against 2.48, n = 1000 2.19 against 2.15.
+int small_tile(int prec, bool wide_lists, int n, int z, int with_p) {
+  const int nmax = wide_lists ? 1984 : prec == kFP32 ? (z <= 1 ? 4608 : z <= 4 ? 2560 : 2048)
+                                                     : (z <= 1 ? 2600 : z <= 4 ? 2048 : 1536);
+  if (n > nmax) return 0;
+  const int t32 = (n + 63) / 64 * 2, jobs32 = t32 * (t32 + 1) / 2 * (z + with_p);
+  return jobs32 <= (prec == kFP32 ? 1280 : 512) ? 32 : 64;
+}
+
+void make_plan(const Opts& o, int nobs, Plan* p, bool small = true) {
   p->n = o.n;
-  p->n_pad = (o.n + kPadTo - 1) / kPadTo * kPadTo;
+  const bool adjoint = nobs > 0 && o.sweep == DMPT_SWEEP_ADJOINT;
+  const bool wide_lists = nobs > 0 && o.prec == kSplit32 && o.refine == 1;
+  p->ts = small ? small_tile(o.prec, wide_lists, o.n, nobs, adjoint ? 0 : 1) : 0;
+  const int pad = p->ts ? 64 : kPadTo;
+  p->n_pad = (o.n + pad - 1) / pad * pad;
   p->nobs = nobs;
   p->prec = o.prec;
-  p->tile = kStepTM;
+  p->tile = p->ts ? p->ts : kStepTM;
   p->ntile = p->n_pad / kStepTN;                       // 128-column blocks
   p->nb64 = p->n_pad / 64;
-  p->nparts_step = step_tile_count(p->n_pad);
-  const bool adjoint = nobs > 0 && o.sweep == DMPT_SWEEP_ADJOINT;
+  p->nparts_step = p->ts ? small_tile_count(p->n_pad, p->ts) : step_tile_count(p->n_pad);
   // The adjoint keeps X_1 .. X_{max_iter+2} (slot n = X_n; the last launch may
   // write one iterate past the result before the stop is seen), or with a
   // checkpoint interval k: two working slots, one slot per X_n with
@@ -174,14 +204,16 @@ void make_plan(const Opts& o, int nobs, Plan* p) {
   p->mat_f32 = np2 * 4;
   p->mat_op = o.prec == kFP32 ? 0 : np2 * operand_bytes(o.prec);
   p->mat_op2 = np2 * operand2_bytes(o.prec);
-  p->mat_meta = meta_bytes(std::max(p->nb64 * p->nb64, p->nparts_step));
+  // norm partials: one per 64 x 64 block (initialisation), or one per step tile
+  // (the FP16 split's sweep launches)
+  p->mat_meta = meta_bytes(o.prec == kSplitH ? std::max(p->nb64 * p->nb64, p->nparts_step) : p->nb64 * p->nb64);
   p->lz_steps = o.lanczos_steps;
   const int ut = p->nparts_step;                       // step tiles covering the upper triangle
   p->njobs_max = ut * (1 + std::max(nobs, 0)) + kMaxSplit;
   p->njobs_proj_max = ut * std::max(nobs, 1) + kMaxSplit;
   size_t off = 0;
   p->off_ctl = off; off = align_up(off + sizeof(Ctl));
-  const size_t part_bytes = (size_t)p->nb64 * p->nb64 * sizeof(Part);
+  const size_t part_bytes = (size_t)std::max(p->nb64 * p->nb64, p->nparts_step) * sizeof(Part);
   p->off_part[0] = off; off = align_up(off + part_bytes);
   p->off_part[1] = off; off = align_up(off + part_bytes);
   p->off_jobs = off; off = align_up(off + (size_t)p->njobs_max * 4);
@@ -197,7 +229,7 @@ void make_plan(const Opts& o, int nobs, Plan* p) {
   p->rprec = o.prec == kSplitH ? kSplitH : o.prec == kFP32 ? kFP32 : kSplit3;
   if (o.refine && nobs > 0 && !adjoint) {
     const int k = std::max(nobs, 0);
-    p->rf_copy_bytes = align_up(np2 * (p->rprec == kFP32 ? 4 : operand_bytes(p->rprec)));
+    p->rf_copy_bytes = align_up(p->rprec == kFP32 ? np2 * 4 : np2 * operand_bytes(p->rprec));
     p->rf_bslot_bytes = align_up(np2 * 4) + align_up(np2 * 2) + align_up(p->mat_meta);
     p->off_rf_copy = off; off = align_up(off + p->rf_copy_bytes * (2 + 2 * (size_t)k));
     p->off_rf_v = off; off = align_up(off + np2 * 4 * 2);
@@ -214,6 +246,13 @@ void make_plan(const Opts& o, int nobs, Plan* p) {
     p->off_split_buf = off; off = align_up(off + (size_t)kMaxSplit * 2 * kSplitTileFloats * sizeof(float));
   }
   p->total = off;
+}
+
+// C = alpha A B^T on the plan's kernels.
+hipError_t gemm_nt(const Plan& p, int prec, const void* A, const void* B, float* C, float alpha, int flush, int sym,
+                   hipStream_t s) {
+  return p.ts ? launch_gemm_small(prec, p.ts, A, B, C, p.n_pad, alpha, flush, sym, s)
+              : launch_gemm_op(prec, A, B, C, p.n_pad, alpha, flush, sym, s);
 }
 
 // Plain BF16 matrix set of the refinement sweep: slot q (0/1) of X, or of
@@ -465,6 +504,7 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
 
   hipStream_t s = o.stream;
   char* ws = o.ws;
+  const int tl = p.ts ? 1 : 0;   // layout of the FP32 masters
   Ctl* ctl = (Ctl*)(ws + p.off_ctl);
   double* a0_part = (double*)(ws + p.off_a0);
   ScopedEvents ev;
@@ -506,13 +546,15 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
   // 256 x 256 sweep-product tiles (one accumulation level) when the residual
   // correction follows: the three-term-X^2 option's steps and projection, and
   // the correction's own launches
-  const bool wide = refining && o.refine == 1 && split_launch;
+  const bool wide = refining && o.refine == 1 && split_launch && !p.ts;
   const int cus = persistent_grid(1 << 30);
   // job tables: [Z-jobs][P-jobs] (one combined table when the step is one launch)
   std::vector<uint32_t> jobs;
   // K-split tail tiles (runs on the wide lists): slot tables and combine lists
   std::vector<uint32_t> slots_main, cjobs_main;
-  if (split_launch && wide) {
+  if (p.ts) {
+    // the small-size kernels derive their tiles from the workgroup index: no list
+  } else if (split_launch && wide) {
     const JobList& L = cached_wide_list(p.n_pad, nobs, true, cus);
     jobs = L.jobs;
     slots_main = L.slots;
@@ -525,7 +567,7 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
     jobs = build_jobs(p.n_pad, adjoint ? 0 : nobs, true);
   }
   uint32_t* d_jobs = (uint32_t*)(ws + p.off_jobs);
-  DMPT_HIP(hipMemcpyAsync(d_jobs, jobs.data(), jobs.size() * 4, hipMemcpyHostToDevice, s));
+  if (!jobs.empty()) DMPT_HIP(hipMemcpyAsync(d_jobs, jobs.data(), jobs.size() * 4, hipMemcpyHostToDevice, s));
   const int njobs_main = (int)jobs.size();
   uint32_t* d_slots_main = wide ? (uint32_t*)(ws + p.off_split_slot) : nullptr;
   uint32_t* d_cjobs_main = wide ? (uint32_t*)(ws + p.off_cjobs) : nullptr;
@@ -551,9 +593,12 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
   }
   // Every step launch takes the next queue counter set (zeroed here, then
   // kept clean by the launches themselves).
-  DMPT_HIP(launch_queue_reset(ctl, s));
+  if (!p.ts) DMPT_HIP(launch_queue_reset(ctl, s));
   unsigned qseq = 0;
-  auto run_step = [&](int prec_, StepArgs& args, int nj, bool wide_ = false) {
+  // a launch over nz observables' Z tiles and, with with_p, the P tiles (the
+  // list of nj jobs in args.jobs holds the same tiles)
+  auto run_step = [&](int prec_, StepArgs& args, int nz, int with_p, int nj, bool wide_ = false) {
+    if (p.ts) return launch_step_small(prec_, p.ts, args, nz, with_p, s);
     if (nj <= 0) return hipSuccess;   // no launch: the counter sets stay in step
     step_queue_sets(ctl, qseq++, &args);
     return launch_step(prec_, args, nj, s, wide_);
@@ -576,10 +621,10 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
   Part* part[2] = {(Part*)(ws + p.off_part[0]), (Part*)(ws + p.off_part[1])};
   // X_1 (and Y_1 = beta A for the forward sweep) into slot of step 1
   if (!reuse_x) {
-    DMPT_HIP(launch_init(p.prec, p.tile, H, A, o.n, p.n_pad, adjoint ? 0 : nobs, nullptr, 0,
+    DMPT_HIP(launch_init(p.prec, tl, H, A, o.n, p.n_pad, adjoint ? 0 : nobs,
                          x_ref(p, ws, xslot(1)), y_ref(p, ws, 1), 0.0, part[1], ctl, s));
     // FP16 split: the Y copies are written once their norms are known
-    if (p.prec == kSplitH && !adjoint && nobs > 0) DMPT_HIP(launch_resplit(p.prec, y_ref(p, ws, 1), p.n_pad, nobs, s));
+    if (p.prec == kSplitH && !adjoint && nobs > 0) DMPT_HIP(launch_resplit(p.prec, y_ref(p, ws, 1), p.n_pad, nobs, tl, s));
   }
   const int mb1 = prof.mark();
   std::vector<std::pair<int, int>> step_marks;
@@ -637,11 +682,11 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
         a.jobs = d_jobs;
         a.flush = flush_interval(xprec, p.n_pad);
         a.flush_z = flush_interval(yprec, p.n_pad);
-        DMPT_HIP(run_step(kSplit32, a, njobs_main, wide));
+        DMPT_HIP(run_step(kSplit32, a, nobs, 1, njobs_main, wide));
         DMPT_HIP(combine(kSplit32, a, d_cjobs_main, cjobs_main.size()));
       } else {
         a.jobs = step_jobs;
-        DMPT_HIP(run_step(xlaunch, a, njobs_step));
+        DMPT_HIP(run_step(xlaunch, a, adjoint ? 0 : nobs, 1, njobs_step));
       }
       step_marks.emplace_back(ma, prof.mark());
       ++launched;
@@ -664,12 +709,13 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
   const int mp0 = prof.mark();
   if (nobs > 0 && st == DMPT_OK && adjoint) {
     // Eq. DM2: Y_M = A; for n = M..1, Y_{n-1} from Y_n with X_n, sigma_n; chi = beta Y_0.
-    DMPT_HIP(launch_init(p.prec, p.tile, nullptr, A, o.n, p.n_pad, -nobs, nullptr, 0,
+    DMPT_HIP(launch_init(p.prec, tl, nullptr, A, o.n, p.n_pad, -nobs,
                          x_ref(p, ws, 0), y_ref(p, ws, 0), 1.0, nullptr, ctl, s));
-    if (p.prec == kSplitH) DMPT_HIP(launch_resplit(p.prec, y_ref(p, ws, 0), p.n_pad, nobs, s));
-    const std::vector<uint32_t> zjobs = build_jobs(p.n_pad, nobs, false);
+    if (p.prec == kSplitH) DMPT_HIP(launch_resplit(p.prec, y_ref(p, ws, 0), p.n_pad, nobs, tl, s));
+    std::vector<uint32_t> zjobs;
+    if (!p.ts) zjobs = build_jobs(p.n_pad, nobs, false);
     uint32_t* d_zjobs = d_jobs + p.nparts_step;
-    DMPT_HIP(hipMemcpyAsync(d_zjobs, zjobs.data(), zjobs.size() * 4, hipMemcpyHostToDevice, s));
+    if (!p.ts) DMPT_HIP(hipMemcpyAsync(d_zjobs, zjobs.data(), zjobs.size() * 4, hipMemcpyHostToDevice, s));
     StepArgs b = a;
     b.decide = 0;
     b.flush = flush_interval(yprec, p.n_pad);
@@ -691,14 +737,14 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
         r.step = n;
         r.x_in = x_ref(p, ws, xslot_bwd(n));
         r.x_out = x_ref(p, ws, xslot_bwd(n + 1));
-        DMPT_HIP(run_step(xlaunch, r, p.nparts_step));
+        DMPT_HIP(run_step(xlaunch, r, 0, 1, p.nparts_step));
       }
       for (int n = n1; n >= n0; --n) {
         b.step = n;
         b.x_in = sweep_x(x_ref(p, ws, xslot_bwd(n)));
         b.y_in = y_ref(p, ws, ys);
         b.y_out = y_ref(p, ws, ys ^ 1);
-        DMPT_HIP(run_step(yprec, b, (int)zjobs.size()));
+        DMPT_HIP(run_step(yprec, b, nobs, 0, (int)zjobs.size()));
         ys ^= 1;
       }
       n1 = n0 - 1;
@@ -724,7 +770,9 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
     const int pprec = proj3 ? kSplit3 : p.prec == kBF16 ? kFP32 : yprec;
     // (the list also serves the launches of the residual correction)
     std::vector<uint32_t> pjobs;
-    if (wide) {
+    if (p.ts) {
+      // no list
+    } else if (wide) {
       const JobList& L = cached_wide_list(p.n_pad, nobs, false, cus);
       pjobs = L.jobs;
       slots_proj = L.slots;
@@ -733,7 +781,7 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
       pjobs = build_jobs(p.n_pad, nobs, false);
     }
     uint32_t* d_pjobs = (uint32_t*)(ws + p.off_jobs_proj);
-    DMPT_HIP(hipMemcpyAsync(d_pjobs, pjobs.data(), pjobs.size() * 4, hipMemcpyHostToDevice, s));
+    if (!pjobs.empty()) DMPT_HIP(hipMemcpyAsync(d_pjobs, pjobs.data(), pjobs.size() * 4, hipMemcpyHostToDevice, s));
     if (!cjobs_proj.empty()) {
       DMPT_HIP(hipMemcpyAsync(d_slots_proj, slots_proj.data(), slots_proj.size() * 4, hipMemcpyHostToDevice, s));
       DMPT_HIP(hipMemcpyAsync(d_cjobs_proj, cjobs_proj.data(), cjobs_proj.size() * 4, hipMemcpyHostToDevice, s));
@@ -754,15 +802,15 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
     b.x_in = pprec == kFP32 ? as_fp32(x_ref(p, ws, xfin)) : proj3 ? x_ref(p, ws, xfin) : sweep_x(x_ref(p, ws, xfin));
     std::vector<uint32_t> rjobs;
     if (proj3) {
-      rjobs = build_jobs(p.n_pad, nobs, false);
-      DMPT_HIP(hipMemcpyAsync(d_jobs, rjobs.data(), rjobs.size() * 4, hipMemcpyHostToDevice, s));
+      if (!p.ts) rjobs = build_jobs(p.n_pad, nobs, false);
+      if (!p.ts) DMPT_HIP(hipMemcpyAsync(d_jobs, rjobs.data(), rjobs.size() * 4, hipMemcpyHostToDevice, s));
       b.jobs = d_jobs;
       b.split_slot = nullptr;
       b.split_buf = nullptr;
       const MatRef y0 = y_ref(p, ws, yfin);   // its operand area holds the three-term copy
       for (int k = 0; k < nobs; ++k)
         DMPT_HIP(launch_copy_src(kSplit3, y0.f32 + (size_t)k * y0.stride_f32, p.n_pad,
-                                 (char*)y0.op + (size_t)k * y0.stride_op, p.n_pad, 0, s));
+                                 (char*)y0.op + (size_t)k * y0.stride_op, p.n_pad, 0, tl, tl, s));
     }
     // The launch after the last step (it ran before the stop was seen, since
     // the stopping test needs its idempotency error) formed Z = D Y + Y D from
@@ -781,7 +829,7 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
     int q0 = 0;
     if (reuse_first) {
       if (sig_next == -1)
-        DMPT_HIP(launch_reflect(pprec, y_ref(p, ws, yfin), y_ref(p, ws, yfin ^ 1), p.n_pad, nobs, s));
+        DMPT_HIP(launch_reflect(pprec, y_ref(p, ws, yfin), y_ref(p, ws, yfin ^ 1), p.n_pad, nobs, tl, s));
       yfin ^= 1;
       q0 = 1;
     }
@@ -791,9 +839,9 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
       b.y_in = view(y_ref(p, ws, yfin));
       b.y_out = view(y_ref(p, ws, yfin ^ 1));
       if (proj3) {
-        DMPT_HIP(run_step(pprec, b, (int)rjobs.size()));
+        DMPT_HIP(run_step(pprec, b, nobs, 0, (int)rjobs.size()));
       } else {
-        DMPT_HIP(run_step(pprec, b, (int)pjobs.size(), wide));
+        DMPT_HIP(run_step(pprec, b, nobs, 0, (int)pjobs.size(), wide));
         DMPT_HIP(combine(pprec, b, d_cjobs_proj, cjobs_proj.size()));
       }
       yfin ^= 1;
@@ -822,6 +870,7 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
     const MatRef xf = x_ref(p, ws, xfin);
     const MatRef yf = y_ref(p, ws, yfin);
     char* cbase = ws + p.off_rf_copy;
+    const size_t bf16_bytes = np2 * 2;   // one plain BF16 copy
     auto cpy = [&](int q) { return (void*)(cbase + (size_t)q * p.rf_copy_bytes); };   // 0 D, 1 H, 2+k A_k, 2+nobs+k Y_k
     float* v1 = (float*)(ws + p.off_rf_v);
     float* v2 = v1 + np2;
@@ -872,23 +921,23 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
     for (int q = 0; q < 2 + 2 * nobs; ++q) {
       if (q == 0 && d_has_copy) continue;
       if (rp == kFP32) {
-        if (q == 1 || (q >= 2 && q < 2 + nobs)) DMPT_HIP(launch_pad(src_of(q), o.n, p.n_pad, (float*)cpy(q), 0, s));
+        if (q == 1 || (q >= 2 && q < 2 + nobs)) DMPT_HIP(launch_pad(src_of(q), o.n, p.n_pad, (float*)cpy(q), 0, tl, s));
       } else {
-        DMPT_HIP(launch_copy_src(rp, src_of(q), nsrc_of(q), cpy(q), p.n_pad, ex[q], s));
+        DMPT_HIP(launch_copy_src(rp, src_of(q), nsrc_of(q), cpy(q), p.n_pad, ex[q],
+                                   q == 0 || q >= 2 + nobs ? tl : 0, tl, s));
       }
     }
     const int flr = flush_interval(rp, p.n_pad);
     char* rbase = ws + p.off_rf_r;
     for (int k = 0; k < nobs; ++k) {
-      DMPT_HIP(launch_gemm_op(rp, opnd(0), opnd(2 + k), v1, p.n_pad, std::ldexp(1.0f, -(ex[0] + ex[2 + k])), flr, 0, s));
-      DMPT_HIP(launch_gemm_op(rp, opnd(2 + nobs + k), opnd(1), v2, p.n_pad,
-                              std::ldexp(1.0f, -(ex[2 + nobs + k] + ex[1])), flr, 0, s));
-      DMPT_HIP(launch_antisym_bf16(v1, v2, p.n_pad, rbase + (size_t)k * np2 * 2, s));
+      DMPT_HIP(gemm_nt(p, rp, opnd(0), opnd(2 + k), v1, std::ldexp(1.0f, -(ex[0] + ex[2 + k])), flr, 0, s));
+      DMPT_HIP(gemm_nt(p, rp, opnd(2 + nobs + k), opnd(1), v2, std::ldexp(1.0f, -(ex[2 + nobs + k] + ex[1])), flr, 0, s));
+      DMPT_HIP(launch_antisym_bf16(v1, v2, p.n_pad, rbase + (size_t)k * bf16_bytes, tl, s));
     }
     // plain BF16 copies of the X_n: slot n of the history (X_1 from the
     // initialisation below, X_2 .. X_{m+1} = D written by the steps)
     char* hist = ws + p.off_rf_hist;
-    const size_t hstride = np2 * 2;
+    const size_t hstride = bf16_bytes;
     const int flb = flush_interval(kBF16, p.n_pad);
     MatRef dref;
     dref.f32 = xf.f32;
@@ -901,7 +950,7 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
     rref.op = rbase;
     rref.meta = xf.meta;
     rref.stride_f32 = 0;
-    rref.stride_op = np2 * 2;
+    rref.stride_op = bf16_bytes;
     auto bx = [&](int q) { return bf16_ref(p, ws, p.off_rf_x, q, 1); };
     auto by = [&](int q) { return bf16_ref(p, ws, p.off_rf_y, q, nobs); };
     const uint32_t* d_pjobs = (const uint32_t*)(ws + p.off_jobs_proj);   // Z-jobs of every observable
@@ -923,12 +972,12 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
     b.y_in = rref;
     b.y_out = by(1);
     b.oscale = (float)(-hctl.beta);
-    DMPT_HIP(run_step(kBF16, b, nzj, wide));
+    DMPT_HIP(run_step(kBF16, b, nobs, 0, nzj, wide));
     DMPT_HIP(combine(kBF16, b, d_cjobs_proj, cjobs_proj.size()));
     // X_1 = alpha I + beta H in plain BF16 (its copy lands in history slot 1)
     MatRef x1 = bx(0);
     x1.op = hist + hstride;
-    DMPT_HIP(launch_init(kBF16, p.tile, H, nullptr, o.n, p.n_pad, 0, nullptr, 0, x1, by(1), 0.0, part[1], ctl, s));
+    DMPT_HIP(launch_init(kBF16, tl, H, nullptr, o.n, p.n_pad, 0, x1, by(1), 0.0, part[1], ctl, s));
     // the sweep of B: Z-jobs only, X_n from the history, sigma_n as recorded;
     // with opts.sweep_tol it stops after the first X_n within sqrt(sweep_tol)
     // of idempotency (the correction only needs accuracy relative to itself)
@@ -949,7 +998,7 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
       r.x_in.op = hist + (size_t)n * hstride;
       r.y_in = by(n & 1);
       r.y_out = by((n + 1) & 1);
-      DMPT_HIP(run_step(kBF16, r, nzj, wide));
+      DMPT_HIP(run_step(kBF16, r, nobs, 0, nzj, wide));
       DMPT_HIP(combine(kBF16, r, d_cjobs_proj, cjobs_proj.size()));
     }
     // projection of delta with D, then Y += P(delta).  project = 2: delta is
@@ -964,7 +1013,7 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
       const MatRef dd = by(yd);
       for (int k = 0; k < nobs; ++k)
         DMPT_HIP(launch_copy_src(kSplit2, dd.f32 + (size_t)k * dd.stride_f32, p.n_pad,
-                                 (char*)yfree.op + (size_t)k * yfree.stride_op, p.n_pad, 0, s));
+                                 (char*)yfree.op + (size_t)k * yfree.stride_op, p.n_pad, 0, tl, tl, s));
       b.flush = flush_interval(kSplit2, p.n_pad);
       b.x_in = sweep_x(xf);
     }
@@ -982,10 +1031,10 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
         b.y_out.op = copy2;
         b.y_out.stride_op = yfree.stride_op;
         b.y_out.meta = yfree.meta;
-        DMPT_HIP(run_step(kSplit2, b, nzj, wide));
+        DMPT_HIP(run_step(kSplit2, b, nobs, 0, nzj, wide));
         DMPT_HIP(combine(kSplit2, b, d_cjobs_proj, cjobs_proj.size()));
       } else {
-        DMPT_HIP(run_step(kBF16, b, nzj, wide));
+        DMPT_HIP(run_step(kBF16, b, nobs, 0, nzj, wide));
         DMPT_HIP(combine(kBF16, b, d_cjobs_proj, cjobs_proj.size()));
       }
       yd ^= 1;
@@ -998,7 +1047,7 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
   const MatRef xf = x_ref(p, ws, xfin);
   const MatRef yf = y_ref(p, ws, yfin);
   DMPT_HIP(launch_output(xf.f32, nobs ? yf.f32 : nullptr, yf.stride_f32, A, o.n, p.n_pad, nobs, D,
-                         nobs ? chi : nullptr, o.spin, adjoint ? 1 : 0, nullptr, 0, 0, a0_part, ctl, s));
+                         nobs ? chi : nullptr, o.spin, adjoint ? 1 : 0, tl, a0_part, ctl, s));
   const int mo1 = prof.mark();
   std::vector<double> hpart((size_t)kOutBlocks * std::max(nobs, 1));
   if (nobs) DMPT_HIP(hipMemcpyAsync(hpart.data(), a0_part, sizeof(double) * hpart.size(), hipMemcpyDeviceToHost, s));
@@ -1197,6 +1246,7 @@ dmpt_status dmpt_susceptibility_nonorth(const float* H, const float* Z, const fl
   if (o.ws_bytes < w.total) return fail(DMPT_ERR_WORKSPACE, "workspace has %zu bytes, need %zu", o.ws_bytes, w.total);
   hipStream_t s = o.stream;
   char* ws = o.ws;
+  const int tl = p.ts ? 1 : 0;
   float* zp = (float*)(ws + w.zp);
   float* ztp = (float*)(ws + w.ztp);
   float* tp = (float*)(ws + w.tp);
@@ -1209,22 +1259,22 @@ dmpt_status dmpt_susceptibility_nonorth(const float* H, const float* Z, const fl
   const int fl = flush_interval(kFP32, np);
   // M_perp = Z^T M Z for symmetric M: T = Z^T M^T = Z^T M, then Z^T T^T = Z^T M Z
   auto to_perp = [&](const float* m, float* out) -> dmpt_status {
-    DMPT_HIP(launch_pad(m, n, np, up, 0, s));
-    DMPT_HIP(launch_gemm_nt(ztp, up, tp, np, 1.0f, fl, s));
-    DMPT_HIP(launch_gemm_nt(ztp, tp, up, np, 1.0f, fl, s));
-    DMPT_HIP(launch_copy_out(up, n, np, out, s));
+    DMPT_HIP(launch_pad(m, n, np, up, 0, tl, s));
+    DMPT_HIP(gemm_nt(p, kFP32, ztp, up, tp, 1.0f, fl, 0, s));
+    DMPT_HIP(gemm_nt(p, kFP32, ztp, tp, up, 1.0f, fl, 0, s));
+    DMPT_HIP(launch_copy_out(up, n, np, out, tl, s));
     return DMPT_OK;
   };
   // M = Z M_perp Z^T for symmetric M_perp: T = Z M_perp^T = Z M_perp, then T Z^T
   auto from_perp = [&](const float* m, float* out) -> dmpt_status {
-    DMPT_HIP(launch_pad(m, n, np, up, 0, s));
-    DMPT_HIP(launch_gemm_nt(zp, up, tp, np, 1.0f, fl, s));
-    DMPT_HIP(launch_gemm_nt(tp, zp, up, np, 1.0f, fl, s));
-    DMPT_HIP(launch_copy_out(up, n, np, out, s));
+    DMPT_HIP(launch_pad(m, n, np, up, 0, tl, s));
+    DMPT_HIP(gemm_nt(p, kFP32, zp, up, tp, 1.0f, fl, 0, s));
+    DMPT_HIP(gemm_nt(p, kFP32, tp, zp, up, 1.0f, fl, 0, s));
+    DMPT_HIP(launch_copy_out(up, n, np, out, tl, s));
     return DMPT_OK;
   };
-  DMPT_HIP(launch_pad(Z, n, np, zp, 0, s));
-  DMPT_HIP(launch_pad(Z, n, np, ztp, 1, s));
+  DMPT_HIP(launch_pad(Z, n, np, zp, 0, tl, s));
+  DMPT_HIP(launch_pad(Z, n, np, ztp, 1, tl, s));
   if ((st = to_perp(H, hperp)) != DMPT_OK) return st;
   for (int k = 0; k < nobs; ++k)
     if ((st = to_perp(A + k * n2, aperp + k * n2)) != DMPT_OK) return st;
@@ -1259,7 +1309,8 @@ static int fermi_copy_prec(int prec) {
   return prec == kSplitH ? kSplitH : prec == kSplit3 ? kSplit3 : prec == kSplit2 ? kSplit2 : kFP32;
 }
 
-static FermiWS fermi_ws(size_t base, int n_pad, int nobs, int cprec) {
+static FermiWS fermi_ws(size_t base, const Plan& p, int nobs, int cprec) {
+  const int n_pad = p.n_pad;
   FermiWS w;
   const size_t m = (size_t)n_pad * n_pad * 4;
   const size_t mc = cprec == kFP32 ? 0 : (size_t)n_pad * n_pad * operand_bytes(cprec);   // operand copy
@@ -1307,7 +1358,7 @@ static dmpt_status fermi_check(const dmpt_opts* opts, const dmpt_fermi_opts* f, 
   if (f->newton_max < 0 || f->newton_max > 200) return fail(DMPT_ERR_ARG, "newton_max out of range [0, 200]");
   if (!(f->count_tol >= 0) || !std::isfinite(f->count_tol)) return fail(DMPT_ERR_ARG, "count_tol must be finite and >= 0");
   if (f->reserved != 0) return fail(DMPT_ERR_ARG, "reserved must be 0");
-  make_plan(*o, 0, p);
+  make_plan(*o, 0, p, false);
   return DMPT_OK;
 }
 
@@ -1315,7 +1366,7 @@ size_t dmpt_fermi_workspace_bytes(const dmpt_opts* opts, const dmpt_fermi_opts* 
   Opts o;
   Plan p;
   if (fermi_check(opts, fopts, nobs, &o, &p) != DMPT_OK) return 0;
-  return fermi_ws(p.off_x, p.n_pad, nobs, fermi_copy_prec(o.prec)).total;
+  return fermi_ws(p.off_x, p, nobs, fermi_copy_prec(o.prec)).total;
 }
 
 // An operand of the finite-temperature products: FP32 master, and for the
@@ -1344,7 +1395,7 @@ dmpt_status dmpt_susceptibility_fermi(const float* H, const float* A, int32_t no
   const int cprec = fermi_copy_prec(o.prec);
   const bool split = cprec != kFP32;
   const size_t cbytes = split ? (size_t)operand_bytes(cprec) : 0;
-  const FermiWS w = fermi_ws(p.off_x, np, nobs, cprec);
+  const FermiWS w = fermi_ws(p.off_x, p, nobs, cprec);
   if (!o.ws) return fail(DMPT_ERR_WORKSPACE, "workspace is NULL (need %zu bytes)", w.total);
   if (o.ws_bytes < w.total) return fail(DMPT_ERR_WORKSPACE, "workspace has %zu bytes, need %zu", o.ws_bytes, w.total);
   if (finfo) std::memset(finfo, 0, sizeof(*finfo));
@@ -1398,7 +1449,7 @@ dmpt_status dmpt_susceptibility_fermi(const float* H, const float* A, int32_t no
     if (!split) return DMPT_OK;
     if (cprec != kSplitH) {   // BF16 terms keep the FP32 exponent range: no scale
       a.e = 0;
-      DMPT_HIP(launch_copy_src(cprec, a.m, np, a.c, np, 0, s));
+      DMPT_HIP(launch_copy_src(cprec, a.m, np, a.c, np, 0, 0, 0, s));
       return DMPT_OK;
     }
     a.e = e;
@@ -1421,9 +1472,9 @@ dmpt_status dmpt_susceptibility_fermi(const float* H, const float* A, int32_t no
   auto prod = [&](const FMat& a, const FMat& b, float* out, double alpha, bool sym) -> dmpt_status {
     ++products;
     if (split)
-      DMPT_HIP(launch_gemm_op(cprec, a.c, b.c, out, np, (float)std::ldexp(alpha, -(a.e + b.e)), fl, sym ? 1 : 0, s));
+      DMPT_HIP(gemm_nt(p, cprec, a.c, b.c, out, (float)std::ldexp(alpha, -(a.e + b.e)), fl, sym ? 1 : 0, s));
     else
-      DMPT_HIP(launch_gemm_op(kFP32, a.m, b.m, out, np, (float)alpha, fl, sym ? 1 : 0, s));
+      DMPT_HIP(gemm_nt(p, kFP32, a.m, b.m, out, (float)alpha, fl, sym ? 1 : 0, s));
     return DMPT_OK;
   };
   auto doublings_for = [&](double mu) {
@@ -1546,7 +1597,7 @@ dmpt_status dmpt_susceptibility_fermi(const float* H, const float* A, int32_t no
   DMPT_HIP(launch_axpby(E2.m, E.m, 1.0f, nullptr, 0.0f, 0.5f, n, np, s));
   double* a0p = (double*)(ws + w.a0p);
   DMPT_HIP(launch_output(E2.m, nobs ? Y[0].m : nullptr, np2, A, n, np, nobs, D, nobs ? chi : nullptr, o.spin, 0,
-                         nullptr, 0, 0, a0p, ctl, s));
+                         0, a0p, ctl, s));
   std::vector<double> hpart((size_t)kOutBlocks * std::max(nobs, 1));
   if (nobs) DMPT_HIP(hipMemcpyAsync(hpart.data(), a0p, sizeof(double) * hpart.size(), hipMemcpyDeviceToHost, s));
   DMPT_HIP(hipEventRecord(ev.e1, s));

@@ -167,9 +167,10 @@ hipError_t launch_lanczos_start(double* v, double* vprev, int n, hipStream_t s);
 hipError_t launch_lanczos_step(const float* h, int n, double* v, double* vprev, double* w,
                                double* ab, int j, hipStream_t s);
 hipError_t launch_set_bounds(Ctl* ctl, double emin, double emax, hipStream_t s);
-hipError_t launch_init(int prec, int tile, const float* h, const float* a, int n, int n_pad,
-                       int nobs, const uint32_t* jobs, int njobs, MatRef x, MatRef y,
-                       double y_scale_mode, Part* part, Ctl* ctl, hipStream_t s);
+// tiled (here and below): the padded FP32 matrices and the operand copies are
+// in the small-size kernels' layouts (m_off, op_off in dmpt_device.h).
+hipError_t launch_init(int prec, int tiled, const float* h, const float* a, int n, int n_pad, int nobs, MatRef x,
+                       MatRef y, double y_scale_mode, Part* part, Ctl* ctl, hipStream_t s);
 // Workgroups of a persistent step launch over njobs jobs (one per CU at most).
 int persistent_grid(int njobs);
 // Step launch: a persistent grid of at most one workgroup per CU working
@@ -189,14 +190,24 @@ hipError_t launch_queue_reset(Ctl* ctl, hipStream_t s);
 // epilogue with the launch's sigma (nothing when that launch stopped, or for
 // Z tiles once the sweep has stopped).  prec as for launch_step with wide.
 hipError_t launch_step_combine(int prec, StepArgs args, const uint32_t* cjobs, int ncomb, hipStream_t s);
+// The small-size kernels (dmpt_small.hip): square tiles of ts = 64 or 32,
+// n_pad a multiple of 64.  One step launch over nz observables' Z tiles and,
+// with with_p, the P tiles (the controller runs with the P tiles only).
+hipError_t launch_step_small(int prec, int ts, const StepArgs& args, int nz, int with_p, hipStream_t s);
+// C = alpha A B^T; FP32 operands and C tiled, split copies as launch_gemm_op's;
+// sym: both triangles are stored.
+hipError_t launch_gemm_small(int prec, int ts, const void* A, const void* B, float* C, int n_pad, float alpha, int flush,
+                             int sym, hipStream_t s);
+inline int small_tile_count(int n_pad, int ts) { const int t = n_pad / ts; return t * (t + 1) / 2; }
+// Upper bound of the norm partials a producer writes for one matrix.
+__host__ __device__ inline int meta_entries(int n_pad) { return (n_pad / 32) * (n_pad / 32); }
 // Step tiles are 256 rows x 128 columns; tile (I, J) with J >= 2I covers the
 // upper triangle.  ntile in StepArgs is the number of 128-column blocks.
 constexpr int kStepTM = 256, kStepTN = 128;
 inline int step_tile_count(int n_pad) { const int t = n_pad / kStepTM; return t * (t + 1); }
 hipError_t launch_output(const float* x32, const float* y32, size_t ystride, const float* a,
                          int n, int n_pad, int nobs, float* d_out, float* chi_out,
-                         double scale, int scale_by_beta, const uint32_t* jobs, int njobs,
-                         int tile, double* a0_part, Ctl* ctl, hipStream_t s);
+                         double scale, int scale_by_beta, int tiled, double* a0_part, Ctl* ctl, hipStream_t s);
 // dmpt_response with the caller's workspace (dmpt_api.cpp), shared by the
 // entry point that brings its own device scratch (dmpt_static.hip), and the
 // error reporter behind dmpt_last_error.
@@ -207,7 +218,7 @@ dmpt_status report_error(dmpt_status st, const char* msg);
 hipError_t launch_response(const float* chi, int nobs, const float* h1, int npert, size_t n2,
                            double* part, int nblk, double* out_dev, int ld, hipStream_t s);
 int response_blocks(size_t n2);
-hipError_t launch_copy_out(const float* src, int n, int n_pad, float* dst, hipStream_t s);
+hipError_t launch_copy_out(const float* src, int n, int n_pad, float* dst, int tiled, hipStream_t s);
 // Non-orthonormal basis: C = alpha A B^T (n_pad x n_pad, n_pad % 256 == 0,
 // FP32 MFMA) and zero-padded (optionally transposed) copies.
 hipError_t launch_gemm_nt(const float* A, const float* B, float* C, int n_pad, float alpha, int flush,
@@ -223,23 +234,25 @@ hipError_t launch_gemm_op(int prec, const void* A, const void* B, float* C, int 
 // Tiled FP16 split copy (the kSplitH operand format) of an n_pad x n_pad FP32
 // matrix scaled by 2^e.
 hipError_t launch_split_copy(const float* src, void* dst, int n_pad, int e, hipStream_t s);
-hipError_t launch_pad(const float* src, int n, int n_pad, float* dst, int transpose, hipStream_t s);
+hipError_t launch_pad(const float* src, int n, int n_pad, float* dst, int transpose, int tiled, hipStream_t s);
 // Residual refinement helpers.
 //   launch_copy_src: tiled operand copy (prec kSplitH at scale 2^e, kSplit3 or
-//     kBF16) of the zero padding of an n_src x n_src row-major FP32 matrix.
+//     kBF16) of the zero padding of an n_src x n_src FP32 matrix (row-major, or
+//     with tiled an n_pad x n_pad one in the tiled layout); small: the copy's layout.
 //   launch_norm2: kNormBlocks FP64 partials of the squared Frobenius norm of
 //     `count` consecutive floats.
 //   launch_antisym_bf16: plain BF16 tiled copy of W - W^T, W = V1 + V2.
 //   launch_add_into: y_k += d_k over nmat n_pad x n_pad FP32 masters.
 constexpr int kNormBlocks = 256;
-hipError_t launch_copy_src(int prec, const float* src, int n_src, void* dst, int n_pad, int e, hipStream_t s);
+hipError_t launch_copy_src(int prec, const float* src, int n_src, void* dst, int n_pad, int e, int tiled, int small,
+                           hipStream_t s);
 hipError_t launch_norm2(const float* src, size_t count, double* part, hipStream_t s);
-hipError_t launch_antisym_bf16(const float* v1, const float* v2, int n_pad, void* dst, hipStream_t s);
+hipError_t launch_antisym_bf16(const float* v1, const float* v2, int n_pad, void* dst, int tiled, hipStream_t s);
 hipError_t launch_add_into(float* y, size_t ys, const float* d, size_t ds, int n_pad, int nmat, hipStream_t s);
-hipError_t launch_resplit(int prec, MatRef m, int n_pad, int nmat, hipStream_t s);
+hipError_t launch_resplit(int prec, MatRef m, int n_pad, int nmat, int tiled, hipStream_t s);
 // b <- 2 a - b for nmat matrices (FP32 masters), rewriting b's operand copy at
 // the scale b's metadata holds and b's norm partials.
-hipError_t launch_reflect(int prec, MatRef a, MatRef b, int n_pad, int nmat, hipStream_t s);
+hipError_t launch_reflect(int prec, MatRef a, MatRef b, int n_pad, int nmat, int tiled, hipStream_t s);
 int stage_k(int prec);   // k values per pipeline stage of the step kernel
 
 }  // namespace dmpt

@@ -44,31 +44,11 @@
 
 #include <type_traits>
 
+#include "dmpt_device.h"
 #include "dmpt_internal.h"
 #include "sp2_rule.h"
 
 namespace dmpt {
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-#define LDS_AS __attribute__((address_space(3)))
-#define GLB_AS __attribute__((address_space(1)))
-
-// Bytes per LDS row per pipeline stage: 16 k values of FP32 / packed split-2
-// (BF16 or FP16; 64 B = 4 slots of 16 B), 32 k values of plain BF16 (64 B),
-// 16 k values of packed split-3 (96 B = 6 slots).
-template <int PREC> struct Fmt {
-  static constexpr int RB = PREC == kSplit3 ? 96 : 64;
-  static constexpr int S = RB / 16;
-  static constexpr int K = PREC == kBF16 ? 32 : 16;
-};
-// Format of the operand copy in HBM (the same as the staged one).
-template <int PREC> struct Store { static constexpr int F = PREC; };
 
 int stage_k(int prec) { return prec == kBF16 ? 32 : 16; }
 
@@ -79,7 +59,6 @@ int stage_k(int prec) { return prec == kBF16 ? 32 : 16; }
 // 128-row B panel.
 constexpr int TM = 256, TN = 128, NW = 8, NT = 512, RING = 4;
 constexpr int BR = 2, BC = 2;
-constexpr int RBLK = 128;   // rows per chunk of the tiled operand layout
 // Epilogue staging of one wave's 64 x 64 output region: row stride 65 floats,
 // so both a row walk and a column walk over 64 lanes hit 64 distinct banks.
 constexpr int kLS = 65;
@@ -101,88 +80,6 @@ template <int PREC> struct Pipe {
   static constexpr int L = (NI + NW - 1) / NW;         // per wave (padded with dummies)
   static constexpr bool TILED = PREC != kFP32;
 };
-
-// ---------------------------------------------------------------- helpers
-
-__device__ __forceinline__ unsigned short bf16_bits(float x) {
-  return __builtin_bit_cast(unsigned short, (__bf16)x);   // round to nearest even
-}
-__device__ __forceinline__ float bf16_val(unsigned short b) {
-  return __builtin_bit_cast(float, ((unsigned int)b) << 16);
-}
-__device__ __forceinline__ unsigned short f16_bits(float x) {
-  return __builtin_bit_cast(unsigned short, (_Float16)x);   // round to nearest even, subnormals kept
-}
-__device__ __forceinline__ float f16_val(unsigned short b) { return (float)__builtin_bit_cast(_Float16, b); }
-// Eq. doubleHalf with BF16 terms: part_0 = RNE(x), part_t = RNE(x - sum_{s<t} part_s).
-template <int T>
-__device__ __forceinline__ void split_terms(float x, unsigned short (&p)[T]) {
-  float r = x;
-#pragma unroll
-  for (int t = 0; t < T; ++t) {
-    p[t] = bf16_bits(r);
-    r = r - bf16_val(p[t]);
-  }
-}
-// Eq. doubleHalf with FP16 terms on the scaled value: hi = RNE(x sc),
-// lo = RNE(x sc - hi); sc is a power of two, x sc - hi is exact in FP32.
-__device__ __forceinline__ void split_terms_h(float x, float sc, unsigned short (&p)[2]) {
-  const float xs = x * sc;
-  p[0] = f16_bits(xs);
-  p[1] = f16_bits(xs - f16_val(p[0]));
-}
-template <int PREC> struct Terms {
-  static constexpr int T = PREC == kSplit3 ? 3 : (PREC == kSplit2 || PREC == kSplitH) ? 2 : 1;
-};
-// The split terms of one element in the operand format F (sc: kSplitH scale).
-template <int F>
-__device__ __forceinline__ void split_for(float v, float sc, unsigned short (&p)[Terms<F>::T]) {
-  if constexpr (F == kSplitH) split_terms_h(v, sc, p);
-  else split_terms<Terms<F>::T>(v, p);
-}
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
-// kSplitH: exponent s of the scale 2^s of a Y copy whose entries are bounded
-// by bound * nrm (nrm a Frobenius norm): the largest s with bound * nrm * 2^s
-// <= kYTarget, clamped to [-100, 100]; 0 for a zero or non-finite norm.
-__device__ __forceinline__ int yscale_exp(double nrm, double bound) {
-  const double b = bound * nrm;
-  if (!(b > 0.0) || !(b < 1e300)) return 0;
-  const int e = (int)floor(log2(kYTarget / b));
-  return e < -100 ? -100 : e > 100 ? 100 : e;
-}
-
-// Frobenius norm of a matrix from its producer's partials (count of them in
-// meta->nrm, at most cap = the allocated number), summed in a fixed order by
-// wave 0 of the block (every block gets the same value); the result is
-// broadcast through *s_out.
-__device__ __forceinline__ double meta_norm(const MatMeta* m, int cap, double* s_out) {
-  if (threadIdx.x < 64) {
-    const int cnt = m->count < cap ? m->count : cap;
-    double t = 0.0;
-    for (int i = threadIdx.x; i < cnt; i += 64) t += m->nrm[i];
-    t = wave_sum(t);
-    if (threadIdx.x == 0) *s_out = sqrt(t);
-  }
-  __syncthreads();
-  return *s_out;
-}
-
-// Physical 16-byte slot of logical slot ls in LDS row r.  4 slots/row:
-// XOR with (r/4)&3; 6 slots/row: XOR with (r/8)&1.  Either way 16 lanes that
-// read one logical slot of 16 consecutive rows hit 16 distinct 4-bank groups.
-template <int S>
-__device__ __forceinline__ int phys_slot(int r, int ls) {
-  if constexpr (S == 4) return ls ^ ((r >> 2) & 3);
-  else return ls ^ ((r >> 3) & 1);
-}
-template <int S>
-__device__ __forceinline__ int swz(int r, int ls) { return r * (S * 16) + 16 * phys_slot<S>(r, ls); }
 
 __device__ __forceinline__ u32x4 lds16(const LDS_AS char* p) { return *(const LDS_AS u32x4*)p; }
 
@@ -255,17 +152,6 @@ __device__ __forceinline__ void dma_stage_tiled(LDS_AS char* slot, const char* a
     const char* src = (region == 0 ? a0 : region == 1 ? a1 : b) + (j - region * NC) * 1024 + lane * 16;
     __builtin_amdgcn_global_load_lds((const GLB_AS void*)src, (LDS_AS void*)(slot + j * 1024), 16, 0, 0);
   }
-}
-
-// Byte offset of element (r, c), split term `part`, in the tiled operand copy.
-template <int PREC>
-__device__ __forceinline__ size_t op_off(int r, int c, int part, int nst) {
-  constexpr int RB = Fmt<PREC>::RB, S = Fmt<PREC>::S, K = Fmt<PREC>::K, T = Terms<PREC>::T;
-  const int rr = r & (RBLK - 1);
-  const int st = c / K, kk = c % K;
-  const int ls = PREC == kBF16 ? (kk >> 3) : T * (kk >> 3) + part;
-  return ((size_t)(r / RBLK) * nst + st) * (size_t)(RBLK * RB) + (size_t)rr * RB + 16 * phys_slot<S>(rr, ls) +
-         (kk & 7) * 2;
 }
 
 // Operand registers of one stage for one wave.
@@ -432,90 +318,10 @@ __device__ __forceinline__ int step_controller(const StepArgs& a, int* s_code, i
     tr = wave_sum(tr);
     sq = wave_sum(sq);
     eps = wave_sum(eps);
-    if (lane == 0) {
-      Ctl* c = a.ctl;
-      const int k = a.step;
-      int code = 1, m = -1;   // m >= 0: the recursion ends with X_{m+1}
-      if (c->nonfinite) {
-        code = kDecideNonfinite;
-        m = k - 1;
-      } else {
-        if (k >= 2) {
-          // eps of X_{k-1} is this launch's; X_j's was recorded at rec[j]
-          const double e1 = k >= 3 ? c->rec[k - 2].eps : 0.0;
-          const double e2 = k >= 4 ? c->rec[k - 3].eps : 0.0;
-          const double e3 = k >= 5 ? c->rec[k - 4].eps : 0.0;
-          if (sp2_should_stop(eps, e1, e2, e3, k - 2, a.n, a.min_iter, a.idem_tol, a.unit)) {
-            code = kDecideStop;
-            m = k - 2;
-          } else if (k - 2 >= a.max_iter) {
-            code = kDecideNotConverged;
-            m = k - 2;
-          }
-        }
-        if (m < 0) {
-          if (!sp2_bounds_ok(tr, sq, a.n)) {
-            code = kDecideBounds;
-            m = k - 1;
-          } else {
-            code = sp2_sigma(tr, sq, a.nocc);
-          }
-        }
-      }
-      // Sweep stop (ytol2 > 0): the Z-jobs of this launch would form Y_{k+1}
-      // from X_k; once X_{k-1} (the operand of Y_k) is within the tolerance
-      // they are skipped here and in every later launch, and Y_k is the
-      // result.  Every workgroup evaluates the same test on the same eps;
-      // workgroup 0 records k.
-      int zs = 0;
-      if (a.ytol2 > 0.0 && k >= 2 && m < 0) {
-        zs = (c->ystop != 0 || eps <= a.ytol2) ? 1 : 0;
-        if (zs && blockIdx.x == 0 && c->ystop == 0) c->ystop = k;
-      }
-      *s_zskip = zs;
-      if (blockIdx.x == 0) {
-        c->rec[k].tr = tr;
-        c->rec[k].sq = sq;
-        if (k >= 2) c->rec[k - 1].eps = eps;
-        c->rec[k].sigma = m < 0 ? code : 0;
-        if (m >= 0) {
-          c->m = m;
-          c->code = code;
-          __threadfence();
-          c->done = 1;
-        }
-      }
-      *s_code = m < 0 ? code : (code == kDecideStop ? 2 : code);
-    }
+    if (lane == 0) *s_code = step_decide(a, ctl_read(a), tr, sq, eps, blockIdx.x == 0, s_zskip);
   }
   __syncthreads();
   return *s_code;
-}
-
-template <int PREC>
-__device__ __forceinline__ void store_split1(char* oop, int nst, int r, int c, float v, float sc) {
-  constexpr int T = Terms<PREC>::T;
-  unsigned short part[T];
-  split_for<PREC>(v, sc, part);
-#pragma unroll
-  for (int t = 0; t < T; ++t) *(unsigned short*)(oop + op_off<PREC>(r, c, t, nst)) = part[t];
-}
-
-// Operand copy of 8 consecutive columns c0..c0+7 (c0 % 8 == 0) of row r, in
-// the tiled layout: each split term of the group is one 16-byte slot.
-template <int PREC>
-__device__ __forceinline__ void store_group8_t(char* op, int nst, int r, int c0, const float (&v)[8], float sc) {
-  constexpr int T = Terms<PREC>::T;
-  unsigned short part[8][T];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) split_for<PREC>(v[e], sc, part[e]);
-#pragma unroll
-  for (int t = 0; t < T; ++t) {
-    u32x4 w;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) w[e] = part[2 * e][t] | ((unsigned)part[2 * e + 1][t] << 16);
-    *(u32x4*)(op + op_off<PREC>(r, c0, t, nst)) = w;
-  }
 }
 
 // s_getreg operand for the 32-bit HW_REG_XCC_ID register (id 20): the XCD a
@@ -1672,7 +1478,7 @@ hipError_t launch_gemm_op(int prec, const void* A, const void* B, float* C, int 
 
 // dst (n_pad x n_pad, zero padded) = src (n x n, row-major, ld n), or its
 // transpose; one 64 x 64 block per workgroup, transposed through LDS.
-__global__ __launch_bounds__(256) void k_pad(const float* src, int n, int n_pad, float* dst, int transpose) {
+__global__ __launch_bounds__(256) void k_pad(const float* src, int n, int n_pad, float* dst, int transpose, int tiled) {
   __shared__ float tile[64][65];
   const int bi = blockIdx.y, bj = blockIdx.x;          // output block
   const int si = transpose ? bj : bi, sj = transpose ? bi : bj;
@@ -1682,15 +1488,25 @@ __global__ __launch_bounds__(256) void k_pad(const float* src, int n, int n_pad,
     tile[r][c] = (gi < n && gj < n) ? src[(size_t)gi * n + gj] : 0.0f;
   }
   __syncthreads();
+  if (tiled) {
+    for (int e = threadIdx.x; e < 64 * 16; e += 256) {
+      const int r = e & 63, c = 4 * (e >> 6);
+      f32x4 v;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = transpose ? tile[c + k][r] : tile[r][c + k];
+      *(f32x4*)(dst + m_off(1, bi * 64 + r, bj * 64 + c, n_pad)) = v;
+    }
+    return;
+  }
   for (int e = threadIdx.x; e < 64 * 64; e += 256) {
     const int r = e >> 6, c = e & 63;
     dst[(size_t)(bi * 64 + r) * n_pad + bj * 64 + c] = transpose ? tile[c][r] : tile[r][c];
   }
 }
 
-hipError_t launch_pad(const float* src, int n, int n_pad, float* dst, int transpose, hipStream_t s) {
+hipError_t launch_pad(const float* src, int n, int n_pad, float* dst, int transpose, int tiled, hipStream_t s) {
   const int nb = n_pad / 64;
-  hipLaunchKernelGGL(k_pad, dim3(nb, nb), dim3(256), 0, s, src, n, n_pad, dst, transpose);
+  hipLaunchKernelGGL(k_pad, dim3(nb, nb), dim3(256), 0, s, src, n, n_pad, dst, transpose, tiled);
   return hipGetLastError();
 }
 
@@ -1937,18 +1753,18 @@ hipError_t launch_lanczos_step(const float* h, int n, double* v, double* vprev, 
 // ---------------------------------------------------------------- operand copies
 
 __device__ __forceinline__ void store_group8(int prec, char* op, int n_pad, int r, int c0, const float (&v)[8],
-                                             float sc) {
-  if (prec == kSplit2) store_group8_t<kSplit2>(op, n_pad / Fmt<kSplit2>::K, r, c0, v, sc);
-  else if (prec == kSplit3) store_group8_t<kSplit3>(op, n_pad / Fmt<kSplit3>::K, r, c0, v, sc);
-  else if (prec == kBF16) store_group8_t<kBF16>(op, n_pad / Fmt<kBF16>::K, r, c0, v, sc);
-  else if (prec == kSplitH) store_group8_t<kSplitH>(op, n_pad / Fmt<kSplitH>::K, r, c0, v, sc);
+                                             float sc, int small) {
+  if (prec == kSplit2) store_group8_t<kSplit2>(op, n_pad / Fmt<kSplit2>::K, r, c0, v, sc, small);
+  else if (prec == kSplit3) store_group8_t<kSplit3>(op, n_pad / Fmt<kSplit3>::K, r, c0, v, sc, small);
+  else if (prec == kBF16) store_group8_t<kBF16>(op, n_pad / Fmt<kBF16>::K, r, c0, v, sc, small);
+  else if (prec == kSplitH) store_group8_t<kSplitH>(op, n_pad / Fmt<kSplitH>::K, r, c0, v, sc, small);
 }
 
 // Rebuild the operand copy of nmat matrices from their FP32 masters.  For
 // kSplitH (used for the Y matrices written by k_init) the scale comes from
 // the matrix's own norm partials: |M_ij| <= ||M||_F, and block (0, z) records
 // the exponent in the matrix's metadata.
-__global__ __launch_bounds__(256) void k_resplit(int prec, MatRef m, int n_pad) {
+__global__ __launch_bounds__(256) void k_resplit(int prec, MatRef m, int n_pad, int tiled) {
   __shared__ double s_nrm;
   const int z = blockIdx.y;
   const float* src = m.f32 + (size_t)z * m.stride_f32;
@@ -1962,12 +1778,13 @@ __global__ __launch_bounds__(256) void k_resplit(int prec, MatRef m, int n_pad) 
   }
   const size_t ngroups = (size_t)n_pad * n_pad / 8;
   for (size_t g = (size_t)blockIdx.x * 256 + threadIdx.x; g < ngroups; g += (size_t)gridDim.x * 256) {
-    const size_t r = g / (n_pad / 8);
-    const int c0 = (int)(g % (n_pad / 8)) * 8;
-    const f32x4 a = *(const f32x4*)(src + r * n_pad + c0);
-    const f32x4 b = *(const f32x4*)(src + r * n_pad + c0 + 4);
+    // tiled: consecutive lanes take consecutive rows of one column group
+    const int r = tiled ? (int)(g % n_pad) : (int)(g / (n_pad / 8));
+    const int c0 = (tiled ? (int)(g / n_pad) : (int)(g % (n_pad / 8))) * 8;
+    const f32x4 a = *(const f32x4*)(src + m_off(tiled, r, c0, n_pad));
+    const f32x4 b = *(const f32x4*)(src + m_off(tiled, r, c0 + 4, n_pad));
     const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-    store_group8(prec, dst, n_pad, (int)r, c0, v, sc);
+    store_group8(prec, dst, n_pad, r, c0, v, sc, tiled);
   }
 }
 
@@ -1993,28 +1810,39 @@ hipError_t launch_split_copy(const float* src, void* dst, int n_pad, int e, hipS
 // n_src x n_src row-major FP32 matrix (n_src <= n_pad), scaled by sc
 // (kSplitH; a power of two).
 template <int F>
-__global__ __launch_bounds__(256) void k_copy_src(const float* src, int n_src, char* dst, int n_pad, float sc) {
+__global__ __launch_bounds__(256) void k_copy_src(const float* src, int n_src, char* dst, int n_pad, float sc, int tiled, int small) {
   const size_t ngroups = (size_t)n_pad * n_pad / 8;
   for (size_t g = (size_t)blockIdx.x * 256 + threadIdx.x; g < ngroups; g += (size_t)gridDim.x * 256) {
-    const int r = (int)(g / (n_pad / 8));
-    const int c0 = (int)(g % (n_pad / 8)) * 8;
+    const int r = small ? (int)(g % n_pad) : (int)(g / (n_pad / 8));
+    const int c0 = (small ? (int)(g / n_pad) : (int)(g % (n_pad / 8))) * 8;
     float v[8];
+    if (tiled) {   // n_src == n_pad
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int c = c0 + e;
-      v[e] = (r < n_src && c < n_src) ? src[(size_t)r * n_src + c] : 0.0f;
+      for (int k = 0; k < 2; ++k) {
+        const f32x4 x = *(const f32x4*)(src + m_off(1, r, c0 + 4 * k, n_pad));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * k + e] = x[e];
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int c = c0 + e;
+        v[e] = (r < n_src && c < n_src) ? src[(size_t)r * n_src + c] : 0.0f;
+      }
     }
-    store_group8_t<F>(dst, n_pad / Fmt<F>::K, r, c0, v, sc);
+    store_group8_t<F>(dst, n_pad / Fmt<F>::K, r, c0, v, sc, small);
   }
 }
 
-hipError_t launch_copy_src(int prec, const float* src, int n_src, void* dst, int n_pad, int e, hipStream_t s) {
+hipError_t launch_copy_src(int prec, const float* src, int n_src, void* dst, int n_pad, int e, int tiled, int small,
+                           hipStream_t s) {
   const float sc = ldexpf(1.0f, e);
+  if (tiled && n_src != n_pad) return hipErrorInvalidValue;
   switch (prec) {
-    case kSplitH: hipLaunchKernelGGL(k_copy_src<kSplitH>, dim3(2048), dim3(256), 0, s, src, n_src, (char*)dst, n_pad, sc); break;
-    case kSplit3: hipLaunchKernelGGL(k_copy_src<kSplit3>, dim3(2048), dim3(256), 0, s, src, n_src, (char*)dst, n_pad, sc); break;
-    case kSplit2: hipLaunchKernelGGL(k_copy_src<kSplit2>, dim3(2048), dim3(256), 0, s, src, n_src, (char*)dst, n_pad, sc); break;
-    case kBF16: hipLaunchKernelGGL(k_copy_src<kBF16>, dim3(2048), dim3(256), 0, s, src, n_src, (char*)dst, n_pad, sc); break;
+    case kSplitH: hipLaunchKernelGGL(k_copy_src<kSplitH>, dim3(2048), dim3(256), 0, s, src, n_src, (char*)dst, n_pad, sc, tiled, small); break;
+    case kSplit3: hipLaunchKernelGGL(k_copy_src<kSplit3>, dim3(2048), dim3(256), 0, s, src, n_src, (char*)dst, n_pad, sc, tiled, small); break;
+    case kSplit2: hipLaunchKernelGGL(k_copy_src<kSplit2>, dim3(2048), dim3(256), 0, s, src, n_src, (char*)dst, n_pad, sc, tiled, small); break;
+    case kBF16: hipLaunchKernelGGL(k_copy_src<kBF16>, dim3(2048), dim3(256), 0, s, src, n_src, (char*)dst, n_pad, sc, tiled, small); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -2044,30 +1872,37 @@ hipError_t launch_norm2(const float* src, size_t count, double* part, hipStream_
 // R = W - W^T with W = V1 + V2 (n_pad x n_pad FP32, V2 nullable), written
 // only as the plain BF16 operand copy (tiled layout).  One 64 x 64 block per
 // workgroup; the block and its transposed partner are staged through LDS.
-__global__ __launch_bounds__(256) void k_antisym_bf16(const float* v1, const float* v2, int n_pad, char* dst) {
+__global__ __launch_bounds__(256) void k_antisym_bf16(const float* v1, const float* v2, int n_pad, char* dst, int tiled) {
   __shared__ float t[64][65];
   __shared__ float tt[64][65];
   const int bi = blockIdx.y, bj = blockIdx.x;
-  for (int e = threadIdx.x; e < 64 * 64; e += 256) {
-    const int r = e >> 6, c = e & 63;
-    const size_t o = (size_t)(bi * 64 + r) * n_pad + bj * 64 + c;
-    const size_t ot = (size_t)(bj * 64 + r) * n_pad + bi * 64 + c;
-    t[r][c] = v1[o] + (v2 ? v2[o] : 0.0f);
-    tt[r][c] = v1[ot] + (v2 ? v2[ot] : 0.0f);
+  for (int e = threadIdx.x; e < 64 * 16; e += 256) {
+    const int r = tiled ? e & 63 : e >> 4, c = 4 * (tiled ? e >> 6 : e & 15);
+    const size_t o = m_off(tiled, bi * 64 + r, bj * 64 + c, n_pad), ot = m_off(tiled, bj * 64 + r, bi * 64 + c, n_pad);
+    f32x4 x = *(const f32x4*)(v1 + o), y = *(const f32x4*)(v1 + ot);
+    if (v2) {
+      x += *(const f32x4*)(v2 + o);
+      y += *(const f32x4*)(v2 + ot);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      t[r][c + k] = x[k];
+      tt[r][c + k] = y[k];
+    }
   }
   __syncthreads();
   for (int g = threadIdx.x; g < 64 * 8; g += 256) {
-    const int r = g >> 3, c0 = (g & 7) * 8;
+    const int r = g & 63, c0 = (g >> 6) * 8;
     float v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = t[r][c0 + e] - tt[c0 + e][r];
-    store_group8_t<kBF16>(dst, n_pad / Fmt<kBF16>::K, bi * 64 + r, bj * 64 + c0, v, 1.0f);
+    store_group8_t<kBF16>(dst, n_pad / Fmt<kBF16>::K, bi * 64 + r, bj * 64 + c0, v, 1.0f, tiled);
   }
 }
 
-hipError_t launch_antisym_bf16(const float* v1, const float* v2, int n_pad, void* dst, hipStream_t s) {
+hipError_t launch_antisym_bf16(const float* v1, const float* v2, int n_pad, void* dst, int tiled, hipStream_t s) {
   const int nb = n_pad / 64;
-  hipLaunchKernelGGL(k_antisym_bf16, dim3(nb, nb), dim3(256), 0, s, v1, v2, n_pad, (char*)dst);
+  hipLaunchKernelGGL(k_antisym_bf16, dim3(nb, nb), dim3(256), 0, s, v1, v2, n_pad, (char*)dst, tiled);
   return hipGetLastError();
 }
 
@@ -2095,7 +1930,7 @@ hipError_t launch_add_into(float* y, size_t ys, const float* d, size_t ds, int n
 // scale b's metadata records (kSplitH) and b's norm partials replaced by one
 // FP64 partial of ||b||_F^2 per 64 x 64 block.  Grid (n_pad / 64,
 // n_pad / 64, observables).
-__global__ __launch_bounds__(256) void k_reflect(int prec, MatRef a, MatRef b, int n_pad) {
+__global__ __launch_bounds__(256) void k_reflect(int prec, MatRef a, MatRef b, int n_pad, int tiled) {
   __shared__ double s_red[4];
   const int z = blockIdx.z, bi = blockIdx.y, bj = blockIdx.x, nb = gridDim.x;
   const float* ya = a.f32 + (size_t)z * a.stride_f32;
@@ -2105,10 +1940,10 @@ __global__ __launch_bounds__(256) void k_reflect(int prec, MatRef a, MatRef b, i
   const float sc = prec == kSplitH ? ldexpf(1.0f, mm->scale) : 1.0f;
   double sq = 0.0;
   for (int g = threadIdx.x; g < 64 * 8; g += 256) {
-    const int r = bi * 64 + (g >> 3), c0 = bj * 64 + (g & 7) * 8;
-    const size_t o = (size_t)r * n_pad + c0;
-    const f32x4 a0 = *(const f32x4*)(ya + o), a1 = *(const f32x4*)(ya + o + 4);
-    const f32x4 b0 = *(const f32x4*)(yb + o), b1 = *(const f32x4*)(yb + o + 4);
+    const int r = bi * 64 + (tiled ? g & 63 : g >> 3), c0 = bj * 64 + (tiled ? g >> 6 : g & 7) * 8;
+    const size_t o = m_off(tiled, r, c0, n_pad), o4 = m_off(tiled, r, c0 + 4, n_pad);
+    const f32x4 a0 = *(const f32x4*)(ya + o), a1 = *(const f32x4*)(ya + o4);
+    const f32x4 b0 = *(const f32x4*)(yb + o), b1 = *(const f32x4*)(yb + o4);
     float v[8];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -2116,8 +1951,8 @@ __global__ __launch_bounds__(256) void k_reflect(int prec, MatRef a, MatRef b, i
       v[4 + e] = 2.0f * a1[e] - b1[e];
     }
     *(f32x4*)(yb + o) = f32x4{v[0], v[1], v[2], v[3]};
-    *(f32x4*)(yb + o + 4) = f32x4{v[4], v[5], v[6], v[7]};
-    if (prec != kFP32) store_group8(prec, op, n_pad, r, c0, v, sc);
+    *(f32x4*)(yb + o4) = f32x4{v[4], v[5], v[6], v[7]};
+    if (prec != kFP32) store_group8(prec, op, n_pad, r, c0, v, sc, tiled);
 #pragma unroll
     for (int e = 0; e < 8; ++e) sq += (double)v[e] * (double)v[e];
   }
@@ -2130,15 +1965,15 @@ __global__ __launch_bounds__(256) void k_reflect(int prec, MatRef a, MatRef b, i
   }
 }
 
-hipError_t launch_reflect(int prec, MatRef a, MatRef b, int n_pad, int nmat, hipStream_t s) {
+hipError_t launch_reflect(int prec, MatRef a, MatRef b, int n_pad, int nmat, int tiled, hipStream_t s) {
   if (nmat <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_reflect, dim3(n_pad / 64, n_pad / 64, nmat), dim3(256), 0, s, prec, a, b, n_pad);
+  hipLaunchKernelGGL(k_reflect, dim3(n_pad / 64, n_pad / 64, nmat), dim3(256), 0, s, prec, a, b, n_pad, tiled);
   return hipGetLastError();
 }
 
-hipError_t launch_resplit(int prec, MatRef m, int n_pad, int nmat, hipStream_t s) {
+hipError_t launch_resplit(int prec, MatRef m, int n_pad, int nmat, int tiled, hipStream_t s) {
   if (prec == kFP32 || nmat <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_resplit, dim3(1024, nmat), dim3(256), 0, s, prec, m, n_pad);
+  hipLaunchKernelGGL(k_resplit, dim3(1024, nmat), dim3(256), 0, s, prec, m, n_pad, tiled);
   return hipGetLastError();
 }
 
@@ -2153,7 +1988,7 @@ hipError_t launch_resplit(int prec, MatRef m, int n_pad, int nmat, hipStream_t s
 // block its own in a fixed order.
 __device__ __forceinline__ void init_block(int prec, const float (*p)[65], const float (*q)[65], int bi, int bj,
                                            int nb, int n, int n_pad, int z, const MatRef& x, const MatRef& y,
-                                           double y_scale_mode, Part* part, const Ctl* ctl, double* s_red) {
+                                           double y_scale_mode, Part* part, const Ctl* ctl, double* s_red, int tiled) {
   // output block (bi, bj): element (r, c) = (p[r][c] + q[c][r]) / 2, p the
   // source block (bi, bj), q the source block (bj, bi)
   const int t = threadIdx.x;
@@ -2173,7 +2008,7 @@ __device__ __forceinline__ void init_block(int prec, const float (*p)[65], const
   double tr = 0.0, sq = 0.0;
   // each thread: 2 groups of 8 consecutive columns
   for (int gidx = t; gidx < 64 * 8; gidx += 256) {
-    const int r = gidx >> 3, cg = (gidx & 7) * 8;
+    const int r = tiled ? gidx & 63 : gidx >> 3, cg = (tiled ? gidx >> 6 : gidx & 7) * 8;
     const int gi = bi * 64 + r;
     float v[8];
 #pragma unroll
@@ -2191,11 +2026,10 @@ __device__ __forceinline__ void init_block(int prec, const float (*p)[65], const
       sq += d * d;
       if (z == 0 && gi == gj) tr += d;
     }
-    float* dst = o32 + (size_t)gi * n_pad + bj * 64 + cg;
-    *(f32x4*)dst = f32x4{v[0], v[1], v[2], v[3]};
-    *(f32x4*)(dst + 4) = f32x4{v[4], v[5], v[6], v[7]};
-    if (!ycopy_later) store_group8(fmt, oop, n_pad, gi, bj * 64 + cg, v, sc);
-    if (oop2) store_group8(kSplit2, oop2, n_pad, gi, bj * 64 + cg, v, 1.0f);
+    *(f32x4*)(o32 + m_off(tiled, gi, bj * 64 + cg, n_pad)) = f32x4{v[0], v[1], v[2], v[3]};
+    *(f32x4*)(o32 + m_off(tiled, gi, bj * 64 + cg + 4, n_pad)) = f32x4{v[4], v[5], v[6], v[7]};
+    if (!ycopy_later) store_group8(fmt, oop, n_pad, gi, bj * 64 + cg, v, sc, tiled);
+    if (oop2) store_group8(kSplit2, oop2, n_pad, gi, bj * 64 + cg, v, 1.0f, tiled);
   }
   if (ycopy_later) {
     sq = wave_sum(sq);
@@ -2230,7 +2064,7 @@ __device__ __forceinline__ void init_block(int prec, const float (*p)[65], const
 
 __global__ __launch_bounds__(256) void k_init(int prec, const float* h, const float* a, int n,
                                               int n_pad, int zoff, MatRef x, MatRef y,
-                                              double y_scale_mode, Part* part, Ctl* ctl) {
+                                              double y_scale_mode, Part* part, Ctl* ctl, int tiled) {
   __shared__ float tile[64][65];    // block (bi, bj) of the source
   __shared__ float tileT[64][65];   // block (bj, bi) of the source
   __shared__ double s_red[8];
@@ -2261,22 +2095,21 @@ __global__ __launch_bounds__(256) void k_init(int prec, const float* h, const fl
   if (bad) ctl->nonfinite = 1;
   __syncthreads();
   if (bi == bj) {
-    init_block(prec, tile, tile, bi, bj, nb, n, n_pad, z, x, y, y_scale_mode, part, ctl, s_red);
+    init_block(prec, tile, tile, bi, bj, nb, n, n_pad, z, x, y, y_scale_mode, part, ctl, s_red, tiled);
   } else {
-    init_block(prec, tile, tileT, bi, bj, nb, n, n_pad, z, x, y, y_scale_mode, part, ctl, s_red);
-    init_block(prec, tileT, tile, bj, bi, nb, n, n_pad, z, x, y, y_scale_mode, part, ctl, s_red);
+    init_block(prec, tile, tileT, bi, bj, nb, n, n_pad, z, x, y, y_scale_mode, part, ctl, s_red, tiled);
+    init_block(prec, tileT, tile, bj, bi, nb, n, n_pad, z, x, y, y_scale_mode, part, ctl, s_red, tiled);
   }
 }
 
 // nobs >= 0: X_1 and nobs observables; nobs < 0: only the -nobs observables.
-hipError_t launch_init(int prec, int /*tile*/, const float* h, const float* a, int n, int n_pad,
-                       int nobs, const uint32_t* /*jobs*/, int /*njobs*/, MatRef x, MatRef y,
-                       double y_scale_mode, Part* part, Ctl* ctl, hipStream_t s) {
+hipError_t launch_init(int prec, int tiled, const float* h, const float* a, int n, int n_pad, int nobs, MatRef x,
+                       MatRef y, double y_scale_mode, Part* part, Ctl* ctl, hipStream_t s) {
   const int nb = n_pad / 64;
   const int zoff = nobs < 0 ? 1 : 0;
   const int nz = nobs < 0 ? -nobs : 1 + nobs;
   hipLaunchKernelGGL(k_init, dim3(nb, nb, nz), dim3(256), 0, s, prec, h, a, n, n_pad, zoff, x, y,
-                     y_scale_mode, part, ctl);
+                     y_scale_mode, part, ctl, tiled);
   return hipGetLastError();
 }
 
@@ -2313,23 +2146,82 @@ __global__ __launch_bounds__(256) void k_output(const float* x32, const float* y
 
 constexpr int kOutBlocks = 1024;
 
+// The same from tiled masters: a thread takes 4 columns of a row; 16 lanes
+// cover 16 rows of one column group (256-byte reads), the wave 4 groups
+// (64-byte row pieces out).  The grid's blocks walk 16-row x 64-column pieces.
+__global__ __launch_bounds__(256) void k_output_tiled(const float* x32, const float* y32, size_t ystride,
+                                                      const float* a, int n, int n_pad, int nobs,
+                                                      float* d_out, float* chi_out, double scale,
+                                                      int scale_by_beta, double* a0_part, Ctl* ctl) {
+  __shared__ double s_red[4];
+  const size_t n2 = (size_t)n * n;
+  const double c = scale * (scale_by_beta ? ctl->beta : 1.0);
+  const int k = blockIdx.y;
+  const int rg = (n + 15) / 16, cg = (n + 15) / 16, pieces = rg * cg;
+  const int lane = threadIdx.x & 63;
+  double acc = 0.0;
+  for (int p = blockIdx.x * 4 + (threadIdx.x >> 6); p < pieces; p += gridDim.x * 4) {
+    const int i = (p / cg) * 16 + (lane & 15), j = (p % cg) * 16 + 4 * (lane >> 4);
+    if (i >= n || j >= n) continue;
+    const size_t o = m_off(1, i, j, n_pad);
+    const f32x4 dv = *(const f32x4*)(x32 + o);
+    const size_t e = (size_t)i * n + j;
+    const int w = n - j < 4 ? n - j : 4;
+    if (k == 0 && d_out)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (q < w) d_out[e + q] = dv[q];
+    if (nobs > 0) {
+      const f32x4 yv = *(const f32x4*)(y32 + (size_t)k * ystride + o);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (q >= w) break;
+        if (chi_out) chi_out[(size_t)k * n2 + e + q] = (float)(c * (double)yv[q]);
+        acc += (double)dv[q] * (double)a[(size_t)k * n2 + e + q];
+      }
+    }
+  }
+  if (nobs > 0 && a0_part) {
+    acc = wave_sum(acc);
+    if (lane == 0) s_red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) a0_part[(size_t)k * gridDim.x + blockIdx.x] = s_red[0] + s_red[1] + s_red[2] + s_red[3];
+  }
+}
+
 hipError_t launch_output(const float* x32, const float* y32, size_t ystride, const float* a, int n,
                          int n_pad, int nobs, float* d_out, float* chi_out, double scale,
-                         int scale_by_beta, const uint32_t*, int, int, double* a0_part, Ctl* ctl,
-                         hipStream_t s) {
+                         int scale_by_beta, int tiled, double* a0_part, Ctl* ctl, hipStream_t s) {
+  if (tiled) {
+    hipLaunchKernelGGL(k_output_tiled, dim3(kOutBlocks, nobs > 0 ? nobs : 1), dim3(256), 0, s, x32, y32,
+                       ystride, a, n, n_pad, nobs, d_out, chi_out, scale, scale_by_beta, a0_part, ctl);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_output, dim3(kOutBlocks, nobs > 0 ? nobs : 1), dim3(256), 0, s, x32, y32,
                      ystride, a, n, n_pad, nobs, d_out, chi_out, scale, scale_by_beta, a0_part, ctl);
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_copy_out(const float* src, int n, int n_pad, float* dst) {
+__global__ __launch_bounds__(256) void k_copy_out(const float* src, int n, int n_pad, float* dst, int tiled) {
   const size_t n2 = (size_t)n * n;
+  if (tiled) {   // as k_output_tiled
+    const int cg = (n + 15) / 16, pieces = cg * cg, lane = threadIdx.x & 63;
+    for (int p = blockIdx.x * 4 + (threadIdx.x >> 6); p < pieces; p += gridDim.x * 4) {
+      const int i = (p / cg) * 16 + (lane & 15), j = (p % cg) * 16 + 4 * (lane >> 4);
+      if (i >= n || j >= n) continue;
+      const f32x4 v = *(const f32x4*)(src + m_off(1, i, j, n_pad));
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (j + q < n) dst[(size_t)i * n + j + q] = v[q];
+    }
+    return;
+  }
   for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n2; e += (size_t)gridDim.x * 256)
     dst[e] = src[(e / n) * n_pad + e % n];
 }
 
-hipError_t launch_copy_out(const float* src, int n, int n_pad, float* dst, hipStream_t s) {
-  hipLaunchKernelGGL(k_copy_out, dim3(kOutBlocks), dim3(256), 0, s, src, n, n_pad, dst);
+hipError_t launch_copy_out(const float* src, int n, int n_pad, float* dst, int tiled, hipStream_t s) {
+  hipLaunchKernelGGL(k_copy_out, dim3(kOutBlocks), dim3(256), 0, s, src, n, n_pad, dst, tiled);
   return hipGetLastError();
 }
 

@@ -1,0 +1,627 @@
+// gfx950 kernels of the matrix products at small sizes: the same SP2 /
+// susceptibility step and general product as dmpt_kernels.hip on square tiles
+// of 64 (or 32) with the K range split over the waves of a workgroup.
+//
+// The 256 x 128 tiles of the large-size kernels leave most of the chip idle
+// when the matrix is small: n = 1000 has 20 of them per product on 256 CUs,
+// and a launch then takes as long as one tile's serial K loop.  Here a
+// workgroup owns one TS x TS tile and each of its waves forms the whole tile
+// over its own part of the K range, so a tile's loop is NWV times shorter and
+// there are 8 times as many tiles.  Waves share no operand bytes (different k),
+// so operands go straight from memory to registers: no LDS ring, no barrier in
+// the loop, D stages in flight.  The partial sums meet in LDS (added in
+// FP64, in wave order), and the workgroup runs the tile's epilogue.
+//
+// What bounds it, and what it measured (one step of one observable, us; the
+// 256 x 128 tiles before): n = 128 FP32 77 -> 7.8, of which the chain of a few
+// dependent memory round trips (operands and partials, the current matrix, the
+// stores) and the launch; n = 1000 FP32 248 -> 51, FP16 split 86 -> 29; n = 2048
+// FP32 562 -> 276, FP16 split 162 -> 114.  From n = 1000 on the operand loads
+// bound the split formats (n = 2048: 0.9 GB of operands a launch; the same loop
+// without its MFMAs takes as long) and the FP32 MFMAs the FP32 ones (0.6 of
+// their peak at n = 2048).  Loads in the order of the 128-row chunks of the
+// large-size kernels (half of each 128-byte line per instruction) ran at 14.8,
+// in the layout here at 22 TB/s; FP32 rows of a row-major matrix slower still.
+//
+// n_pad is a multiple of 64 on this path, and the FP32 masters and operand
+// copies are laid out for these loads (m_off, op_off in dmpt_device.h).
+#include <hip/hip_runtime.h>
+
+#include "dmpt_device.h"
+#include "dmpt_internal.h"
+#include "sp2_rule.h"
+
+namespace dmpt {
+
+namespace {
+
+// ---------------------------------------------------------------- operand loads and products
+
+// 16-byte operand registers of one stage: Q per 32 rows of A and of B.
+template <int PREC> struct SFmt {
+  static constexpr int Q = PREC == kSplit3 ? 3 : 2;
+  static constexpr int D = PREC == kFP32 ? 4 : PREC == kSplit3 ? 2 : 3;   // stages in registers
+  static constexpr int BLK = 32 * Fmt<PREC>::RB;   // bytes of a 32-row block of one stage
+};
+template <int PREC, int BA, int B> struct SOps { u32x4 a[BA][SFmt<PREC>::Q], b[B][SFmt<PREC>::Q]; };
+
+// Byte offset of row r0 (a multiple of 32), stage 0 of an operand copy.
+template <int PREC>
+__device__ __forceinline__ size_t panel_off(int r0, int n_pad) { return (size_t)r0 * n_pad * operand_bytes(PREC); }
+
+// One stage's operands: 32-row group i of a panel starts i * rstep bytes on;
+// within a group's block register q of lane l is the 16 bytes at 1024 q + 16 l
+// (row l % 32; split: k-group l / 32 of term q; BF16: k16 step q; FP32: columns
+// 8 q + 4 (l / 32), the same k permutation on A and B).
+template <int PREC, int BA, int B>
+__device__ __forceinline__ void s_load(SOps<PREC, BA, B>& o, const char* pa, const char* pb, size_t rstep,
+                                       uint32_t off) {
+#pragma unroll
+  for (int i = 0; i < BA; ++i)
+#pragma unroll
+    for (int q = 0; q < SFmt<PREC>::Q; ++q) o.a[i][q] = *(const u32x4*)(pa + i * rstep + q * 1024 + off);
+#pragma unroll
+  for (int i = 0; i < B; ++i)
+#pragma unroll
+    for (int q = 0; q < SFmt<PREC>::Q; ++q) o.b[i][q] = *(const u32x4*)(pb + i * rstep + q * 1024 + off);
+}
+
+// acc[i][j] += A_i B_j^T for one stage; the products and their order are those
+// of the large-size kernels (split-3: mm, hl, lh, hm, mh, hh; two terms: hl, lh, hh).
+// The blocks are taken in the order F, F + 1, ... (FP32 flushes block F after it).
+template <int PREC, int BA, int B, int F>
+__device__ __forceinline__ void s_mma(const SOps<PREC, BA, B>& o, f32x16 (&acc)[BA][B]) {
+#pragma unroll
+  for (int t = 0; t < BA * B; ++t) {
+    const int blk = (F + t) % (BA * B), i = blk / B, j = blk % B;
+    f32x16 c = acc[i][j];
+    if constexpr (PREC == kFP32) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const f32x4 x = __builtin_bit_cast(f32x4, o.a[i][q]), y = __builtin_bit_cast(f32x4, o.b[j][q]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], c, 0, 0, 0);
+      }
+    } else if constexpr (PREC == kSplitH) {
+      constexpr int pa[3] = {0, 1, 0}, pb[3] = {1, 0, 0};
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, o.a[i][pa[q]]),
+                                                   __builtin_bit_cast(f16x8, o.b[j][pb[q]]), c, 0, 0, 0);
+    } else {
+      constexpr int np = PREC == kSplit3 ? 6 : PREC == kSplit2 ? 3 : 2;
+      constexpr int pa3[6] = {1, 0, 2, 0, 1, 0}, pb3[6] = {1, 2, 0, 1, 0, 0};
+      constexpr int pa2[3] = {0, 1, 0}, pb2[3] = {1, 0, 0};
+#pragma unroll
+      for (int q = 0; q < np; ++q) {
+        const int pa = PREC == kSplit3 ? pa3[q] : PREC == kSplit2 ? pa2[q % 3] : q;
+        const int pb = PREC == kSplit3 ? pb3[q] : PREC == kSplit2 ? pb2[q % 3] : q;
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, o.a[i][pa]),
+                                                    __builtin_bit_cast(bf16x8, o.b[j][pb]), c, 0, 0, 0);
+      }
+    }
+    acc[i][j] = c;
+  }
+}
+
+// W waves: KP parts of the K range x WR row parts of the tile.  FP32 keeps
+// FP64 partial sums beside its accumulators: at TS = 64 a wave takes 32 rows.
+template <int PREC, int B, int W> struct SGeo {
+  static constexpr int NWV = W, NTH = NWV * 64;
+  static constexpr int WR = PREC == kFP32 ? B : 1, KP = NWV / WR, BA = B / WR;
+  static constexpr int TS = 32 * B, LS = TS + 1;
+  using P = typename std::conditional<PREC == kFP32, double, float>::type;
+  static constexpr int SUMS = KP * B * B * 16 * 64 * (int)sizeof(P);
+  static constexpr int PART = SUMS > TS * LS * 4 ? SUMS : TS * LS * 4;   // the tile takes the sums' place
+  static constexpr int VX = (TS * TS / 4 + NTH - 1) / NTH;   // 16-byte pieces of the tile per thread
+};
+
+// This wave's part of the tile sum over stages [0, nst) of the K stream: stages
+// below spass come from panels (a0, b0), the rest from (a1, b1).  Adds the
+// waves' sums in `part` and leaves the tile (times the scales) there, row stride LS.
+// Two-level accumulation as in the large-size kernels: FP32 operands go into
+// FP64 sums every 4 stages, the split formats into a second FP32 level every
+// 4 x flush stages (within the wave's range); the waves' sums add in FP64.
+// ov runs while the first loads are in flight (false: leave, in every thread
+// alike); pre runs before the partial sums are exchanged.
+template <int PREC, int B, int W, class Ov, class Pre>
+__device__ __forceinline__ bool tile_sum(const char* a0, const char* b0, const char* a1, const char* b1, int spass,
+                                         int nst, int n_pad, int flush, float scale, float scale2, LDS_AS char* part_,
+                                         int wave, int lane, Ov ov, Pre pre) {
+  using G = SGeo<PREC, B, W>;
+  constexpr int D = SFmt<PREC>::D, BA = G::BA, NB = BA * B;
+  const int h = lane >> 5, l32 = lane & 31;
+  const int kp = wave / G::WR, wr = wave % G::WR;
+  const size_t step_b = SFmt<PREC>::BLK, rstep = (size_t)32 * n_pad * operand_bytes(PREC);
+  const uint32_t off = 16u * (uint32_t)lane;
+  const int per = (nst + G::KP - 1) / G::KP;
+  const int s0 = kp * per;
+  const int cnt = s0 >= nst ? 0 : (nst - s0 < per ? nst - s0 : per);
+  const size_t arow = (size_t)(wr * BA) * rstep;
+  auto load = [&](SOps<PREC, BA, B>& o, int s) {   // past the end: the last stage again (never multiplied)
+    const int sc = s < nst ? s : nst - 1;
+    const bool first = sc < spass;
+    const size_t ko = (size_t)(first ? sc : sc - spass) * step_b;
+    s_load<PREC, BA, B>(o, (first ? a0 : a1) + ko + arow, (first ? b0 : b1) + ko, rstep, off);
+  };
+  SOps<PREC, BA, B> o[D];
+  f32x16 acc[BA][B];
+#pragma unroll
+  for (int q = 0; q < NB; ++q) acc[q / B][q % B] = f32x16{0};
+#pragma unroll
+  for (int d = 0; d < D - 1; ++d) load(o[d], s0 + d);
+  __builtin_amdgcn_sched_barrier(0);
+  if (!ov()) return false;
+  LDS_AS typename G::P* part = (LDS_AS typename G::P*)part_;
+  const int pbase = (kp * B * B + wr * NB) * 16;   // this wave's first register row of the exchange
+  if constexpr (PREC == kFP32) {
+    double td[NB][16];
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) td[q][e] = 0.0;
+    // each block goes into its FP64 sum once in 4 stages, the blocks at different ones:
+    // no FP32 chain is longer than 4 stages
+#define DMPT_SSTAGE(K)                                                              \
+  {                                                                                 \
+    load(o[((K) + D - 1) % D], s0 + s + (K) + D - 1);                               \
+    __builtin_amdgcn_sched_barrier(0);                                              \
+    if (s + (K) < cnt) {                                                            \
+      constexpr int blk = (K) * NB / 4;                                             \
+      s_mma<PREC, BA, B, blk>(o[K], acc);                                           \
+      if ((K) % (4 / NB) == 4 / NB - 1) {                                                 \
+        _Pragma("unroll") for (int e = 0; e < 16; ++e) td[blk][e] += (double)acc[blk / B][blk % B][e]; \
+        acc[blk / B][blk % B] = f32x16{0};                                          \
+      }                                                                             \
+    }                                                                               \
+  }
+    for (int s = 0; s < cnt; s += 4) {
+      DMPT_SSTAGE(0)
+      DMPT_SSTAGE(1)
+      DMPT_SSTAGE(2)
+      DMPT_SSTAGE(3)
+    }
+#undef DMPT_SSTAGE
+    pre();
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) part[(pbase + q * 16 + e) * 64 + lane] = td[q][e] + (double)acc[q / B][q % B][e];
+  } else {
+    f32x16 tot[BA][B];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) tot[q / B][q % B] = f32x16{0};
+    const int fl = flush > 0 ? 4 * flush : 1 << 30;
+    int since = 0;
+    for (int s = 0; s < cnt; s += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        load(o[(d + D - 1) % D], s0 + s + d + D - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s + d < cnt) {
+          s_mma<PREC, BA, B, 0>(o[d], acc);
+          if (++since == fl) {
+            since = 0;
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+              tot[q / B][q % B] += acc[q / B][q % B];
+              acc[q / B][q % B] = f32x16{0};
+            }
+          }
+        }
+      }
+    }
+    pre();
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) part[(pbase + q * 16 + e) * 64 + lane] = tot[q / B][q % B][e] + acc[q / B][q % B][e];
+  }
+  __syncthreads();
+  // register e of a 32 x 32 block: row 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32
+  constexpr int PER = B * B * 16 / G::NWV;
+  float f[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int idx = wave * PER + k;
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < G::KP; ++w) v += (double)part[(w * B * B * 16 + idx) * 64 + lane];
+    f[k] = (float)v;
+    f[k] *= scale;
+    f[k] *= scale2;
+  }
+  __syncthreads();   // the sums are read: the tile takes their place
+  LDS_AS float* T = (LDS_AS float*)part_;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int idx = wave * PER + k, q = idx >> 4, e = idx & 15;
+    T[((q / B) * 32 + 8 * (e >> 2) + 4 * h + (e & 3)) * G::LS + (q % B) * 32 + l32] = f[k];
+  }
+  return true;
+}
+
+// Tile t of the upper triangle (J >= I) of an nt x nt grid: bands of 4 tile
+// rows, first the band's own triangle, then its columns from left to right,
+// so that a run of tiles shares few row panels.
+__device__ __forceinline__ void tri_tile(int t, int nt, int* ti, int* tj) {
+  const float m = (float)nt + 0.5f;
+  int i = (int)(m - sqrtf(m * m - 2.0f * (float)t));
+  i = i < 0 ? 0 : i > nt - 1 ? nt - 1 : i;
+  while (i > 0 && i * nt - i * (i - 1) / 2 > t) --i;
+  while (i + 1 < nt && (i + 1) * nt - (i + 1) * i / 2 <= t) ++i;
+  const int r0 = i & ~3, hb = nt - r0 < 4 ? nt - r0 : 4;   // the band's first row and height
+  int local = t - (r0 * nt - r0 * (r0 - 1) / 2);
+  if (local < hb * (hb + 1) / 2) {
+    int r = 0;
+    while (local >= hb - r) {
+      local -= hb - r;
+      ++r;
+    }
+    *ti = r0 + r;
+    *tj = r0 + r + local;
+  } else {
+    local -= hb * (hb + 1) / 2;
+    *ti = r0 + local % hb;
+    *tj = r0 + hb + local / hb;
+  }
+}
+
+// Tile t of a whole nt x nt grid in the same bands.
+__device__ __forceinline__ void full_tile(int t, int nt, int* ti, int* tj) {
+  const int r0 = t / (4 * nt) * 4, hb = nt - r0 < 4 ? nt - r0 : 4;
+  const int local = t - r0 * nt;
+  *ti = r0 + local % hb;
+  *tj = local / hb;
+}
+
+// Position p of cnt tiles as workgroups are dealt to the XCDs in turn: each
+// XCD takes a contiguous run of tiles, which share row panels in its L2.
+__device__ __forceinline__ int xcd_order(int p, int cnt) {
+  const int x = p & 7, per = cnt >> 3, rest = cnt & 7;
+  return x * per + (x < rest ? x : rest) + (p >> 3);
+}
+
+// ---------------------------------------------------------------- step kernel
+
+// One SP2 / sweep step (see the step kernel of dmpt_kernels.hip): workgroup =
+// one tile of Z = Y_n X_n + X_n Y_n (nz observables, first: twice the work) or
+// of P = X_n X_n (with_p).  The controller's reduction of the previous
+// launch's partials overlaps the main loop; the decision is needed only by
+// the epilogue, which every workgroup reaches or leaves together.
+template <int PREC, int B, int W, bool MIX>
+__device__ __forceinline__ void small_job(const StepArgs& a, const int kind, const int obs, const int t, LDS_AS char* part,
+                                          double* s_ctl, double* s_red, int* s_code) {
+  using G = SGeo<PREC, B, W>;
+  LDS_AS float* T = (LDS_AS float*)part;
+  constexpr int TS = G::TS, LS = G::LS, NTH = G::NTH, V4 = TS / 4;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nt = a.n_pad / TS;
+  int ti, tj;
+  tri_tile(t, nt, &ti, &tj);
+  const int spass = a.n_pad / Fmt<PREC>::K;
+  const bool zk = kind == kJobZ;
+  const int nst = zk ? 2 * spass : spass;
+
+  const char* xop = (const char*)(MIX && zk ? a.x_in.op2 : a.x_in.op);
+  const char* yop = (const char*)a.y_in.op + obs * a.y_in.stride_op;
+  // kSplitH: products scaled by 2^(s_a + s_b), outputs by 2^s_out (Z: from ||Y_n||_F)
+  float usc = 1.0f, sc_out = 1.0f;
+  int s_out = 0;
+  if constexpr (PREC == kSplitH) {
+    if (zk) {
+      usc = ldexpf(1.0f, -(kXScaleExp + ((const MatMeta*)(a.y_in.meta + obs * a.y_in.stride_op))->scale));
+    } else {
+      usc = ldexpf(1.0f, -2 * kXScaleExp);
+      s_out = kXScaleExp;
+    }
+  }
+  // while the first operands are on their way: leave after the stop, and the
+  // FP64 sums (lane-strided, fixed order) of the controller's partials and of ||Y_n||^2
+  CtlIn ci = {};
+  auto ov = [&]() {
+    if (a.decide) {
+      // everything the decision reads is asked for at once
+      ci = ctl_read(a);
+      const int done = a.ctl->done;
+      double tr = 0.0, sq = 0.0, eps = 0.0;
+      for (int q = tid; q < a.nparts; q += NTH) {
+        const Part p = a.part_in[q];
+        tr += p.tr;
+        sq += p.sq;
+        eps += p.eps;
+      }
+      // sweep stop (ytol2): recorded by an earlier launch, or by this one,
+      // whose Z tiles are then dropped either way
+      if (done || (zk && a.ytol2 > 0.0 && ci.ystop != 0)) return false;
+      tr = wave_sum(tr);
+      sq = wave_sum(sq);
+      eps = wave_sum(eps);
+      if (lane == 0) {
+        s_ctl[3 * wave] = tr;
+        s_ctl[3 * wave + 1] = sq;
+        s_ctl[3 * wave + 2] = eps;
+      }
+    }
+    if constexpr (PREC == kSplitH) {
+      if (zk) {
+        const MatMeta* mi = (const MatMeta*)(a.y_in.meta + obs * a.y_in.stride_op);
+        const int cap = meta_entries(a.n_pad), cnt = mi->count < cap ? mi->count : cap;
+        double s = 0.0;
+        for (int q = tid; q < cnt; q += NTH) s += mi->nrm[q];
+        s = wave_sum(s);
+        if (lane == 0) s_red[wave] = s;
+      }
+    }
+    return true;
+  };
+  // this thread's pieces of the current matrix, for the update
+  const float* cur = zk ? a.y_in.f32 + obs * a.y_in.stride_f32 : a.x_in.f32;
+  const int gr0 = ti * TS, gc0 = tj * TS;
+  f32x4 xc[G::VX];
+  auto pre = [&]() {
+    if (zk && !a.decide && !a.sigma_src && a.fixed_sigma > 0) return;   // not read
+#pragma unroll
+    for (int q = 0; q < G::VX; ++q) {
+      const int e = tid + q * NTH;
+      if (TS * V4 % NTH == 0 || e < TS * V4) xc[q] = *(const f32x4*)(cur + m_off(1, gr0 + e % TS, gc0 + 4 * (e / TS), a.n_pad));
+    }
+  };
+  const size_t rI = panel_off<PREC>(ti * TS, a.n_pad), rJ = panel_off<PREC>(tj * TS, a.n_pad);
+  const int fl = MIX && zk && a.flush_z > 0 ? a.flush_z : a.flush;
+  if (!tile_sum<PREC, B, W>((zk ? yop : xop) + rI, xop + rJ, xop + rI, yop + rJ, spass, nst, a.n_pad, fl, usc,
+                         a.oscale != 0.0f ? a.oscale : 1.0f, part, wave, lane, ov, pre))
+    return;
+  if constexpr (PREC == kSplitH) {
+    if (zk) {   // s_red was written before tile_sum's barrier
+      double s = 0.0;
+      for (int w = 0; w < G::NWV; ++w) s += s_red[w];
+      s_out = yscale_exp(sqrt(s), kYBound);
+    }
+    sc_out = ldexpf(1.0f, s_out);
+  }
+  if (a.decide && tid == 0) {
+    double tr = 0.0, sq = 0.0, eps = 0.0;
+    for (int w = 0; w < G::NWV; ++w) {
+      tr += s_ctl[3 * w];
+      sq += s_ctl[3 * w + 1];
+      eps += s_ctl[3 * w + 2];
+    }
+    int zs = 0;
+    const int code = step_decide(a, ci, tr, sq, eps, blockIdx.x == gridDim.x - 1, &zs);
+    s_code[0] = code;
+    s_code[1] = zs;
+  }
+  __syncthreads();
+  int sigma;
+  if (a.decide) {
+    sigma = s_code[0];
+    if (!(sigma == 1 || sigma == -1) || (zk && s_code[1])) return;
+  } else {
+    sigma = a.sigma_src ? a.sigma_src[a.step].sigma : a.fixed_sigma;
+  }
+
+  // epilogue: sigma-update in T, then rows, mirror rows and operand copies
+  float* o32 = zk ? a.y_out.f32 + obs * a.y_out.stride_f32 : a.x_out.f32;
+  char* oop = zk ? (char*)a.y_out.op + obs * a.y_out.stride_op : (char*)a.x_out.op;
+  char* oop2 = nullptr;
+  if constexpr (MIX) {
+    char* o2 = (char*)(zk ? a.y_out.op2 : a.x_out.op2);
+    oop2 = o2 ? o2 + (zk ? obs * a.y_out.stride_op : 0) : nullptr;
+  }
+  char* hop = !zk && a.hist ? a.hist + (size_t)(a.step + 1) * a.hist_stride : nullptr;
+  const bool wsplit = a.write_split && PREC != kFP32;
+  const bool diag = ti == tj;
+  double tr = 0.0, sq = 0.0, ep = 0.0;
+#pragma unroll
+  for (int q = 0; q < G::VX; ++q) {
+    const int e = tid + q * NTH;
+    if (TS * V4 % NTH != 0 && e >= TS * V4) break;
+    const int r = e % TS, c = 4 * (e / TS);
+    const f32x4 x = xc[q];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (diag && r > c + k) continue;   // a diagonal tile keeps its upper triangle and mirrors it
+      const float p = T[r * LS + c + k];
+      const float v = sigma > 0 ? p : 2.0f * x[k] - p;
+      T[r * LS + c + k] = v;
+      const double w = diag && r == c + k ? 1.0 : 2.0;
+      if (!zk) {
+        const double d = x[k] - p;         // X_n - X_n^2
+        if (diag && r == c + k) tr += v;
+        sq += w * (double)v * (double)v;
+        ep += w * d * d;
+      } else if constexpr (PREC == kSplitH) {
+        sq += w * (double)v * (double)v;
+      }
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < TS * V4; e += NTH) {
+    const int r = e % TS, c = 4 * (e / TS);
+    f32x4 v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = diag && r > c + k ? T[(c + k) * LS + r] : T[r * LS + c + k];
+    *(f32x4*)(o32 + m_off(1, gr0 + r, gc0 + c, a.n_pad)) = v;
+    if (!diag) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = T[(c + k) * LS + r];
+      *(f32x4*)(o32 + m_off(1, gc0 + r, gr0 + c, a.n_pad)) = v;
+    }
+  }
+  if (wsplit || hop) {
+    const int nstp = a.n_pad / Fmt<PREC>::K, nsth = a.n_pad / Fmt<kBF16>::K;
+    constexpr int V8 = TS / 8;
+    const int groups = diag ? TS * V8 : 2 * TS * V8;
+    for (int e = tid; e < groups; e += NTH) {
+      const bool mir = e >= TS * V8;
+      const int g = mir ? e - TS * V8 : e;
+      const int r = g % TS, c = 8 * (g / TS);
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        v[k] = mir || (diag && r > c + k) ? T[(c + k) * LS + r] : T[r * LS + c + k];
+      const int gr = (mir ? gc0 : gr0) + r, gc = (mir ? gr0 : gc0) + c;
+      if (wsplit) {
+        if constexpr (PREC != kFP32) store_group8_t<PREC>(oop, nstp, gr, gc, v, sc_out, 1);
+        if constexpr (MIX) {
+          if (oop2) store_group8_t<kSplit2>(oop2, nstp, gr, gc, v, 1.0f, 1);
+        }
+      }
+      if (hop) store_group8_t<kBF16>(hop, nsth, gr, gc, v, 1.0f, 1);
+    }
+  }
+  if (!zk || PREC == kSplitH) {
+    sq = wave_sum(sq);
+    if (!zk) {
+      tr = wave_sum(tr);
+      ep = wave_sum(ep);
+    }
+    if (lane == 0) {
+      s_ctl[3 * wave] = tr;
+      s_ctl[3 * wave + 1] = sq;
+      s_ctl[3 * wave + 2] = ep;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      Part p = {0.0, 0.0, 0.0, 0.0};
+      for (int w = 0; w < G::NWV; ++w) {
+        p.tr += s_ctl[3 * w];
+        p.sq += s_ctl[3 * w + 1];
+        p.eps += s_ctl[3 * w + 2];
+      }
+      if (!zk) {
+        a.part_out[t] = p;
+      } else {
+        MatMeta* mo = (MatMeta*)(a.y_out.meta + obs * a.y_out.stride_op);
+        mo->nrm[t] = p.sq;
+        if (t == 0) {
+          mo->scale = s_out;
+          mo->count = nt * (nt + 1) / 2;
+        }
+      }
+    }
+  }
+}
+
+template <int PP, int PZ, int B, int W>
+__global__ __launch_bounds__((W * 64)) __attribute__((amdgpu_waves_per_eu((B == 1 ? 4 : 2), (B == 1 ? 4 : 2))))
+void k_step_small(StepArgs a, int nz) {
+  using G = SGeo<PP, B, W>;
+  constexpr int PART = G::PART > SGeo<PZ, B, W>::PART ? G::PART : SGeo<PZ, B, W>::PART;
+  __shared__ __attribute__((aligned(1024))) char part[PART];
+  __shared__ double s_ctl[3 * 8];
+  __shared__ double s_red[8];
+  __shared__ int s_code[2];
+  const int nt = a.n_pad / G::TS, tri = nt * (nt + 1) / 2;
+  int b = blockIdx.x;
+  if (b < nz * tri) {
+    const int obs = b / tri;
+    b = xcd_order(b - obs * tri, tri);
+    small_job<PZ, B, W, PP != PZ>(a, kJobZ, obs, b, (LDS_AS char*)part, s_ctl, s_red, s_code);
+  } else {
+    b = xcd_order(b - nz * tri, tri);
+    small_job<PP, B, W, PP != PZ>(a, kJobP, 0, b, (LDS_AS char*)part, s_ctl, s_red, s_code);
+  }
+}
+
+// Waves of a 64 x 64 tile's workgroup.  Four (64 KB of sums, so that two
+// workgroups share a CU and one's epilogue runs under the other's loop) except
+// where the tiles fill the chip once and a bit: there the few extra ones
+// would double up on some CUs for the whole launch, while eight waves (one
+// workgroup a CU) leave them to the CUs that finish first.  Step, us, four /
+// eight waves: n = 850 (210 tiles) FP32 42.2 / 44.9; n = 1000 (272) FP32
+// 70.7 / 57.2, FP16 split 35.6 / 34.4; n = 2048 (1056) 275 / 300, 114 / 137.
+inline bool eight_waves(int grid) { return grid > 256 && grid <= 384; }
+
+}  // namespace
+
+hipError_t launch_step_small(int prec, int ts, const StepArgs& args, int nz, int with_p, hipStream_t s) {
+  if (args.n_pad <= 0 || args.n_pad % 64 != 0 || (ts != 32 && ts != 64) || (args.decide && !with_p))
+    return hipErrorInvalidValue;
+  const int nt = args.n_pad / ts, grid = (nz + (with_p ? 1 : 0)) * (nt * (nt + 1) / 2);
+  if (grid <= 0) return hipSuccess;
+#define DMPT_SMALL(PP, PZ)                                                                                          \
+  if (ts == 32) hipLaunchKernelGGL((k_step_small<PP, PZ, 1, 8>), dim3(grid), dim3(512), 0, s, args, nz);       \
+  else if (eight_waves(grid)) hipLaunchKernelGGL((k_step_small<PP, PZ, 2, 8>), dim3(grid), dim3(512), 0, s, args, nz); \
+  else hipLaunchKernelGGL((k_step_small<PP, PZ, 2, 4>), dim3(grid), dim3(256), 0, s, args, nz);                \
+  break;
+  switch (prec) {
+    case kFP32: DMPT_SMALL(kFP32, kFP32)
+    case kSplit2: DMPT_SMALL(kSplit2, kSplit2)
+    case kSplit3: DMPT_SMALL(kSplit3, kSplit3)
+    case kSplit32: DMPT_SMALL(kSplit3, kSplit2)
+    case kBF16: DMPT_SMALL(kBF16, kBF16)
+    case kSplitH: DMPT_SMALL(kSplitH, kSplitH)
+    default: return hipErrorInvalidValue;
+  }
+#undef DMPT_SMALL
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- general product
+
+// C = alpha A B^T over the TS x TS tiles (sym: the upper triangle of a product
+// known to be symmetric, with the mirror tile stored from the same sums).
+namespace {
+template <int PREC, int B, int W>
+__global__ __launch_bounds__((W * 64)) __attribute__((amdgpu_waves_per_eu((B == 1 ? 4 : 2), (B == 1 ? 4 : 2))))
+void k_gemm_small(const char* A, const char* Bm, float* C, int n_pad, float alpha, int flush, int sym) {
+  using G = SGeo<PREC, B, W>;
+  constexpr int TS = G::TS, LS = G::LS, NTH = G::NTH, V4 = TS / 4;
+  __shared__ __attribute__((aligned(1024))) char part[G::PART];
+  LDS_AS float* T = (LDS_AS float*)part;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nt = n_pad / TS;
+  const int t = xcd_order(blockIdx.x, gridDim.x);
+  int ti, tj;
+  if (sym) tri_tile(t, nt, &ti, &tj);
+  else full_tile(t, nt, &ti, &tj);
+  const int nst = n_pad / Fmt<PREC>::K;
+  const char* pa = A + panel_off<PREC>(ti * TS, n_pad);
+  const char* pb = Bm + panel_off<PREC>(tj * TS, n_pad);
+  tile_sum<PREC, B, W>(pa, pb, pa, pb, nst, nst, n_pad, flush, alpha, 1.0f, (LDS_AS char*)part, wave, lane,
+                       [] { return true; }, [] {});
+  __syncthreads();
+  const bool diag = sym && ti == tj;
+  for (int e = tid; e < TS * V4; e += NTH) {
+    const int r = e % TS, c = 4 * (e / TS);
+    f32x4 v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = diag && r > c + k ? T[(c + k) * LS + r] : T[r * LS + c + k];
+    *(f32x4*)(C + m_off(1, ti * TS + r, tj * TS + c, n_pad)) = v;
+    if (sym && !diag) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = T[(c + k) * LS + r];
+      *(f32x4*)(C + m_off(1, tj * TS + r, ti * TS + c, n_pad)) = v;
+    }
+  }
+}
+}  // namespace
+
+hipError_t launch_gemm_small(int prec, int ts, const void* A, const void* B, float* C, int n_pad, float alpha, int flush,
+                             int sym, hipStream_t s) {
+  if (n_pad <= 0 || n_pad % 64 != 0 || (ts != 32 && ts != 64)) return hipErrorInvalidValue;
+  const int nt = n_pad / ts, grid = sym ? nt * (nt + 1) / 2 : nt * nt;
+#define DMPT_GSMALL(P)                                                                                              \
+  if (ts == 32) hipLaunchKernelGGL((k_gemm_small<P, 1, 8>), dim3(grid), dim3(512), 0, s, (const char*)A,       \
+                                   (const char*)B, C, n_pad, alpha, flush, sym);                               \
+  else if (eight_waves(grid)) hipLaunchKernelGGL((k_gemm_small<P, 2, 8>), dim3(grid), dim3(512), 0, s, (const char*)A, \
+                                                 (const char*)B, C, n_pad, alpha, flush, sym);                 \
+  else hipLaunchKernelGGL((k_gemm_small<P, 2, 4>), dim3(grid), dim3(256), 0, s, (const char*)A, (const char*)B, C, \
+                          n_pad, alpha, flush, sym);                                                           \
+  break;
+  switch (prec) {
+    case kFP32: DMPT_GSMALL(kFP32)
+    case kSplit2: DMPT_GSMALL(kSplit2)
+    case kSplit3: DMPT_GSMALL(kSplit3)
+    case kSplitH: DMPT_GSMALL(kSplitH)
+    default: return hipErrorInvalidValue;
+  }
+#undef DMPT_GSMALL
+  return hipGetLastError();
+}
+
+}  // namespace dmpt

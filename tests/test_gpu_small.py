@@ -1,0 +1,69 @@
+"""Small-size kernels at the edges of their tiles and dispatch.
+
+Partial recursions (five steps, no projection) on two observables against the
+FP64 recursion on the sigma sequence and bounds the device chose, with the
+per-step bounds that the large-size kernels are held to (2e-6 a step for the
+FP32-accurate products, 6e-5 where the sweep products have two BF16 terms).
+Sizes: one partial tile of 32, whole tiles and one row more, an odd number of
+64-row blocks, the first sizes of the 64 x 64 tiles, a tile count just above
+the number of CUs (eight waves a tile), and the last size of the wide-list rule.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import closed_form as cf
+from oracle import sp2
+
+pytestmark = pytest.mark.gpu
+
+STEPS = 5
+
+
+@pytest.fixture(scope="module")
+def inputs():
+    cache = {}
+
+    def get(n):
+        if n not in cache:
+            wl = W.dense_gapped(n, nocc=max(1, n // 3), nobs=2, npert=1, cfg=21)
+            cache[n] = wl
+        return cache[n]
+    return get
+
+
+@pytest.mark.parametrize("prec", ["fp32", "split_fp16", "split3_bf16", "split3x_bf16", "split_bf16"])
+@pytest.mark.parametrize("n", [5, 32, 33, 64, 95, 129, 449, 705, 960, 1030])
+def test_partial_recursion_at_tile_edges(gpu, inputs, n, prec):
+    import torch
+
+    import paper_2409_17033_amd as dm
+    wl = inputs(n)
+    H, A = torch.from_numpy(wl.H).to(gpu), torch.from_numpy(wl.A).to(gpu)
+    chi, D, _, info = dm.susceptibility(H, A, wl.nocc, precision=prec, bounds="gershgorin", max_iter=STEPS,
+                                        min_iter=STEPS + 1, project=False, spin=1.0, raise_on_error=False)
+    assert info["m"] == STEPS and info["tile"] in (32, 64)
+    h = wl.H.astype(np.float64)
+    xs, beta = sp2.sp2_sequence(h, info["sigma"], info["emin"], info["emax"])
+    tol = 6e-5 * STEPS if prec in ("split_bf16", "split3x_bf16") else 2e-6 * STEPS
+    assert cf.rel_frobenius(D.double().cpu().numpy(), xs[-1]) < tol
+    for k in range(2):
+        y = sp2.forward_sweep(xs, info["sigma"], beta, wl.A[k].astype(np.float64))
+        c = chi[k].double().cpu().numpy()
+        assert cf.rel_frobenius(c, y) < tol
+        assert np.array_equal(c, c.T)
+
+
+@pytest.mark.parametrize("n,tile", [(1984, 64), (1985, 256)])
+def test_wide_list_runs_keep_the_large_tiles(gpu, n, tile):
+    """Corrected runs of the three-term-X^2 option change to the large-size
+    lists above n = 1984; both sides meet the refined 1e-5."""
+    import torch
+
+    import paper_2409_17033_amd as dm
+    wl = W.banded_gapped(n, cfg=22, npert=1, cache=False)
+    chi, D, _, info = dm.susceptibility(torch.from_numpy(wl.H).to(gpu), torch.from_numpy(wl.A[0]).to(gpu), wl.nocc,
+                                        precision="split3x_bf16", refine=True, sweep_tol=1e-3)
+    assert info["tile"] == tile
+    ref = cf.susceptibility(wl.H.astype(np.float64), wl.A[0].astype(np.float64), wl.nocc, spin=2.0)
+    assert cf.rel_frobenius(chi.double().cpu().numpy(), ref) <= 1e-5
