@@ -1639,7 +1639,7 @@ namespace dmpt {
 namespace {
 
 constexpr int kMixerMaxSteps = 65536;
-constexpr int kMixerMseBlocks = 256;
+constexpr int kMixerPartials = 1024;   // loss partials: 256, or one per 64 sites of n <= 65536
 
 struct MixWS {
   size_t scratch, part, grad, loss, total;
@@ -1655,7 +1655,7 @@ static MixWS mixer_ws(int n, int w, int h, int batch) {
   MixWS m;
   size_t off = 0;
   m.scratch = off; off = align_up(off + mixer_scratch_floats(n, w, h, batch) * 4);
-  m.part = off; off = align_up(off + (size_t)kMixerMseBlocks * 8);
+  m.part = off; off = align_up(off + (size_t)kMixerPartials * 8);
   m.grad = off; off = align_up(off + mixer_param_count(w, h) * 4);
   m.loss = off; off = align_up(off + (size_t)kMixerMaxSteps * 8);
   m.total = off;

@@ -9,10 +9,12 @@
 // Parameters (FP32 masters and the BF16 copy alike): [W1 (h x k, row-major) |
 // b1 (h) | w2 (h) | b2 (1)].  Training: MSE loss, Adam (Kingma & Ba, 2015).
 // Shapes are small next to the SP2 products (B n ~ 1e4-1e5 site rows,
-// k ~ 66, h = 256), so the products use one LDS-tiled FP32 kernel with an
-// optional deterministic split over K; weights are read as BF16 and widened.
+// k ~ 131, h = 256).  Up to h = 256 and w = 64 one fused kernel forms outputs,
+// loss and gradients; beyond, the products use one LDS-tiled FP32 kernel with
+// an optional deterministic split over K.  Weights are read as BF16 and widened.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "dmpt_internal.h"
@@ -231,6 +233,267 @@ __global__ void k_init_params(float* p, uint16_t* p16, int k, int h, uint64_t se
   p16[i] = to_bf16(val);
 }
 
+// ---------------------------------------------------------------- fused network pass
+
+// One workgroup takes 64 sites and, one after the other, its share of the
+// batch: forward, loss and the gradients of those rows without writing Z, A or
+// their gradients to memory.  Wave w owns the hidden units 32 w .. 32 w + 31.
+// Products on v_mfma_f32_32x32x2_f32 (FP32 operands and sums; the weights are
+// BF16 values, widened exactly):
+//   * Z is a Toeplitz matrix of x: operand (i, f) is x_{i + f - w}, read from
+//     one LDS row, so it is never formed.  The columns of E and U are the same
+//     for every state of the batch: their part of W1 z (with b1) is formed once
+//     per workgroup and starts every accumulator.
+//   * The accumulator holds rows 8 (e / 4) + 4 h + e % 4 of hidden unit l32 in
+//     register e of lane (h, l32), which is the operand layout of dZ^T for the
+//     row pair (r, r + 4): the weight gradient takes it as it stands.
+//   * The gradient's E and U columns are linear in dZ summed over the batch:
+//     one product at the end.
+// Each workgroup writes its own gradient (summed afterwards in order, in FP64).
+// Covers h <= 256 and windows w <= 64 (FB blocks of 32 window columns and one
+// column more); other shapes take the general products above.
+// Bound by the FP32 MFMAs beside tanh on the vector ALU.  n = 1024, batch 64,
+// w = 32, h = 256: loss and gradient 1145 -> 125 us (the pass 95 us, of which 35
+// are its MFMAs; the sum over the workgroups 10), error of the gradient against
+// 64 bits 1.3e-7 -> 3.6e-8.
+typedef float f16v __attribute__((ext_vector_type(16)));
+constexpr int kFusedSites = 64, kFusedHidden = 256, kFusedWGs = 256;
+
+inline int fused_blocks(int w) { return (2 * w + 1) / 32 + ((2 * w + 1) % 32 > 1 ? 1 : 0); }   // FB (0: one column)
+inline bool fused_shape(int w, int h) { return h <= kFusedHidden && fused_blocks(w) <= 4; }
+// Batch groups a 64-site block is cut into: about one workgroup per CU.
+inline int fused_groups(int n, int B) {
+  const int ib = (n + kFusedSites - 1) / kFusedSites;
+  int g = kFusedWGs / ib;
+  g = g < 1 ? 1 : g > B ? B : g;
+  const int per = (B + g - 1) / g;
+  return (B + per - 1) / per;
+}
+
+template <int FB, bool BWD>
+__global__ __launch_bounds__(512) void k_mixer_fused(const uint16_t* p16, int w, int h, const float* u, const float* en,
+                                                     int n, const float* x, const float* t, int B, int per, float* y,
+                                                     double* loss_part, float* gpart, double scale) {
+  constexpr int KM = 32 * FB + 2;                  // window columns, padded to an even count
+  constexpr int XS = kFusedSites + KM + 32;
+  __shared__ uint16_t wx[KM * kFusedHidden];       // W1's x columns, [f][unit]
+  __shared__ uint16_t we[KM * kFusedHidden];       // its E columns
+  __shared__ float xs[XS], es[XS], us[kFusedSites];
+  __shared__ float ysum[8][kFusedSites];
+  __shared__ __attribute__((aligned(16))) float dys[kFusedSites];
+  const int m = 2 * w + 1, k = 2 * m + 1, km = m + 1;
+  const int tid = threadIdx.x, nth = blockDim.x, lane = tid & 63, wave = tid >> 6;
+  const int hf = lane >> 5, l32 = lane & 31, unit = wave * 32 + l32, hp = (nth >> 6) * 32;
+  const int i0 = blockIdx.x * kFusedSites;
+  const uint16_t* b1 = p16 + (size_t)h * k;
+  const uint16_t* w2 = b1 + h;
+  const int b0 = blockIdx.y * per, be = b0 + per < B ? b0 + per : B;
+  for (int q = tid; q < km * hp; q += nth) {
+    const int f = q % km, c = q / km;              // along a row of W1
+    const bool in = f < m && c < h;
+    wx[f * hp + c] = in ? p16[(size_t)c * k + f] : (uint16_t)0;
+    we[f * hp + c] = in ? p16[(size_t)c * k + m + f] : (uint16_t)0;
+  }
+  for (int q = tid; q < XS; q += nth) {
+    const int j = i0 + q - w;
+    es[q] = j >= 0 && j < n ? en[j] : 0.0f;
+  }
+  for (int q = tid; q < kFusedSites; q += nth) us[q] = i0 + q < n ? u[i0 + q] : 0.0f;
+  const float w2c = unit < h ? ld(w2, unit) : 0.0f, b1c = unit < h ? ld(b1, unit) : 0.0f;
+  const float wuc = unit < h ? ld(p16, (size_t)unit * k + 2 * m) : 0.0f, b2 = ld(w2 + h, 0);
+  __syncthreads();
+  // row of register e, block bi: 32 bi + 8 (e / 4) + 4 hf + e % 4
+  f16v site[2];
+#pragma unroll
+  for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) site[bi][e] = b1c + us[32 * bi + 8 * (e >> 2) + 4 * hf + (e & 3)] * wuc;
+  auto forward = [&](const float* v, const uint16_t* wt, f16v (&acc)[2]) {
+#pragma unroll 4
+    for (int s = 0; s < km / 2; ++s) {
+      const int f = 2 * s + hf;
+      const float bv = ld(wt, f * hp + unit);
+      acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[l32 + f], bv, acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[32 + l32 + f], bv, acc[1], 0, 0, 0);
+    }
+  };
+  forward(es, we, site);
+  constexpr int GB = FB > 0 ? FB : 1;
+  f16v g[GB];
+  f16v sdz[2];
+  float grem = 0.0f, gw2 = 0.0f;
+#pragma unroll
+  for (int q = 0; q < GB; ++q) g[q] = f16v{0};
+  sdz[0] = f16v{0};
+  sdz[1] = f16v{0};
+  double loss = 0.0;
+  float gb2 = 0.0f;
+  // g[fb] += (dZ rows of this wave's units)^T (window columns of v); rem: column 32 FB
+  auto backward = [&](const f16v (&dz)[2], const float* v, float& rem) {
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int row = 32 * bi + 8 * (e >> 2) + 4 * hf + (e & 3);
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb)
+          g[fb] = __builtin_amdgcn_mfma_f32_32x32x2f32(dz[bi][e], v[row + 32 * fb + l32], g[fb], 0, 0, 0);
+        rem += dz[bi][e] * v[row + 32 * FB];
+      }
+  };
+  for (int b = b0; b < be; ++b) {
+    for (int q = tid; q < XS; q += nth) {
+      const int j = i0 + q - w;
+      xs[q] = j >= 0 && j < n ? x[(size_t)b * n + j] : 0.0f;
+    }
+    __syncthreads();
+    f16v a[2] = {site[0], site[1]};
+    forward(xs, wx, a);
+    float v[32];
+#pragma unroll
+    for (int q = 0; q < 32; ++q) {
+      a[q >> 4][q & 15] = tanhf(a[q >> 4][q & 15]);
+      v[q] = a[q >> 4][q & 15] * w2c;
+    }
+    // sums over the 32 units: halve the values a lane holds with each exchange;
+    // lane l32 ends with value l32
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) {
+      const bool up = (l32 & off) != 0;
+#pragma unroll
+      for (int q = 0; q < off; ++q) {
+        const float keep = up ? v[q + off] : v[q], send = up ? v[q] : v[q + off];
+        v[q] = keep + __shfl_xor(send, off, 64);
+      }
+    }
+    ysum[wave][32 * (l32 >> 4) + 8 * ((l32 & 15) >> 2) + 4 * hf + (l32 & 3)] = v[0];
+    __syncthreads();
+    if (tid < kFusedSites) {
+      float yv = 0.0f;
+      for (int q = 0; q < (nth >> 6); ++q) yv += ysum[q][tid];
+      yv += b2;
+      const bool in = i0 + tid < n;
+      const size_t row = (size_t)b * n + i0 + tid;
+      if (!BWD) {
+        if (in) y[row] = yv;
+      } else {
+        const double r = in ? (double)yv - (double)t[row] : 0.0;
+        loss += r * r;
+        const float d = (float)(scale * r);
+        dys[tid] = d;
+        gb2 += d;
+      }
+    }
+    __syncthreads();
+    if (BWD) {
+#pragma unroll
+      for (int q = 0; q < 32; ++q) {
+        const int bi = q >> 4, e = q & 15;
+        const float d = dys[32 * bi + 8 * (e >> 2) + 4 * hf + (e & 3)], av = a[bi][e];
+        gw2 += av * d;
+        const float dz = d * w2c * (1.0f - av * av);
+        sdz[bi][e] += dz;
+        a[bi][e] = dz;
+      }
+      backward(a, xs, grem);
+      __syncthreads();   // xs is read: the next state may take its place
+    }
+  }
+  if (!BWD) return;
+  const int wg = blockIdx.y * gridDim.x + blockIdx.x;
+  float* gp = gpart + (size_t)wg * ((size_t)h * k + 2 * h + 1);
+  // accumulator of a weight block: row = unit, column = window column
+  auto store = [&](int c0, float rem) {
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int un = wave * 32 + 8 * (e >> 2) + 4 * hf + (e & 3), f = 32 * fb + l32;
+        if (un < h && f < m) gp[(size_t)un * k + c0 + f] = g[fb][e];
+      }
+    rem += __shfl_xor(rem, 32, 64);
+    if (hf == 0 && unit < h && 32 * FB < m) gp[(size_t)unit * k + c0 + 32 * FB] = rem;
+  };
+  store(0, grem);
+#pragma unroll
+  for (int q = 0; q < GB; ++q) g[q] = f16v{0};
+  grem = 0.0f;
+  backward(sdz, es, grem);
+  store(m, grem);
+  float gu = 0.0f, gb1 = 0.0f;
+#pragma unroll
+  for (int q = 0; q < 32; ++q) {
+    const int bi = q >> 4, e = q & 15;
+    gu += sdz[bi][e] * us[32 * bi + 8 * (e >> 2) + 4 * hf + (e & 3)];
+    gb1 += sdz[bi][e];
+  }
+  gu += __shfl_xor(gu, 32, 64);
+  gb1 += __shfl_xor(gb1, 32, 64);
+  gw2 += __shfl_xor(gw2, 32, 64);
+  if (hf == 0 && unit < h) {
+    gp[(size_t)unit * k + 2 * m] = gu;
+    gp[(size_t)h * k + unit] = gb1;
+    gp[(size_t)h * k + h + unit] = gw2;
+  }
+  if (tid < 64) {
+    for (int off = 32; off > 0; off >>= 1) {
+      loss += __shfl_xor(loss, off, 64);
+      gb2 += __shfl_xor(gb2, off, 64);
+    }
+    if (tid == 0) {
+      loss_part[wg] = loss;
+      gp[(size_t)h * k + 2 * h] = gb2;
+    }
+  }
+}
+
+// grad[p] = sum over the workgroups' gradients (FP64, fixed order: four
+// interleaved runs), and in workgroup 0 the loss.
+__global__ __launch_bounds__(256) void k_mixer_reduce(const float* gpart, int nwg, size_t count, float* grad,
+                                                      const double* loss_part, double inv, double* loss_out, int idx) {
+  __shared__ double red[4][64];
+  const size_t p = (size_t)blockIdx.x * 64 + (threadIdx.x & 63);
+  const int q = threadIdx.x >> 6;
+  double acc = 0.0;
+  if (p < count)
+#pragma unroll 8
+    for (int z = q; z < nwg; z += 4) acc += (double)gpart[(size_t)z * count + p];
+  red[q][threadIdx.x & 63] = acc;
+  __syncthreads();
+  if (q == 0 && p < count) grad[p] = (float)(red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x]);
+  if (blockIdx.x == 0 && q == 1) {
+    double l = 0.0;
+    for (int z = threadIdx.x - 64; z < nwg; z += 64) l += loss_part[z];
+    for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
+    if (threadIdx.x == 64) loss_out[idx] = l * inv;
+  }
+}
+
+// The fused pass over B states; gradient and loss with t, outputs y without.
+hipError_t launch_fused(const uint16_t* p16, int w, int h, const float* u, const float* en, int n, const float* x,
+                        const float* t, int B, float* y, double* loss_part, float* gpart, hipStream_t s) {
+  const int groups = fused_groups(n, B), per = (B + groups - 1) / groups;
+  const dim3 grid((n + kFusedSites - 1) / kFusedSites, groups), block((h + 31) / 32 * 64);
+  const double scale = 2.0 / ((double)B * n);
+#define DMPT_FUSED(FB)                                                                                              \
+  case FB:                                                                                                          \
+    if (t) hipLaunchKernelGGL((k_mixer_fused<FB, true>), grid, block, 0, s, p16, w, h, u, en, n, x, t, B, per, y,      \
+                              loss_part, gpart, scale);                                                             \
+    else hipLaunchKernelGGL((k_mixer_fused<FB, false>), grid, block, 0, s, p16, w, h, u, en, n, x, t, B, per, y,       \
+                            loss_part, gpart, scale);                                                               \
+    break;
+  switch (fused_blocks(w)) {
+    DMPT_FUSED(0)
+    DMPT_FUSED(1)
+    DMPT_FUSED(2)
+    DMPT_FUSED(3)
+    DMPT_FUSED(4)
+    default: return hipErrorInvalidValue;
+  }
+#undef DMPT_FUSED
+  return hipGetLastError();
+}
+
 }  // namespace
 
 size_t mixer_param_count(int w, int h) { return (size_t)h * mixer_features(w) + 2 * h + 1; }
@@ -243,12 +506,17 @@ hipError_t mixer_diag(const float* m, int n, float* out, hipStream_t s) {
 size_t mixer_scratch_floats(int n, int w, int h, int B) {
   const size_t rows = (size_t)B * n, k = mixer_features(w);
   // z, a, y, da, split partials of the weight gradients
-  return rows * k + rows * h + rows + rows * h + (size_t)kSplits * (h * k + h + 1);
+  const size_t general = rows * k + rows * h + rows + rows * h + (size_t)kSplits * (h * k + h + 1);
+  if (!fused_shape(w, h)) return general;
+  // the fused pass: one gradient per workgroup
+  const size_t wgs = (size_t)((n + kFusedSites - 1) / kFusedSites) * fused_groups(n, B);
+  return std::max(general, wgs * mixer_param_count(w, h));
 }
 
 // forward: y (B x n) for states x (B x n).  scratch: mixer_scratch_floats.
 hipError_t mixer_forward(const uint16_t* p16, int w, int h, const float* u, const float* en, int n, const float* x,
                          int B, float* y, float* scratch, hipStream_t s) {
+  if (fused_shape(w, h)) return launch_fused(p16, w, h, u, en, n, x, nullptr, B, y, nullptr, nullptr, s);
   const int k = mixer_features(w);
   const size_t rows = (size_t)B * n;
   const uint16_t* w1 = p16;
@@ -275,6 +543,15 @@ hipError_t mixer_loss_grad(const uint16_t* p16, int w, int h, const float* u, co
                            int idx, hipStream_t s) {
   const int k = mixer_features(w);
   const size_t rows = (size_t)B * n;
+  if (fused_shape(w, h)) {
+    const int nwg = (n + kFusedSites - 1) / kFusedSites * fused_groups(n, B);
+    hipError_t e = launch_fused(p16, w, h, u, en, n, x, t, B, nullptr, part, scratch, s);
+    if (e != hipSuccess) return e;
+    const size_t np = mixer_param_count(w, h);
+    hipLaunchKernelGGL(k_mixer_reduce, dim3(blocks(np, 64)), dim3(256), 0, s, scratch, nwg, np, grad, part,
+                       1.0 / (double)rows, loss_out, idx);
+    return hipGetLastError();
+  }
   float* z = scratch;
   float* a = z + rows * k;
   float* y = a + rows * h;
