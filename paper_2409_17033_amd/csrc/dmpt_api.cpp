@@ -219,7 +219,7 @@ void make_plan(const Opts& o, int nobs, Plan* p, bool small = true) {
   p->off_jobs = off; off = align_up(off + (size_t)p->njobs_max * 4);
   p->off_jobs_proj = off; off = align_up(off + (size_t)p->njobs_proj_max * 4);
   p->off_gersh = off; off = align_up(off + (size_t)gershgorin_blocks(o.n) * sizeof(double2));
-  p->off_lz = off; off = align_up(off + (size_t)(3 * o.n + 2 * (p->lz_steps + 2)) * sizeof(double));
+  p->off_lz = off; off = align_up(off + (lanczos_doubles(o.n) + 2 * (p->lz_steps + 2)) * sizeof(double));
   p->off_a0 = off; off = align_up(off + (size_t)kOutBlocks * std::max(nobs, 1) * sizeof(double));
   p->x_slot_bytes = align_up(p->mat_f32) + align_up(p->mat_op) + align_up(p->mat_op2) + align_up(p->mat_meta);
   p->off_x = off; off = align_up(off + p->x_slot_bytes * p->xslots);
@@ -307,63 +307,6 @@ MatRef as_fp32(MatRef m) {
   return m;
 }
 
-// ---------------------------------------------------------------- Lanczos (host part)
-
-// Number of eigenvalues of the symmetric tridiagonal (a, b) below x (Sturm count).
-int sturm_below(const std::vector<double>& a, const std::vector<double>& b, double x) {
-  int cnt = 0;
-  double d = 1.0;
-  for (size_t i = 0; i < a.size(); ++i) {
-    const double bb = i ? b[i - 1] * b[i - 1] : 0.0;
-    d = a[i] - x - (i ? bb / d : 0.0);
-    if (d == 0.0) d = -1e-300;
-    if (d < 0.0) ++cnt;
-  }
-  return cnt;
-}
-
-// k-th smallest eigenvalue (0-based) by bisection.
-double tridiag_eig(const std::vector<double>& a, const std::vector<double>& b, int k) {
-  double lo = 1e300, hi = -1e300;
-  for (size_t i = 0; i < a.size(); ++i) {
-    const double r = (i ? std::fabs(b[i - 1]) : 0.0) + (i + 1 < a.size() ? std::fabs(b[i]) : 0.0);
-    lo = std::min(lo, a[i] - r);
-    hi = std::max(hi, a[i] + r);
-  }
-  for (int it = 0; it < 200 && hi - lo > 1e-15 * std::max(1.0, std::fabs(hi) + std::fabs(lo)); ++it) {
-    const double mid = 0.5 * (lo + hi);
-    if (sturm_below(a, b, mid) > k) hi = mid; else lo = mid;
-  }
-  return 0.5 * (lo + hi);
-}
-
-// |last component| of the unit eigenvector of T for the extreme eigenvalue
-// theta, by two steps of inverse iteration with shift just outside the
-// spectrum (T - shift I is then definite and the LDL^T solve is stable).
-double last_component(const std::vector<double>& a, const std::vector<double>& b, double theta,
-                      double shift_dir, double width) {
-  const size_t k = a.size();
-  const double sh = theta + shift_dir * 1e-10 * std::max(width, 1e-300);
-  std::vector<double> x(k, 1.0), d(k), l(k), y(k);
-  for (int it = 0; it < 3; ++it) {
-    // LDL^T of (T - sh I), forward/back solve
-    d[0] = a[0] - sh;
-    for (size_t i = 1; i < k; ++i) {
-      l[i] = b[i - 1] / d[i - 1];
-      d[i] = a[i] - sh - l[i] * b[i - 1];
-    }
-    y[0] = x[0];
-    for (size_t i = 1; i < k; ++i) y[i] = x[i] - l[i] * y[i - 1];
-    for (size_t i = 0; i < k; ++i) y[i] /= d[i];
-    for (size_t i = k - 1; i-- > 0;) y[i] -= l[i + 1] * y[i + 1];
-    double nrm = 0.0;
-    for (double v : y) nrm += v * v;
-    nrm = std::sqrt(nrm);
-    for (size_t i = 0; i < k; ++i) x[i] = y[i] / nrm;
-  }
-  return std::fabs(x[k - 1]);
-}
-
 struct ScopedEvents {
   hipEvent_t e0 = nullptr, e1 = nullptr;
   ~ScopedEvents() {
@@ -421,46 +364,9 @@ dmpt_status compute_bounds(const Opts& o, const Plan& p, const float* H, Ctl* ct
   }
   if (o.bounds == DMPT_BOUNDS_GERSHGORIN) return DMPT_OK;
   const int k = std::min(p.lz_steps, o.n);
-  double* v = lz;
-  double* vprev = lz + o.n;
-  double* w = lz + 2 * o.n;
-  double* ab = lz + 3 * o.n;
-  DMPT_HIP(launch_lanczos_start(v, vprev, o.n, s));
-  for (int j = 0; j < k; ++j) DMPT_HIP(launch_lanczos_step(H, o.n, v, vprev, w, ab, j, s));
-  std::vector<double> hab(2 * k);
-  double g[2];
-  int nonfinite = 0;
-  DMPT_HIP(hipMemcpyAsync(hab.data(), ab, sizeof(double) * 2 * k, hipMemcpyDeviceToHost, s));
-  DMPT_HIP(hipMemcpyAsync(g, &ctl->gmin, sizeof(g), hipMemcpyDeviceToHost, s));
-  DMPT_HIP(hipMemcpyAsync(&nonfinite, &ctl->nonfinite, sizeof(int), hipMemcpyDeviceToHost, s));
-  DMPT_HIP(hipStreamSynchronize(s));
-  if (nonfinite) {
-    DMPT_HIP(launch_set_bounds(ctl, g[0], g[1], s));
-    return DMPT_OK;   // the step kernel reports DMPT_ERR_NONFINITE
-  }
-  // Truncate at breakdown (invariant subspace: the Ritz values are exact).
-  std::vector<double> a, b;
-  double scale = 0.0;
-  for (int j = 0; j < k; ++j) scale = std::max(scale, std::fabs(hab[2 * j]) + std::fabs(hab[2 * j + 1]));
-  int kk = k;
-  for (int j = 0; j < k; ++j) {
-    a.push_back(hab[2 * j]);
-    if (hab[2 * j + 1] <= 1e-12 * std::max(scale, 1e-300)) { kk = j + 1; break; }
-    if (j + 1 < k) b.push_back(hab[2 * j + 1]);
-  }
-  const double beta_last = kk < k ? 0.0 : hab[2 * k - 1];
-  b.resize(a.size() > 0 ? a.size() - 1 : 0);
-  const double tmin = tridiag_eig(a, b, 0);
-  const double tmax = tridiag_eig(a, b, (int)a.size() - 1);
-  const double width = std::max(tmax - tmin, 1e-12 * std::max(1.0, std::fabs(tmax)));
-  const double rmin = beta_last * last_component(a, b, tmin, -1.0, width);
-  const double rmax = beta_last * last_component(a, b, tmax, +1.0, width);
-  double emin = tmin - std::max(rmin, 0.01 * width);
-  double emax = tmax + std::max(rmax, 0.01 * width);
-  emin = std::max(emin, g[0]);
-  emax = std::min(emax, g[1]);
-  if (!(emax > emin)) { emin = g[0]; emax = g[1]; }
-  DMPT_HIP(launch_set_bounds(ctl, emin, emax, s));
+  double* ab = lz + lanczos_doubles(o.n);
+  DMPT_HIP(launch_lanczos(H, o.n, lz, ab, k, s));
+  DMPT_HIP(launch_ritz_bounds(ab, k, ctl, s));
   return DMPT_OK;
 }
 

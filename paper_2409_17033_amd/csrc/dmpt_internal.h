@@ -163,9 +163,12 @@ hipError_t launch_ctl_reset(Ctl* ctl, hipStream_t s);
 hipError_t launch_gershgorin(const float* h, int n, double2* scratch, int nblk, Ctl* ctl,
                              int set_coeffs, hipStream_t s);
 int gershgorin_blocks(int n);
-hipError_t launch_lanczos_start(double* v, double* vprev, int n, hipStream_t s);
-hipError_t launch_lanczos_step(const float* h, int n, double* v, double* vprev, double* w,
-                               double* ab, int j, hipStream_t s);
+// k Lanczos steps on H from the fixed start vector: ab[2 j], ab[2 j + 1] =
+// alpha_{j+1}, beta_{j+1}; vec: lanczos_doubles(n) doubles.
+size_t lanczos_doubles(int n);
+hipError_t launch_lanczos(const float* h, int n, double* vec, double* ab, int k, hipStream_t s);
+// Bounds (ctl's alpha, beta) from k Lanczos coefficients and the Gershgorin interval.
+hipError_t launch_ritz_bounds(const double* ab, int k, Ctl* ctl, hipStream_t s);
 hipError_t launch_set_bounds(Ctl* ctl, double emin, double emax, hipStream_t s);
 // tiled (here and below): the padded FP32 matrices and the operand copies are
 // in the small-size kernels' layouts (m_off, op_off in dmpt_device.h).

@@ -1660,8 +1660,7 @@ __global__ __launch_bounds__(1024) void k_lanczos_start(double* v, double* vprev
   for (int i = threadIdx.x; i < n; i += 1024) v[i] *= inv;
 }
 
-// w = H v, one wave per row, FP64 accumulation.
-// One wave per row.  When rows are 16-byte aligned (n % 4 == 0, aligned H) each lane
+// w = H v, one wave per row, FP64 accumulation (n > kLanczosLds).  When rows are 16-byte aligned (n % 4 == 0, aligned H) each lane
 // takes 4 consecutive columns per load, two loads in flight on separate
 // accumulators; otherwise one column per lane.  The summation order is fixed.
 __global__ __launch_bounds__(256) void k_gemv(const float* h, const double* v, double* w, int n) {
@@ -1738,15 +1737,346 @@ __global__ __launch_bounds__(1024) void k_lanczos_update(double* v, double* vpre
   }
 }
 
-hipError_t launch_lanczos_start(double* v, double* vprev, int n, hipStream_t s) {
-  hipLaunchKernelGGL(k_lanczos_start, dim3(1), dim3(1024), 0, s, v, vprev, n);
+constexpr int kLanczosLds = 4096;
+
+// Lanczos recurrence, FP64 vectors: with w = H v_j,
+//   alpha_j = v_j . w,  w' = w - alpha_j v_j - beta_{j-1} v_{j-1},
+//   beta_j = |w'|,      v_{j+1} = w' / beta_j   (v_1: the hashed start vector).
+//
+// One launch a step (n <= kLanczosLds): every workgroup forms v_{j+1} by itself (all of w, v_j,
+// v_{j-1}, the same sums in the same order) into LDS, then multiplies its own
+// rows of H with it; workgroup 0 also writes v_{j+1} and the coefficients.  A
+// launch for the sums between two products, and its gap, are saved: what is
+// left is the launch and reading H.  30 steps with the bounds: n = 257 226 -> 158
+// us, n = 1000 239 -> 178, n = 4096 653 -> 603; at n = 8192 the sums that every
+// workgroup repeats cost more than the launch (1567 -> 1696): two launches there.
+__global__ __launch_bounds__(512) void k_lanczos(const float* h, int n, int j, const double* v, const double* vprev,
+                                                 const double* w, double* v_out, double* w_out, double* ab, int last) {
+  __shared__ __attribute__((aligned(16))) double vn[kLanczosLds];
+  __shared__ double red[8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  auto wg_sum = [&](double x) {
+    x = wave_sum(x);
+    __syncthreads();   // the previous sum is read
+    if (lane == 0) red[wave] = x;
+    __syncthreads();
+    double t = 0.0;
+    for (int q = 0; q < 8; ++q) t += red[q];
+    return t;
+  };
+  double alpha = 0.0;
+  if (j == 0) {
+    for (int i = tid; i < n; i += 512) vn[i] = hash_unit(i);
+  } else {
+    double a = 0.0;
+    for (int i = tid; i < n; i += 512) a += v[i] * w[i];
+    alpha = wg_sum(a);
+    const double bprev = j > 1 ? ab[2 * (j - 2) + 1] : 0.0;
+    for (int i = tid; i < n; i += 512) vn[i] = w[i] - alpha * v[i] - (j > 1 ? bprev * vprev[i] : 0.0);
+  }
+  double a = 0.0;
+  for (int i = tid; i < n; i += 512) a += vn[i] * vn[i];
+  const double beta = sqrt(wg_sum(a));
+  const double inv = beta > 0.0 ? 1.0 / beta : 0.0;
+  if (blockIdx.x == 0 && j > 0 && tid == 0) {
+    ab[2 * (j - 1)] = alpha;
+    ab[2 * (j - 1) + 1] = beta;
+  }
+  if (last) return;
+  for (int i = tid; i < n; i += 512) {
+    vn[i] *= inv;
+    if (blockIdx.x == 0) v_out[i] = vn[i];
+  }
+  __syncthreads();
+  // rows: one wave each; 16-byte loads where the rows are 16-byte aligned
+  for (int i = blockIdx.x * 8 + wave; i < n; i += gridDim.x * 8) {
+    const float* row = h + (size_t)i * n;
+    double a0 = 0.0, a1 = 0.0;
+    if ((n & 3) == 0 && ((uintptr_t)h & 15) == 0) {
+      const int n4 = n >> 2;
+      const f32x4* row4 = (const f32x4*)row;
+      int q = lane;
+      for (; q + 64 < n4; q += 128) {
+        const f32x4 x0 = row4[q], x1 = row4[q + 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          a0 += (double)x0[e] * vn[4 * q + e];
+          a1 += (double)x1[e] * vn[4 * q + 256 + e];
+        }
+      }
+      if (q < n4) {
+        const f32x4 x0 = row4[q];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a0 += (double)x0[e] * vn[4 * q + e];
+      }
+    } else {
+      for (int q = lane; q < n; q += 64) a0 += (double)row[q] * vn[q];
+    }
+    const double t = wave_sum(a0 + a1);
+    if (lane == 0) w_out[i] = t;
+  }
+}
+
+// n <= 128: all steps in one launch of one workgroup, H in registers: wave w
+// holds rows 8 w .. 8 w + 7, a lane columns lane and lane + 64.  A step is then a
+// few barriers, 3.0 us at n = 128 (two launches took 8.6 with their gaps).  With 16 rows a
+// wave (n <= 256) the registers spill: 12 us a step.
+__global__ __launch_bounds__(1024) void k_lanczos_one(const float* h, int n, int k, double* ab) {
+  constexpr int R = 8, NMAX = 16 * R, C = NMAX / 64;
+  __shared__ double vs[NMAX], wsh[NMAX];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  float hr[R][C];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int i = wave * R + r, q = lane + 64 * c;
+      hr[r][c] = i < n && q < n ? h[(size_t)i * n + q] : 0.0f;
+    }
+  // wave 0 does the vector part alone (two elements a lane): no barrier inside
+  // it, and one wave's square root and division instead of sixteen's
+  double v[C], vp[C], bprev = 0.0;
+  if (wave == 0) {
+    double a = 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int i = lane + 64 * c;
+      v[c] = i < n ? hash_unit(i) : 0.0;
+      vp[c] = 0.0;
+      a += v[c] * v[c];
+    }
+    const double inv = 1.0 / sqrt(wave_sum(a));
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      v[c] *= inv;
+      vs[lane + 64 * c] = v[c];
+    }
+  }
+  __syncthreads();
+  for (int j = 0; j < k; ++j) {
+    double acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const double x = vs[lane + 64 * c];
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[r] += (double)hr[r][c] * x;
+    }
+    // the sums of 8 rows over 64 lanes: halve the rows a lane holds with each exchange
+#pragma unroll
+    for (int off = R / 2; off > 0; off >>= 1) {
+      const bool up = (lane & off) != 0;
+#pragma unroll
+      for (int r = 0; r < off; ++r) {
+        const double keep = up ? acc[r + off] : acc[r], send = up ? acc[r] : acc[r + off];
+        acc[r] = keep + __shfl_xor(send, off, 64);
+      }
+    }
+#pragma unroll
+    for (int off = R; off < 64; off <<= 1) acc[0] += __shfl_xor(acc[0], off, 64);
+    if (lane < R) wsh[wave * R + lane] = acc[0];
+    __syncthreads();
+    if (wave == 0) {
+      double w[C], a = 0.0, b = 0.0;
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        w[c] = wsh[lane + 64 * c];
+        a += v[c] * w[c];
+      }
+      const double alpha = wave_sum(a);
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        w[c] = w[c] - alpha * v[c] - bprev * vp[c];
+        b += w[c] * w[c];
+      }
+      const double beta = sqrt(wave_sum(b));
+      const double inv = beta > 0.0 ? 1.0 / beta : 0.0;
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        vp[c] = v[c];
+        v[c] = w[c] * inv;
+        vs[lane + 64 * c] = v[c];
+      }
+      bprev = beta;
+      if (lane == 0) {
+        ab[2 * j] = alpha;
+        ab[2 * j + 1] = beta;
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// Spectral bounds from the Lanczos coefficients: the extreme Ritz values
+// widened by max(residual, 1 % of the width) and clipped to the Gershgorin
+// interval.  Wave 0 takes the lower end, wave 1 the upper one.  Bound by serial
+// chains: every round tries 64 points of the interval at once, one per lane, and
+// a Sturm count is a chain of two products a row instead of a division.  33 us
+// for 32 steps, where the host took a synchronisation, three copies and 40 - 60
+// us of bisections: whole solves at n = 128 lose 110 us with the kernels above.
+constexpr int kMaxLanczos = 512;
+__global__ __launch_bounds__(128) void k_ritz_bounds(const double* ab, int k, Ctl* ctl) {
+  __shared__ double sa[kMaxLanczos + 8], sb[kMaxLanczos], sb2[kMaxLanczos + 8];   // T and its squared off-diagonal
+  __shared__ double sd[2][kMaxLanczos], sl[2][kMaxLanczos], sx[2][kMaxLanczos];
+  __shared__ double ritz[2], comp[2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int i = threadIdx.x; i < k; i += 128) {
+    sa[i] = ab[2 * i];
+    sb[i] = ab[2 * i + 1];
+    sb2[i] = sb[i] * sb[i];
+  }
+  for (int i = k + threadIdx.x; i < k + 8; i += 128) sa[i] = sb2[i] = 0.0;   // read, not used
+  __syncthreads();
+  if (ctl->nonfinite) {   // the step kernel reports it
+    if (threadIdx.x == 0) set_coeffs(ctl, ctl->gmin, ctl->gmax);
+    return;
+  }
+  auto wmax = [&](double v) {
+    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+    return v;
+  };
+  // truncate at breakdown (invariant subspace: the Ritz values are exact)
+  double scale = 0.0;
+  for (int i = lane; i < k; i += 64) scale = fmax(scale, fabs(sa[i]) + fabs(sb[i]));
+  scale = fmax(wmax(scale), 1e-300);
+  int kk = k;
+  for (int i = lane; i < k; i += 64)
+    if (sb[i] <= 1e-12 * scale) kk = kk < i + 1 ? kk : i + 1;
+  for (int o = 32; o > 0; o >>= 1) kk = min(kk, __shfl_xor(kk, o, 64));
+  const double beta_last = kk < k ? 0.0 : sb[k - 1];
+  double lo = 1e300, hi = -1e300;
+  for (int i = lane; i < kk; i += 64) {
+    const double r = (i ? fabs(sb[i - 1]) : 0.0) + (i + 1 < kk ? fabs(sb[i]) : 0.0);
+    lo = fmin(lo, sa[i] - r);
+    hi = fmax(hi, sa[i] + r);
+  }
+  lo = -wmax(-lo);
+  hi = wmax(hi);
+  const int want = wave == 0 ? 0 : kk - 1;   // the want-th smallest eigenvalue
+  for (int it = 0; it < 16 && hi - lo > 1e-15 * fmax(1.0, fabs(hi) + fabs(lo)); ++it) {
+    const double x = lo + (hi - lo) * ((lane + 1) / 65.0);
+    // eigenvalues below x: sign changes of the leading minors p_i of T - x
+    int cnt = 0;
+    double pm = 1.0, p = sa[0] - x;
+    if (p == 0.0) p = -1e-200;
+    cnt += p < 0.0;
+    for (int i0 = 1; i0 < kk; i0 += 8) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const double q = (sa[i0 + e] - x) * p - sb2[i0 + e - 1] * pm;
+        const bool in = i0 + e < kk;
+        pm = in ? p : pm;
+        const double r = q == 0.0 ? (pm > 0.0 ? -1e-200 : 1e-200) : q;   // a zero counts as a change
+        p = in ? r : p;
+        cnt += in && (p < 0.0) != (pm < 0.0);
+      }
+      // keep both in range (a power of two)
+      const int ex = -ilogb(fmax(fabs(p), fabs(pm)));
+      p = ldexp(p, ex);
+      pm = ldexp(pm, ex);
+    }
+    const unsigned long long above = __ballot(cnt > want);   // points above the eigenvalue
+    const int first = above ? __ffsll((long long)above) - 1 : 64;
+    const double step = (hi - lo) / 65.0;
+    const double nlo = first > 0 ? lo + (hi - lo) * (first / 65.0) : lo;
+    const double nhi = first < 64 ? lo + (hi - lo) * ((first + 1) / 65.0) : hi;
+    if (!(step > 0.0) || (nlo == lo && nhi == hi)) break;
+    lo = nlo;
+    hi = nhi;
+  }
+  const double theta = 0.5 * (lo + hi);
+  if (lane == 0) ritz[wave] = theta;
+  __syncthreads();
+  const double tmin = ritz[0], tmax = ritz[1];
+  const double width = fmax(tmax - tmin, 1e-12 * fmax(1.0, fabs(tmax)));
+  // |last component| of the extreme Ritz vectors: three steps of inverse
+  // iteration with the shift just outside the spectrum (T - shift is definite
+  // and its LDL^T solve stable)
+  if (lane == 0) {
+    double *d = sd[wave], *l = sl[wave], *x = sx[wave];
+    const double sh = theta + (wave == 0 ? -1.0 : 1.0) * 1e-10 * fmax(width, 1e-300);
+    double di = 1.0 / (sa[0] - sh);
+    d[0] = di;
+    x[0] = 1.0;
+#pragma unroll 8
+    for (int i = 1; i < kk; ++i) {
+      const double li = sb[i - 1] * di;
+      di = 1.0 / (sa[i] - sh - li * sb[i - 1]);
+      l[i] = li;
+      d[i] = di;
+      x[i] = 1.0;
+    }
+    double inv = 1.0;   // the previous step's normalisation
+    for (int it = 0; it < 3; ++it) {
+      double y = x[0] * inv;
+      x[0] = y;
+#pragma unroll 8
+      for (int i = 1; i < kk; ++i) {
+        y = x[i] * inv - l[i] * y;
+        x[i] = y;
+      }
+      y = x[kk - 1] * d[kk - 1];
+      x[kk - 1] = y;
+      double nrm = y * y;
+#pragma unroll 8
+      for (int i = kk - 2; i >= 0; --i) {
+        y = x[i] * d[i] - l[i + 1] * y;
+        x[i] = y;
+        nrm += y * y;
+      }
+      inv = 1.0 / sqrt(nrm);
+    }
+    x[kk - 1] *= inv;
+    comp[wave] = fabs(x[kk - 1]);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const double rmin = beta_last * comp[0], rmax = beta_last * comp[1];
+    double emin = fmax(tmin - fmax(rmin, 0.01 * width), ctl->gmin);
+    double emax = fmin(tmax + fmax(rmax, 0.01 * width), ctl->gmax);
+    if (!(emax > emin)) {
+      emin = ctl->gmin;
+      emax = ctl->gmax;
+    }
+    set_coeffs(ctl, emin, emax);
+  }
+}
+
+hipError_t launch_ritz_bounds(const double* ab, int k, Ctl* ctl, hipStream_t s) {
+  if (k < 1 || k > kMaxLanczos) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_ritz_bounds, dim3(1), dim3(128), 0, s, ab, k, ctl);
   return hipGetLastError();
 }
 
-hipError_t launch_lanczos_step(const float* h, int n, double* v, double* vprev, double* w,
-                               double* ab, int j, hipStream_t s) {
-  hipLaunchKernelGGL(k_gemv, dim3((n + 3) / 4), dim3(256), 0, s, h, v, w, n);
-  hipLaunchKernelGGL(k_lanczos_update, dim3(1), dim3(1024), 0, s, v, vprev, w, ab, j, n);
+// Room in doubles of the vectors of launch_lanczos.
+size_t lanczos_doubles(int n) { return 5 * (size_t)n; }
+
+hipError_t launch_lanczos(const float* h, int n, double* vec, double* ab, int k, hipStream_t s) {
+  if (n <= 128) {
+    hipLaunchKernelGGL(k_lanczos_one, dim3(1), dim3(1024), 0, s, h, n, k, ab);
+    return hipGetLastError();
+  }
+  if (n <= kLanczosLds) {
+    const int grid = (n + 7) / 8 < 256 ? (n + 7) / 8 : 256;
+    auto vb = [&](int q) { return vec + (size_t)(q % 3) * n; };       // v_{q+1}
+    auto wb = [&](int q) { return vec + (size_t)(3 + (q & 1)) * n; };
+    for (int j = 0; j <= k; ++j) {
+      const double* v = j > 0 ? vb(j - 1) : nullptr;
+      const double* vp = j > 1 ? vb(j - 2) : nullptr;
+      const double* w = j > 0 ? wb(j - 1) : nullptr;
+      const int last = j == k ? 1 : 0;
+      hipLaunchKernelGGL(k_lanczos, dim3(last ? 1 : grid), dim3(512), 0, s, h, n, j, v, vp, w, vb(j), wb(j), ab, last);
+    }
+    return hipGetLastError();
+  }
+  // a launch for the product and one for the sums
+  double *v = vec, *vprev = vec + n, *w = vec + 2 * (size_t)n;
+  hipLaunchKernelGGL(k_lanczos_start, dim3(1), dim3(1024), 0, s, v, vprev, n);
+  for (int j = 0; j < k; ++j) {
+    hipLaunchKernelGGL(k_gemv, dim3((n + 3) / 4), dim3(256), 0, s, h, v, w, n);
+    hipLaunchKernelGGL(k_lanczos_update, dim3(1), dim3(1024), 0, s, v, vprev, w, ab, j, n);
+  }
   return hipGetLastError();
 }
 
@@ -2075,7 +2405,8 @@ __global__ __launch_bounds__(256) void k_init(int prec, const float* h, const fl
   const float* src = z == 0 ? h : a + (size_t)(z - 1) * n * n;
   const int t = threadIdx.x;
   int bad = 0;
-  // stage both blocks row-wise (coalesced)
+  // stage both blocks row-wise (coalesced, eight pairs of loads in flight)
+#pragma unroll 8
   for (int e = t; e < 64 * 64; e += 256) {
     const int r = e >> 6, c = e & 63;
     const int gi = bi * 64 + r, gj = bj * 64 + c;
