@@ -277,7 +277,8 @@ dmpt_status dmpt_susceptibility_nonorth(const float* H, const float* Z, const fl
  * Phys. Rev. B 66, 155115 (2002)), run on E = D - I/2 so that FP32 keeps
  * the relative precision of the high-temperature start:
  *   E_0 = -(beta / 2^{m+2}) (H - mu I),  E_{k+1} = 2 E_k (I + 4 E_k^2)^{-1},
- * D = I/2 + E_m; each inverse by Newton-Schulz iterations (the spectrum of
+ * D = I/2 + E_m; each inverse by Newton-Schulz iterations from the linear
+ * polynomial in E_k^2 with the smallest residual (the spectrum of
  * I + 4 E_k^2 lies in [1, 1 + tanh^2(2^{k-1-m} beta w)], w = max |e - mu|
  * over the bounds, which fixes the start and the iteration count).  The
  * response Y = dE/dlambda of each observable runs alongside:
@@ -286,11 +287,12 @@ dmpt_status dmpt_susceptibility_nonorth(const float* H, const float* Z, const fl
  * Newton steps on Tr D(mu) = N_occ with dTr D/dmu = beta Tr[D - D^2]
  * = beta (n/4 - ||E_m||_F^2), safeguarded by bisection; then
  * mu_1 = Tr Y_m / (beta Tr[D - D^2]) and chi = s (Y_m - mu_1 beta (D - D^2)).
- * Products: FP32 MFMA (DMPT_FP32) or the FP16 double-half split
+ * Products: FP32 MFMA (DMPT_FP32), the FP16 double-half split
  * (DMPT_SPLIT_FP16: tiled FP16 copies of every operand, scaled by 2^15 for E,
- * 2^16 for E^2, 2^14 for R and T (entry bounds 1/2, 1/4, 1, 1), and by
- * 2^15 / ||M||_F for the responses and their intermediates); other
- * precisions return DMPT_ERR_UNSUPPORTED.
+ * 2^16 for E^2, 2^14 for R and T (entry bounds 1/2, 1/4, 1, 1), and for the
+ * responses and their intermediates by a power of two from a bound by
+ * ||Y_k||_F) or the two- or three-term BF16 split; other precisions return
+ * DMPT_ERR_UNSUPPORTED.  A batch of observables gives the bits of single runs.
  * H (n x n), A (nobs x n x n) device FP32 symmetric; chi (nobs x n x n) and
  * D (n x n, nullable) device; a0 host (nobs, nullable) = s Tr[A D].  opts:
  * n, nocc, bounds (Lanczos / Gershgorin / given, as for dmpt_sp2_density),

@@ -114,6 +114,7 @@ dmpt_status normalise(const dmpt_opts* o, Opts* r) {
 struct Plan {
   int n, n_pad, nobs, prec, tile, ntile, nb64, nparts_step;
   int ts;                          // tile edge of the small-size kernels (0: the large-size ones)
+  int nparts_cap;                  // step tiles at most (small-size kernels: with 32 x 32 tiles)
   int xslots;
   int ckpt, nckpt;                 // adjoint checkpoint interval (0: every X_n kept) and slot count
   size_t mat_f32, mat_op, mat_op2, mat_meta; // bytes per matrix: master, operand copy (and the
@@ -130,6 +131,7 @@ struct Plan {
   // correction): list-position -> slot tables, the combine lists and the
   // scratch of partial tile sums
   size_t off_split_slot, off_split_slot_proj, off_cjobs, off_cjobs_proj, off_split_buf;
+  size_t off_prod_jobs;            // job list of the residual's products
   size_t total;
   int njobs_max, njobs_proj_max, lz_steps;
 };
@@ -172,19 +174,33 @@ int flush_interval(int prec, int n_pad) {
 //    1.32.  FP32 tiles have four times the MFMA time, and the finer grain
 //    balances it up to five rounds: n = 700 1.27 against 1.61, z = 4 2.15
 //    against 2.48, n = 1000 2.19 against 2.15.
+int square_tile(int prec, int n, int matrices) {
+  const int t32 = (n + 63) / 64 * 2, jobs32 = t32 * (t32 + 1) / 2 * matrices;
+  return jobs32 <= (prec == kFP32 ? 1280 : 512) ? 32 : 64;
+}
 int small_tile(int prec, bool wide_lists, int n, int z, int with_p) {
   const int nmax = wide_lists ? 1984 : prec == kFP32 ? (z <= 1 ? 4608 : z <= 4 ? 2560 : 2048)
                                                      : (z <= 1 ? 2600 : z <= 4 ? 2048 : 1536);
-  if (n > nmax) return 0;
-  const int t32 = (n + 63) / 64 * 2, jobs32 = t32 * (t32 + 1) / 2 * (z + with_p);
-  return jobs32 <= (prec == kFP32 ? 1280 : 512) ? 32 : 64;
+  return n > nmax ? 0 : square_tile(prec, n, z + with_p);
 }
 
-void make_plan(const Opts& o, int nobs, Plan* p, bool small = true) {
+// The same for a solve made of general products (the finite-temperature path; not
+// by the number of observables, whose batches give the bits of single ones).
+// Whole solves with one observable, ms, small / large: FP16 split n = 2048 22.3 /
+// 25.2, n = 2600 29.1 / 36.4, n = 3000 40.7 / 40.6, n = 3500 62.9 / 51.5; FP32, where
+// the padding to 256 and the number of tiles move the large side more, n = 2048
+// 55.1 / 49.9, n = 2300 51.6 / 60.3, n = 3000 107 / 128, n = 3500 171 / 162, n = 4096
+// 324 / 270.  32 x 32 tiles, four observables: FP16 split n = 1000 9.4 against 8.6
+// with 64 x 64, FP32 14.4 against 15.9.
+int product_tile(int prec, int n) {
+  return n > (prec == kFP32 ? 3328 : 2944) ? 0 : square_tile(prec, n, 1);
+}
+
+void make_plan(const Opts& o, int nobs, Plan* p, bool products = false) {
   p->n = o.n;
   const bool adjoint = nobs > 0 && o.sweep == DMPT_SWEEP_ADJOINT;
   const bool wide_lists = nobs > 0 && o.prec == kSplit32 && o.refine == 1;
-  p->ts = small ? small_tile(o.prec, wide_lists, o.n, nobs, adjoint ? 0 : 1) : 0;
+  p->ts = products ? product_tile(o.prec, o.n) : small_tile(o.prec, wide_lists, o.n, nobs, adjoint ? 0 : 1);
   const int pad = p->ts ? 64 : kPadTo;
   p->n_pad = (o.n + pad - 1) / pad * pad;
   p->nobs = nobs;
@@ -192,6 +208,7 @@ void make_plan(const Opts& o, int nobs, Plan* p, bool small = true) {
   p->tile = p->ts ? p->ts : kStepTM;
   p->ntile = p->n_pad / kStepTN;                       // 128-column blocks
   p->nb64 = p->n_pad / 64;
+  p->nparts_cap = p->ts ? small_tile_count(p->n_pad, 32) : step_tile_count(p->n_pad);
   p->nparts_step = p->ts ? small_tile_count(p->n_pad, p->ts) : step_tile_count(p->n_pad);
   // The adjoint keeps X_1 .. X_{max_iter+2} (slot n = X_n; the last launch may
   // write one iterate past the result before the stop is seen), or with a
@@ -208,12 +225,12 @@ void make_plan(const Opts& o, int nobs, Plan* p, bool small = true) {
   // (the FP16 split's sweep launches)
   p->mat_meta = meta_bytes(o.prec == kSplitH ? std::max(p->nb64 * p->nb64, p->nparts_step) : p->nb64 * p->nb64);
   p->lz_steps = o.lanczos_steps;
-  const int ut = p->nparts_step;                       // step tiles covering the upper triangle
+  const int ut = p->nparts_cap;                        // step tiles covering the upper triangle
   p->njobs_max = ut * (1 + std::max(nobs, 0)) + kMaxSplit;
   p->njobs_proj_max = ut * std::max(nobs, 1) + kMaxSplit;
   size_t off = 0;
   p->off_ctl = off; off = align_up(off + sizeof(Ctl));
-  const size_t part_bytes = (size_t)std::max(p->nb64 * p->nb64, p->nparts_step) * sizeof(Part);
+  const size_t part_bytes = (size_t)std::max(p->nb64 * p->nb64, p->nparts_cap) * sizeof(Part);
   p->off_part[0] = off; off = align_up(off + part_bytes);
   p->off_part[1] = off; off = align_up(off + part_bytes);
   p->off_jobs = off; off = align_up(off + (size_t)p->njobs_max * 4);
@@ -243,17 +260,70 @@ void make_plan(const Opts& o, int nobs, Plan* p, bool small = true) {
     p->off_split_slot_proj = off; off = align_up(off + (size_t)p->njobs_proj_max * 4);
     p->off_cjobs = off; off = align_up(off + (size_t)kMaxSplit * 4);
     p->off_cjobs_proj = off; off = align_up(off + (size_t)kMaxSplit * 4);
+    static_assert(kMaxPieces <= 2 * kMaxSplit, "the products' pieces take the split tiles' scratch");
     p->off_split_buf = off; off = align_up(off + (size_t)kMaxSplit * 2 * kSplitTileFloats * sizeof(float));
+    p->off_prod_jobs = off; off = align_up(off + sizeof(ProdJob) * (p->ts ? 0 : prod_list_entries(p->n_pad, 1)));
   }
   p->total = off;
 }
 
-// C = alpha A B^T on the plan's kernels.
-hipError_t gemm_nt(const Plan& p, int prec, const void* A, const void* B, float* C, float alpha, int flush, int sym,
-                   hipStream_t s) {
-  return p.ts ? launch_gemm_small(prec, p.ts, A, B, C, p.n_pad, alpha, flush, sym, s)
-              : launch_gemm_op(prec, A, B, C, p.n_pad, alpha, flush, sym, s);
+// General products of one call on the plan's kernels.  The large-size ones read
+// job lists; each list a call uses is copied once into its workspace area
+// (kProdLists areas for batches of up to nb matrices).
+constexpr int kProdLists = 5;
+size_t prod_area_bytes(const Plan& p, int nb) {
+  return p.ts ? 0 : align_up(sizeof(ProdJob) * prod_list_entries(p.n_pad, nb));
 }
+size_t prod_pieces_bytes(const Plan& p, int nb) {
+  return p.ts ? 0 : sizeof(float) * kSplitTileFloats * (size_t)kMaxPieces * nb;
+}
+struct Products {
+  const Plan& p;
+  hipStream_t s;
+  char* area;
+  int nb;
+  float* pieces;
+  struct Up {
+    const ProdList* list;
+    const ProdJob* jobs;
+  };
+  std::vector<Up> up;
+  hipError_t run(int prec, const ProdArgs& a) {
+    if (p.ts) return launch_prod_small(prec, p.ts, a, s);
+    const ProdList& L = cached_prod_list(p.n_pad, a.kind == kProdFull, a.nb, persistent_grid(1 << 30), a.kind == kProdAnti);
+    for (const Up& u : up)
+      if (u.list == &L) return launch(prec, a, u);
+    if (a.nb > nb || (int)up.size() >= kProdLists) return hipErrorInvalidValue;
+    char* d = area + up.size() * prod_area_bytes(p, nb);
+    hipError_t e = hipMemcpyAsync(d, L.jobs.data(), L.jobs.size() * sizeof(ProdJob), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess && !L.split.empty())
+      e = hipMemcpyAsync(d + L.jobs.size() * sizeof(ProdJob), L.split.data(), L.split.size() * sizeof(ProdJob),
+                         hipMemcpyHostToDevice, s);
+    if (e != hipSuccess) return e;
+    up.push_back(Up{&L, (const ProdJob*)d});
+    return launch(prec, a, up.back());
+  }
+  // C = alpha A B^T, all tiles
+  hipError_t nt(int prec, const void* A, const void* B, float* C, float alpha, int flush) {
+    ProdArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.n = p.n;
+    a.n_pad = p.n_pad;
+    a.nb = 1;
+    a.kind = kProdFull;
+    a.flush = flush;
+    a.a = (const char*)A;
+    a.b = (const char*)B;
+    a.alpha = alpha;
+    a.m = C;
+    return run(prec, a);
+  }
+ private:
+  hipError_t launch(int prec, const ProdArgs& a, const Up& u) {
+    return launch_prod_large(prec, a, u.jobs, (int)u.list->jobs.size(), u.jobs + u.list->jobs.size(),
+                             (int)u.list->split.size(), pieces, s);
+  }
+};
 
 // Plain BF16 matrix set of the refinement sweep: slot q (0/1) of X, or of
 // observable k's Y (stride between observables).
@@ -834,10 +904,11 @@ dmpt_status run(const float* H, const float* A, int nobs, float* chi, float* D, 
       }
     }
     const int flr = flush_interval(rp, p.n_pad);
+    Products prod{p, s, ws + p.off_prod_jobs, 1, (float*)(ws + p.off_split_buf), {}};
     char* rbase = ws + p.off_rf_r;
     for (int k = 0; k < nobs; ++k) {
-      DMPT_HIP(gemm_nt(p, rp, opnd(0), opnd(2 + k), v1, std::ldexp(1.0f, -(ex[0] + ex[2 + k])), flr, 0, s));
-      DMPT_HIP(gemm_nt(p, rp, opnd(2 + nobs + k), opnd(1), v2, std::ldexp(1.0f, -(ex[2 + nobs + k] + ex[1])), flr, 0, s));
+      DMPT_HIP(prod.nt(rp, opnd(0), opnd(2 + k), v1, std::ldexp(1.0f, -(ex[0] + ex[2 + k])), flr));
+      DMPT_HIP(prod.nt(rp, opnd(2 + nobs + k), opnd(1), v2, std::ldexp(1.0f, -(ex[2 + nobs + k] + ex[1])), flr));
       DMPT_HIP(launch_antisym_bf16(v1, v2, p.n_pad, rbase + (size_t)k * bf16_bytes, tl, s));
     }
     // plain BF16 copies of the X_n: slot n of the history (X_1 from the
@@ -1103,10 +1174,11 @@ dmpt_status dmpt_susceptibility(const float* H, const float* A, int32_t nobs, fl
 // padded operand/result) and n x n FP32 matrices for H_perp, D_perp and
 // nobs each of A_perp and chi_perp.
 struct NonorthWS {
-  size_t run, zp, ztp, tp, up, hperp, dperp, aperp, cperp, total;
+  size_t run, zp, ztp, tp, up, hperp, dperp, aperp, cperp, lists, pieces, total;
 };
 
-static NonorthWS nonorth_ws(size_t run_bytes, int n, int n_pad, int nobs) {
+static NonorthWS nonorth_ws(size_t run_bytes, const Plan& p, int nobs) {
+  const int n = p.n, n_pad = p.n_pad;
   NonorthWS w;
   const size_t pad2 = (size_t)n_pad * n_pad * 4, n2 = (size_t)n * n * 4;
   size_t off = align_up(run_bytes);
@@ -1119,6 +1191,8 @@ static NonorthWS nonorth_ws(size_t run_bytes, int n, int n_pad, int nobs) {
   w.dperp = off; off = align_up(off + n2);
   w.aperp = off; off = align_up(off + n2 * nobs);
   w.cperp = off; off = align_up(off + n2 * nobs);
+  w.lists = off; off = align_up(off + prod_area_bytes(p, 1));
+  w.pieces = off; off = align_up(off + prod_pieces_bytes(p, 1));
   w.total = off;
   return w;
 }
@@ -1135,7 +1209,7 @@ size_t dmpt_nonorth_workspace_bytes(const dmpt_opts* opts, int32_t nobs) {
   Opts o;
   Plan p;
   if (nonorth_check(opts, nobs, &o, &p) != DMPT_OK) return 0;
-  return nonorth_ws(p.total, o.n, p.n_pad, nobs).total;
+  return nonorth_ws(p.total, p, nobs).total;
 }
 
 dmpt_status dmpt_susceptibility_nonorth(const float* H, const float* Z, const float* A, int32_t nobs,
@@ -1147,7 +1221,7 @@ dmpt_status dmpt_susceptibility_nonorth(const float* H, const float* Z, const fl
   if (st != DMPT_OK) return st;
   if (!H || !Z || !A) return fail(DMPT_ERR_ARG, "H, Z and A must not be NULL");
   const int n = o.n, np = p.n_pad;
-  const NonorthWS w = nonorth_ws(p.total, n, np, nobs);
+  const NonorthWS w = nonorth_ws(p.total, p, nobs);
   if (!o.ws) return fail(DMPT_ERR_WORKSPACE, "workspace is NULL (need %zu bytes)", w.total);
   if (o.ws_bytes < w.total) return fail(DMPT_ERR_WORKSPACE, "workspace has %zu bytes, need %zu", o.ws_bytes, w.total);
   hipStream_t s = o.stream;
@@ -1163,19 +1237,20 @@ dmpt_status dmpt_susceptibility_nonorth(const float* H, const float* Z, const fl
   float* cperp = chi_perp ? chi_perp : (float*)(ws + w.cperp);
   const size_t n2 = (size_t)n * n;
   const int fl = flush_interval(kFP32, np);
+  Products prod{p, s, ws + w.lists, 1, (float*)(ws + w.pieces), {}};
   // M_perp = Z^T M Z for symmetric M: T = Z^T M^T = Z^T M, then Z^T T^T = Z^T M Z
   auto to_perp = [&](const float* m, float* out) -> dmpt_status {
     DMPT_HIP(launch_pad(m, n, np, up, 0, tl, s));
-    DMPT_HIP(gemm_nt(p, kFP32, ztp, up, tp, 1.0f, fl, 0, s));
-    DMPT_HIP(gemm_nt(p, kFP32, ztp, tp, up, 1.0f, fl, 0, s));
+    DMPT_HIP(prod.nt(kFP32, ztp, up, tp, 1.0f, fl));
+    DMPT_HIP(prod.nt(kFP32, ztp, tp, up, 1.0f, fl));
     DMPT_HIP(launch_copy_out(up, n, np, out, tl, s));
     return DMPT_OK;
   };
   // M = Z M_perp Z^T for symmetric M_perp: T = Z M_perp^T = Z M_perp, then T Z^T
   auto from_perp = [&](const float* m, float* out) -> dmpt_status {
     DMPT_HIP(launch_pad(m, n, np, up, 0, tl, s));
-    DMPT_HIP(gemm_nt(p, kFP32, zp, up, tp, 1.0f, fl, 0, s));
-    DMPT_HIP(gemm_nt(p, kFP32, tp, zp, up, 1.0f, fl, 0, s));
+    DMPT_HIP(prod.nt(kFP32, zp, up, tp, 1.0f, fl));
+    DMPT_HIP(prod.nt(kFP32, tp, zp, up, 1.0f, fl));
     DMPT_HIP(launch_copy_out(up, n, np, out, tl, s));
     return DMPT_OK;
   };
@@ -1201,13 +1276,25 @@ dmpt_status dmpt_susceptibility_nonorth(const float* H, const float* Z, const fl
 // ---------------------------------------------------------------- finite temperature
 
 // Workspace of dmpt_susceptibility_fermi: the bounds part of the plan of an
-// SP2 solve (control block, Lanczos and Gershgorin scratch), then n_pad x
-// n_pad FP32 matrices E, E^2, R, T, V, E_next and, per observable, Y, four
-// product temporaries, and for the FP16 split the operand copies of E, E^2,
-// R, T, E_next, every Y, S and W; trace and a0 partials.
+// SP2 solve (control block, Lanczos and Gershgorin scratch, X_1's partials), then
+// the n_pad x n_pad FP32 matrices E (two, in turn), E^2, R (two), and per
+// observable Y; for split products the operand copies of these and of T, S and
+// W, for FP32 products T, S and W themselves (S, W: one per observable of a
+// group, see fermi_group); the metadata of Y (two sets), S and W; trace and a0
+// partials, and the products' job lists and pieces.
 struct FermiWS {
-  size_t e, e2, r, t, v, en, y, g, sm, u, w, ce, ce2, cr, ct, cen, cy, cs, cw, part, a0p, total;
+  size_t e[2], e2, r[2], t, y, sm, w, ce[2], ce2, cr[2], ct, cy, cs, cw, my[2], ms, mw, part, a0p, lists, pieces, total;
+  size_t meta;   // bytes of one matrix's metadata
 };
+constexpr int kTraceBlocks = 128;
+
+// Observables whose products share a launch: the small sizes need several to
+// fill the chip, the large ones would only need more room for S, W and the pieces.
+static int fermi_group(const Plan& p, int nobs) {
+  const size_t all = ((size_t)1 << 26) / ((size_t)p.n_pad * p.n_pad);
+  const size_t g = p.ts ? all : std::min<size_t>(all, 4);
+  return (int)std::max<size_t>(1, std::min<size_t>((size_t)std::max(nobs, 1), g));
+}
 
 // Operand copy format of the finite-temperature products: none (FP32
 // masters), the scaled FP16 split, or the two- / three-term BF16 split.
@@ -1216,32 +1303,37 @@ static int fermi_copy_prec(int prec) {
 }
 
 static FermiWS fermi_ws(size_t base, const Plan& p, int nobs, int cprec) {
-  const int n_pad = p.n_pad;
   FermiWS w;
-  const size_t m = (size_t)n_pad * n_pad * 4;
-  const size_t mc = cprec == kFP32 ? 0 : (size_t)n_pad * n_pad * operand_bytes(cprec);   // operand copy
+  const size_t m = (size_t)p.n_pad * p.n_pad * 4;
+  const size_t mc = cprec == kFP32 ? 0 : (size_t)p.n_pad * p.n_pad * operand_bytes(cprec);   // operand copy
+  const int g = fermi_group(p, nobs), k = std::max(nobs, 1);
+  w.meta = align_up(meta_bytes(std::max(p.nb64 * p.nb64, p.nparts_cap)));
   size_t off = align_up(base);
-  w.e = off; off = align_up(off + m);
-  w.e2 = off; off = align_up(off + m);
-  w.r = off; off = align_up(off + m);
-  w.t = off; off = align_up(off + m);
-  w.v = off; off = align_up(off + m);
-  w.en = off; off = align_up(off + m);
-  w.y = off; off = align_up(off + m * nobs);
-  w.g = off; off = align_up(off + m);
-  w.sm = off; off = align_up(off + m);
-  w.u = off; off = align_up(off + m);
-  w.w = off; off = align_up(off + m);
-  w.ce = off; off = align_up(off + mc);
-  w.ce2 = off; off = align_up(off + mc);
-  w.cr = off; off = align_up(off + mc);
-  w.ct = off; off = align_up(off + mc);
-  w.cen = off; off = align_up(off + mc);
-  w.cy = off; off = align_up(off + mc * nobs);
-  w.cs = off; off = align_up(off + mc);
-  w.cw = off; off = align_up(off + mc);
-  w.part = off; off = align_up(off + sizeof(double) * 2 * (size_t)trace_sq_blocks(n_pad));
-  w.a0p = off; off = align_up(off + sizeof(double) * kOutBlocks * (size_t)std::max(nobs, 1));
+  auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes); return at; };
+  for (int q = 0; q < 2; ++q) w.e[q] = take(m);
+  w.e2 = take(m);
+  for (int q = 0; q < 2; ++q) w.r[q] = take(m);
+  w.y = take(m * nobs);
+  // one area: T, S and W of FP32 products, or for split products, which keep
+  // these as copies only, the copies of S and W
+  const size_t fx = m * (1 + 2 * (size_t)g), sx = mc * 2 * (size_t)g;
+  w.t = take(mc == 0 ? fx : std::max(fx + mc, sx));
+  w.sm = w.t + m;
+  w.w = w.sm + m * g;
+  w.cs = w.t;
+  w.cw = w.t + mc * g;
+  for (int q = 0; q < 2; ++q) w.ce[q] = take(mc);
+  w.ce2 = take(mc);
+  for (int q = 0; q < 2; ++q) w.cr[q] = take(mc);
+  w.ct = take(mc);
+  w.cy = take(mc * nobs);
+  for (int q = 0; q < 2; ++q) w.my[q] = take(w.meta * k);
+  w.ms = take(w.meta * g);
+  w.mw = take(w.meta * g);
+  w.part = take(sizeof(double) * 2 * kTraceBlocks * (size_t)k);
+  w.a0p = take(sizeof(double) * kOutBlocks * (size_t)k);
+  w.lists = take(kProdLists * prod_area_bytes(p, g));
+  w.pieces = take(prod_pieces_bytes(p, g));
   w.total = off;
   return w;
 }
@@ -1264,7 +1356,7 @@ static dmpt_status fermi_check(const dmpt_opts* opts, const dmpt_fermi_opts* f, 
   if (f->newton_max < 0 || f->newton_max > 200) return fail(DMPT_ERR_ARG, "newton_max out of range [0, 200]");
   if (!(f->count_tol >= 0) || !std::isfinite(f->count_tol)) return fail(DMPT_ERR_ARG, "count_tol must be finite and >= 0");
   if (f->reserved != 0) return fail(DMPT_ERR_ARG, "reserved must be 0");
-  make_plan(*o, 0, p, false);
+  make_plan(*o, 0, p, true);
   return DMPT_OK;
 }
 
@@ -1275,17 +1367,22 @@ size_t dmpt_fermi_workspace_bytes(const dmpt_opts* opts, const dmpt_fermi_opts* 
   return fermi_ws(p.off_x, p, nobs, fermi_copy_prec(o.prec)).total;
 }
 
-// An operand of the finite-temperature products: FP32 master, and for the
-// split formats its tiled copy (FP16 split: at the scale 2^e; BF16: e = 0).
+// A matrix of the finite-temperature recursion: its FP32 form, its operand (the
+// copy of the split formats, at 2^e for the FP16 split; FP32: the matrix), and,
+// where the exponent is the matrix's own, its metadata.
 struct FMat {
   float* m;
-  void* c;
+  char* c;
   int e;
+  char* meta;
 };
 
 // Fixed exponents of the FP16 copies (entry bounds x 2^e <= 2^14..2^15):
-// |E| <= 1/2 (E = D - I/2), |E^2| <= 1/4, |R| <= 1 and |T| <= 1 (spectra in
-// [1/2, 1] and [0, 1]); Y, S and W take 2^15 / ||M||_F (|M_ij| <= ||M||_F).
+// |E| <= 1/2 (E = D - I/2; its start at kXScaleExp), |E^2| <= 1/4, |R| and |T|
+// near 1 (spectra in [1/2, 1] and about 1).  Y, S and W take the exponent that
+// bounds a multiple of ||Y||_F: ||S||_2 <= 2 ||E||_2 ||Y||_F <= ||Y||_F,
+// ||W|| <= (2 + 4 ||E'||_2) ||Y||_F <= 4 ||Y||_F, ||Y'|| <= ||W||, each with a margin.
+constexpr double kBoundS = 1.05, kBoundW = 4.2;
 constexpr int kExpE = 15, kExpE2 = 16, kExpR = 14, kExpT = 14;
 
 dmpt_status dmpt_susceptibility_fermi(const float* H, const float* A, int32_t nobs, float* chi, float* D,
@@ -1309,17 +1406,19 @@ dmpt_status dmpt_susceptibility_fermi(const float* H, const float* A, int32_t no
   char* ws = o.ws;
   Ctl* ctl = (Ctl*)(ws + p.off_ctl);
   const size_t np2 = (size_t)np * np;
-  auto fm = [&](size_t master, size_t copy, size_t k) {
-    return FMat{(float*)(ws + master) + k * np2, split ? (void*)(ws + copy + k * np2 * cbytes) : nullptr, 0};
+  const size_t mop = split ? np2 * cbytes : np2 * 4;   // bytes of one operand
+  auto fm = [&](size_t master, size_t copy, char* meta) {
+    return FMat{(float*)(ws + master), split ? ws + copy : ws + master, 0, meta};
   };
-  FMat E = fm(w.e, w.ce, 0), E2 = fm(w.e2, w.ce2, 0), R = fm(w.r, w.cr, 0), T = fm(w.t, w.ct, 0);
-  FMat En = fm(w.en, w.cen, 0), Sm = fm(w.sm, w.cs, 0), Wm = fm(w.w, w.cw, 0);
-  std::vector<FMat> Y(std::max(nobs, 1));
-  for (int k = 0; k < nobs; ++k) Y[k] = fm(w.y, w.cy, k);
-  float* V = (float*)(ws + w.v);
-  float* G = (float*)(ws + w.g);
-  float* U = (float*)(ws + w.u);
+  FMat E[2] = {fm(w.e[0], w.ce[0], nullptr), fm(w.e[1], w.ce[1], nullptr)};
+  FMat R[2] = {fm(w.r[0], w.cr[0], nullptr), fm(w.r[1], w.cr[1], nullptr)};
+  FMat E2 = fm(w.e2, w.ce2, nullptr), T = fm(w.t, w.ct, nullptr);
+  const FMat Y = fm(w.y, w.cy, nullptr), Sm = fm(w.sm, w.cs, ws + w.ms), Wm = fm(w.w, w.cw, ws + w.mw);
+  char* ymeta[2] = {ws + w.my[0], ws + w.my[1]};
+  const int group = fermi_group(p, nobs);
+  const int tl = p.ts ? 1 : 0;
   double* part = (double*)(ws + w.part);
+  Products prods{p, s, ws + w.lists, group, (float*)(ws + w.pieces), {}};
   const int fl = flush_interval(cprec, np);
   const double beta = 1.0 / fopts->kt;
   ScopedEvents ev;
@@ -1337,51 +1436,56 @@ dmpt_status dmpt_susceptibility_fermi(const float* H, const float* A, int32_t no
   if (hctl.nonfinite) return fail(DMPT_ERR_NONFINITE, "H holds NaN or Inf");
   const double emin = hctl.emin, emax = hctl.emax;
 
-  // traces over the leading n x n block: (Tr M, ||M||_F^2), fixed order
-  auto trace_sq = [&](const float* m, double* tr, double* sq) -> dmpt_status {
-    const int nb = trace_sq_blocks(np);
-    std::vector<double> h(2 * nb);
-    DMPT_HIP(launch_trace_sq(m, n, np, part, s));
-    DMPT_HIP(hipMemcpyAsync(h.data(), part, sizeof(double) * 2 * nb, hipMemcpyDeviceToHost, s));
+  // (Tr M, ||M||_F^2) of nmat matrices (zero padded), fixed order
+  std::vector<double> hpart_tr;
+  auto traces = [&](const float* m, int nmat, std::vector<double>* tr, std::vector<double>* sq) -> dmpt_status {
+    hpart_tr.resize((size_t)2 * kTraceBlocks * nmat);
+    DMPT_HIP(launch_trace_sq(m, np2, nmat, n, np, tl, part, kTraceBlocks, s));
+    DMPT_HIP(hipMemcpyAsync(hpart_tr.data(), part, sizeof(double) * hpart_tr.size(), hipMemcpyDeviceToHost, s));
     DMPT_HIP(hipStreamSynchronize(s));
-    double a = 0.0, b = 0.0;
-    for (int i = 0; i < nb; ++i) { a += h[2 * i]; b += h[2 * i + 1]; }
-    *tr = a;
-    *sq = b;
+    tr->assign(nmat, 0.0);
+    sq->assign(nmat, 0.0);
+    for (int k = 0; k < nmat; ++k)
+      for (int i = 0; i < kTraceBlocks; ++i) {
+        (*tr)[k] += hpart_tr[2 * ((size_t)k * kTraceBlocks + i)];
+        (*sq)[k] += hpart_tr[2 * ((size_t)k * kTraceBlocks + i) + 1];
+      }
     return DMPT_OK;
-  };
-  // operand copy at a fixed exponent, or at 2^15 / ||M||_F
-  auto refresh = [&](FMat& a, int e) -> dmpt_status {
-    if (!split) return DMPT_OK;
-    if (cprec != kSplitH) {   // BF16 terms keep the FP32 exponent range: no scale
-      a.e = 0;
-      DMPT_HIP(launch_copy_src(cprec, a.m, np, a.c, np, 0, 0, 0, s));
-      return DMPT_OK;
-    }
-    a.e = e;
-    DMPT_HIP(launch_split_copy(a.m, a.c, np, e, s));
-    return DMPT_OK;
-  };
-  auto refresh_dyn = [&](FMat& a) -> dmpt_status {
-    if (!split) return DMPT_OK;
-    if (cprec != kSplitH) return refresh(a, 0);
-    double tr = 0.0, sq = 0.0;
-    dmpt_status e = trace_sq(a.m, &tr, &sq);
-    if (e != DMPT_OK) return e;
-    const double nrm = std::sqrt(sq);
-    int ex = 0;
-    if (nrm > 0 && std::isfinite(nrm)) ex = std::max(-100, std::min(100, (int)std::floor(std::log2(32768.0 / nrm))));
-    return refresh(a, ex);
   };
   int products = 0;
-  // out = alpha a b^T (all tiles, or the symmetric triangle + mirror)
-  auto prod = [&](const FMat& a, const FMat& b, float* out, double alpha, bool sym) -> dmpt_status {
-    ++products;
-    if (split)
-      DMPT_HIP(gemm_nt(p, cprec, a.c, b.c, out, (float)std::ldexp(alpha, -(a.e + b.e)), fl, sym ? 1 : 0, s));
-    else
-      DMPT_HIP(gemm_nt(p, kFP32, a.m, b.m, out, (float)alpha, fl, sym ? 1 : 0, s));
-    return DMPT_OK;
+  // V = alpha P + beta X, P from operands a and b (per-matrix strides sa, sb)
+  auto product = [&](ProdKind kind, int nb, const FMat& a, size_t sa, const FMat& b, size_t sb, double alpha) {
+    ProdArgs q;
+    std::memset(&q, 0, sizeof(q));
+    q.n = n;
+    q.n_pad = np;
+    q.nb = nb;
+    q.kind = kind;
+    q.flush = fl;
+    q.a = a.c;
+    q.b = b.c;
+    q.sa = sa;
+    q.sb = sb;
+    q.ea = a.e;
+    q.eb = b.e;
+    if (cprec == kSplitH) {
+      q.ma = a.meta;
+      q.mb = b.meta;
+      q.sma = q.smb = w.meta;
+    }
+    q.alpha = (float)alpha;
+    products += nb;
+    return q;
+  };
+  // V's operand: the copy at 2^e, or for FP32 products the matrix itself
+  auto to_operand = [&](ProdArgs* q, FMat* v, int e) {
+    if (split) {
+      v->e = cprec == kSplitH ? e : 0;
+      q->c = v->c;
+      q->ec = v->e;
+    } else {
+      q->m = v->m;
+    }
   };
   auto doublings_for = [&](double mu) {
     if (fopts->doublings > 0) return fopts->doublings;
@@ -1391,59 +1495,119 @@ dmpt_status dmpt_susceptibility_fermi(const float* H, const float* A, int32_t no
     return m;
   };
   // The recursion at mu; with ny > 0 also the responses Y_k (k < ny) of the
-  // observables.  Leaves E_m in E.m and E_m^2 in E2.m.
+  // observables.  Leaves E_m in E[cur].m and E_m^2 in E2.m.  Nothing in it waits
+  // for the device: the exponents of the FP16 copies are found there.
+  int cur = 0;
   auto recursion = [&](double mu, int ny, int* m_out) -> dmpt_status {
     const int m = doublings_for(mu);
     *m_out = m;
     const double c = beta / std::ldexp(1.0, m + 2);
     const double wmax = std::max(std::fabs(emax - mu), std::fabs(emin - mu));
-    dmpt_status e;
-    DMPT_HIP(launch_fermi_start(H, n, np, -c, mu, E.m, s));
-    if ((e = refresh(E, kExpE)) != DMPT_OK) return e;
-    for (int k = 0; k < ny; ++k) {
-      DMPT_HIP(launch_fermi_start(A + (size_t)k * n * n, n, np, -c, 0.0, Y[k].m, s));
-      if ((e = refresh_dyn(Y[k])) != DMPT_OK) return e;
-    }
+    cur = 0;
+    int ym = 0;   // Y's metadata set
+    // E_0 = c mu I - c H and Y_0 = -c A with their operands
+    DMPT_HIP(launch_set_affine(ctl, c * mu, -c, s));
+    auto ref = [&](const FMat& x, char* meta, size_t smeta) {
+      MatRef r;
+      r.f32 = x.m;
+      r.op = x.c;
+      r.stride_f32 = np2;
+      r.stride_op = mop;
+      r.meta = meta;
+      r.stride_meta = smeta;
+      return r;
+    };
+    E[0].e = cprec == kSplitH ? kXScaleExp : 0;
+    const MatRef yr = ref(Y, ymeta[0], w.meta);
+    DMPT_HIP(launch_init(cprec, tl, H, A, n, np, ny, ref(E[0], ymeta[0], 0), yr, -c, (Part*)(ws + p.off_part[0]), ctl, s));
+    if (cprec == kSplitH && ny > 0) DMPT_HIP(launch_resplit(cprec, yr, np, ny, tl, s));
     for (int step = 0; step < m; ++step) {
-      if ((e = prod(E, E, E2.m, 1.0, true)) != DMPT_OK) return e;
-      if ((e = refresh(E2, kExpE2)) != DMPT_OK) return e;
-      // R = (I + 4 E^2)^{-1}: spectrum in [1, b], b from |E_k| <= tanh(2^{k-1-m} beta w) / 2
-      // (with a margin for the linearised start and rounding)
+      FMat &Ec = E[cur], &En = E[cur ^ 1];
+      // R = (I + 4 E^2)^{-1}: spectrum of I + 4 E^2 in [1, b], b from
+      // |E_k| <= tanh(2^{k-1-m} beta w) / 2 (with a margin for the linearised
+      // start and rounding).  Start: the linear polynomial in E^2 whose residual
+      // is the scaled Chebyshev polynomial T_2, written by the launch that forms
+      // E^2; then Newton-Schulz steps, each squaring the residual.
       const double th = std::tanh(std::ldexp(beta * wmax, step - 1 - m));
       const double b = 1.0 + std::min(1.0, 1.02 * th * th + 1e-6);
-      const double alpha = 2.0 / (1.0 + b);
-      double err = (b - 1.0) / (b + 1.0);
+      const double cen = 0.5 * (b + 1.0), hw = 0.5 * (b - 1.0), den = 2.0 * cen * cen - hw * hw;
+      double err = hw * hw / den;
       int iters = 0;
       while (err > 1e-8 && iters < 8) { err *= err; ++iters; }
-      DMPT_HIP(launch_axpby(R.m, E2.m, 0.0f, nullptr, 0.0f, (float)alpha, np, np, s));
-      if ((e = refresh(R, kExpR)) != DMPT_OK) return e;
-      for (int it = 0; it < iters; ++it) {
-        // T = (I + 4 E^2) R, V = R T, R = 2 R - V
-        if ((e = prod(E2, R, T.m, 4.0, true)) != DMPT_OK) return e;
-        DMPT_HIP(launch_axpby(T.m, T.m, 1.0f, R.m, 1.0f, 0.0f, 0, np, s));
-        if ((e = refresh(T, kExpT)) != DMPT_OK) return e;
-        if ((e = prod(R, T, V, 1.0, true)) != DMPT_OK) return e;
-        DMPT_HIP(launch_axpby(R.m, R.m, 2.0f, V, -1.0f, 0.0f, 0, np, s));
-        if ((e = refresh(R, kExpR)) != DMPT_OK) return e;
+      int rc = 0;
+      ProdArgs q = product(kProdSym, 1, Ec, 0, Ec, 0, 1.0);
+      if (iters > 0) to_operand(&q, &E2, kExpE2);
+      q.g0 = (float)((4.0 * cen - 2.0) / den);
+      q.g1 = (float)(-8.0 / den);
+      q.m2 = R[0].m;
+      if (split) {
+        R[0].e = R[1].e = cprec == kSplitH ? kExpR : 0;
+        q.c2 = R[0].c;
+        q.ec2 = R[0].e;
       }
-      // E_next = 2 E R
-      if ((e = prod(E, R, En.m, 2.0, true)) != DMPT_OK) return e;
-      if ((e = refresh(En, kExpE)) != DMPT_OK) return e;
-      for (int k = 0; k < ny; ++k) {
-        // S = Y E + E Y; U = E_next S; W = 2 Y - 4 U; Y = sym(W R)
-        if ((e = prod(Y[k], E, G, 1.0, false)) != DMPT_OK) return e;
-        DMPT_HIP(launch_symm(G, 1.0f, nullptr, 0.0f, Sm.m, np, s));
-        if ((e = refresh_dyn(Sm)) != DMPT_OK) return e;
-        if ((e = prod(En, Sm, U, 1.0, false)) != DMPT_OK) return e;
-        DMPT_HIP(launch_axpby(Wm.m, Y[k].m, 2.0f, U, -4.0f, 0.0f, 0, np, s));
-        if ((e = refresh_dyn(Wm)) != DMPT_OK) return e;
-        if ((e = prod(Wm, R, G, 1.0, false)) != DMPT_OK) return e;
-        DMPT_HIP(launch_symm(G, 0.5f, nullptr, 0.0f, Y[k].m, np, s));
-        if (step + 1 < m && (e = refresh_dyn(Y[k])) != DMPT_OK) return e;
+      DMPT_HIP(prods.run(cprec, q));
+      for (int it = 0; it < iters; ++it, rc ^= 1) {
+        // T = (I + 4 E^2) R, R' = 2 R - R T
+        q = product(kProdSym, 1, E2, 0, R[rc], 0, 4.0);
+        q.beta = 1.0f;
+        q.x = R[rc].m;
+        to_operand(&q, &T, kExpT);
+        DMPT_HIP(prods.run(cprec, q));
+        q = product(kProdSym, 1, R[rc], 0, T, 0, -1.0);
+        q.beta = 2.0f;
+        q.x = R[rc].m;
+        q.m = R[rc ^ 1].m;
+        to_operand(&q, &R[rc ^ 1], kExpR);
+        DMPT_HIP(prods.run(cprec, q));
       }
-      std::swap(E, En);
+      // E' = 2 E R
+      q = product(kProdSym, 1, Ec, 0, R[rc], 0, 2.0);
+      to_operand(&q, &En, kExpE);
+      if (step + 1 == m) q.m = En.m;
+      DMPT_HIP(prods.run(cprec, q));
+      for (int k0 = 0; k0 < ny; k0 += group) {
+        // S = Y E + E Y; W = 2 Y - 4 E' S; Y' = (W R + R W^T) / 2
+        const int nb = std::min(group, ny - k0);
+        FMat Yk = Y, S = Sm, W = Wm;
+        Yk.m += (size_t)k0 * np2;
+        Yk.c += (size_t)k0 * mop;
+        Yk.meta = ymeta[ym] + (size_t)k0 * w.meta;
+        auto scaled = [&](ProdArgs* v, FMat* x, double bound, char* meta_out) {
+          to_operand(v, x, 0);
+          if (cprec != kSplitH) return;
+          v->mn = Yk.meta;
+          v->smn = w.meta;
+          v->bound = bound;
+          v->mo = meta_out;
+          v->smo = w.meta;
+        };
+        q = product(kProdAnti, nb, Yk, mop, Ec, 0, 1.0);
+        scaled(&q, &S, kBoundS, S.meta);
+        q.sm = np2;
+        q.sc = mop;
+        DMPT_HIP(prods.run(cprec, q));
+        q = product(kProdFull, nb, En, 0, S, mop, -4.0);
+        q.beta = 2.0f;
+        q.x = Yk.m;
+        q.sx = np2;
+        scaled(&q, &W, kBoundW, W.meta);
+        q.sm = np2;
+        q.sc = mop;
+        DMPT_HIP(prods.run(cprec, q));
+        q = product(kProdAnti, nb, W, mop, R[rc], 0, 0.5);
+        q.m = Yk.m;
+        q.sm = np2;
+        if (step + 1 < m) scaled(&q, &Yk, kBoundW, ymeta[ym ^ 1] + (size_t)k0 * w.meta);
+        q.m = Yk.m;
+        q.sc = mop;
+        DMPT_HIP(prods.run(cprec, q));
+      }
+      ym ^= 1;
+      cur ^= 1;
     }
-    if ((e = prod(E, E, E2.m, 1.0, true)) != DMPT_OK) return e;
+    ProdArgs q = product(kProdSym, 1, E[cur], 0, E[cur], 0, 1.0);
+    q.m = E2.m;
+    DMPT_HIP(prods.run(cprec, q));
     return DMPT_OK;
   };
 
@@ -1454,6 +1618,15 @@ dmpt_status dmpt_susceptibility_fermi(const float* H, const float* A, int32_t no
   double mu = fopts->mu;
   int newton = 0, m = 0;
   double tre = 0.0, sqe = 0.0;
+  std::vector<double> vtr, vsq;
+  auto trace_e = [&]() -> dmpt_status {
+    const dmpt_status e = traces(E[cur].m, 1, &vtr, &vsq);
+    if (e == DMPT_OK) {
+      tre = vtr[0];
+      sqe = vsq[0];
+    }
+    return e;
+  };
   bool have_final = false;
   if (fopts->canonical) {
     const double nocc = o.nocc;
@@ -1466,7 +1639,7 @@ dmpt_status dmpt_susceptibility_fermi(const float* H, const float* A, int32_t no
     for (newton = 1; newton <= maxn; ++newton) {
       products = 0;
       if ((st = recursion(mu, with_obs ? nobs : 0, &m)) != DMPT_OK) return st;
-      if ((st = trace_sq(E.m, &tre, &sqe)) != DMPT_OK) return st;
+      if ((st = trace_e()) != DMPT_OK) return st;
       const double count = 0.5 * n + tre;
       const double slope = beta * (0.25 * n - sqe);   // dTr D / dmu = beta Tr[D - D^2]
       if (std::fabs(count - nocc) <= tol) { have_final = with_obs || nobs == 0; break; }
@@ -1485,25 +1658,23 @@ dmpt_status dmpt_susceptibility_fermi(const float* H, const float* A, int32_t no
   if (!have_final) {
     products = 0;
     if ((st = recursion(mu, nobs, &m)) != DMPT_OK) return st;
-    if ((st = trace_sq(E.m, &tre, &sqe)) != DMPT_OK) return st;
+    if ((st = trace_e()) != DMPT_OK) return st;
   }
   const double trdd = 0.25 * n - sqe;   // Tr[D - D^2]
+  // chi' = Y + mu_1 chi_gc(I), chi_gc(I) = -beta (D - D^2) = -beta (I/4 - E^2)
   std::vector<double> mu1(std::max(nobs, 1), 0.0);
-  for (int k = 0; k < nobs; ++k) {
-    if (fopts->canonical && trdd > 0) {
-      double try_ = 0.0, sqy = 0.0;
-      if ((st = trace_sq(Y[k].m, &try_, &sqy)) != DMPT_OK) return st;
-      mu1[k] = try_ / (beta * trdd);
-      // chi' = Y + mu_1 chi_gc(I), chi_gc(I) = -beta (D - D^2) = -beta (I/4 - E^2)
-      const float gam = (float)(-mu1[k] * beta);
-      DMPT_HIP(launch_axpby(Y[k].m, Y[k].m, 1.0f, E2.m, -gam, 0.25f * gam, n, np, s));
+  FermiShift shift = {};
+  if (nobs > 0 && fopts->canonical && trdd > 0) {
+    if ((st = traces(Y.m, nobs, &vtr, &vsq)) != DMPT_OK) return st;
+    for (int k = 0; k < nobs; ++k) {
+      mu1[k] = vtr[k] / (beta * trdd);
+      shift.g[k] = (float)(-mu1[k] * beta);
     }
   }
-  // D = I/2 + E (into E^2's buffer, no longer needed), outputs and a0 = s Tr[A D]
-  DMPT_HIP(launch_axpby(E2.m, E.m, 1.0f, nullptr, 0.0f, 0.5f, n, np, s));
+  // D = I/2 + E, chi = s chi' and a0 = s Tr[A D]
   double* a0p = (double*)(ws + w.a0p);
-  DMPT_HIP(launch_output(E2.m, nobs ? Y[0].m : nullptr, np2, A, n, np, nobs, D, nobs ? chi : nullptr, o.spin, 0,
-                         0, a0p, ctl, s));
+  DMPT_HIP(launch_fermi_output(E[cur].m, E2.m, Y.m, np2, A, n, np, nobs, tl, shift, o.spin, D, nobs ? chi : nullptr, a0p,
+                               kOutBlocks, s));
   std::vector<double> hpart((size_t)kOutBlocks * std::max(nobs, 1));
   if (nobs) DMPT_HIP(hipMemcpyAsync(hpart.data(), a0p, sizeof(double) * hpart.size(), hipMemcpyDeviceToHost, s));
   DMPT_HIP(hipEventRecord(ev.e1, s));

@@ -98,7 +98,13 @@ __device__ __forceinline__ double meta_norm(const MatMeta* m, int cap, double* s
   if (threadIdx.x < 64) {
     const int cnt = m->count < cap ? m->count : cap;
     double t = 0.0;
-    for (int i = threadIdx.x; i < cnt; i += 64) t += m->nrm[i];
+    for (int i = threadIdx.x; i < cnt; i += 64 * 16) {   // 16 loads in flight, added in order
+      double u[16];
+#pragma unroll
+      for (int z = 0; z < 16; ++z) u[z] = i + 64 * z < cnt ? m->nrm[i + 64 * z] : 0.0;
+#pragma unroll
+      for (int z = 0; z < 16; ++z) t += u[z];
+    }
     t = wave_sum(t);
     if (threadIdx.x == 0) *s_out = sqrt(t);
   }
@@ -169,6 +175,104 @@ __device__ __forceinline__ void store_group8_t(char* op, int nst, int r, int c0,
     for (int e = 0; e < 4; ++e) w[e] = part[2 * e][t] | ((unsigned)part[2 * e + 1][t] << 16);
     *(u32x4*)(op + op_off<PREC>(r, c0, t, nst, small)) = w;
   }
+}
+
+template <bool WG>
+__device__ __forceinline__ void region_sync() {
+  if constexpr (WG) {
+    __syncthreads();
+  } else {   // one wave: its LDS accesses in order
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Epilogue of a general product (ProdArgs) on one TS x TS region of V at
+// (gr0, gc0), whose product sums stand in T (row stride LS): NTH threads (a
+// workgroup, or with WG false one wave).  sym: the region is stored at its
+// mirror place too; a region on the diagonal keeps its upper triangle.
+// Returns this thread's part of ||V||_F^2 over the region and its mirror.
+template <int PREC, int TS, int LS, int NTH, bool WG, int SMALL>
+__device__ __forceinline__ double prod_region(const ProdArgs& a, int k, LDS_AS float* T, int tid, int gr0, int gc0,
+                                              bool sym, float alpha, float sc) {
+  constexpr int V4 = TS / 4, V8 = TS / 8;
+  const bool diag = sym && gr0 == gc0;
+  const float* x = a.x ? a.x + (size_t)k * a.sx : nullptr;
+  double sq = 0.0;
+  constexpr int NX = (TS * V4 + NTH - 1) / NTH;
+  f32x4 xv[NX];   // all of X's loads in flight at once
+#pragma unroll
+  for (int z = 0; z < NX; ++z) {
+    const int e = tid + z * NTH, r = SMALL ? e % TS : e / V4, c = 4 * (SMALL ? e / TS : e % V4);
+    xv[z] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    if (x && e < TS * V4) xv[z] = *(const f32x4*)(x + m_off(SMALL, gr0 + r, gc0 + c, a.n_pad));
+  }
+#pragma unroll
+  for (int z = 0; z < NX; ++z) {
+    const int e = tid + z * NTH, r = SMALL ? e % TS : e / V4, c = 4 * (SMALL ? e / TS : e % V4);
+    if (e >= TS * V4) continue;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (diag && r > c + q) continue;
+      float v = alpha * T[r * LS + c + q] + a.beta * xv[z][q];
+      if (gr0 + r == gc0 + c + q && gr0 + r < a.n) v += a.delta;
+      T[r * LS + c + q] = v;
+      if (a.mo) sq += (sym && !(diag && r == c + q) ? 2.0 : 1.0) * (double)v * (double)v;
+    }
+  }
+  region_sync<WG>();
+  auto at = [&](bool mir, int r, int c) { return mir || (diag && r > c) ? T[c * LS + r] : T[r * LS + c]; };
+  const bool two = sym && !diag;   // also the mirror region
+  float* m = a.m ? a.m + (size_t)k * a.sm : nullptr;
+  if (m || a.m2) {
+#pragma unroll 4
+    for (int e = tid; e < (two ? 2 : 1) * TS * V4; e += NTH) {
+      const bool mir = e >= TS * V4;
+      const int g = mir ? e - TS * V4 : e, r = SMALL ? g % TS : g / V4, c = 4 * (SMALL ? g / TS : g % V4);
+      const int gr = (mir ? gc0 : gr0) + r, gc = (mir ? gr0 : gc0) + c;
+      f32x4 v;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = at(mir, r, c + q);
+      const size_t o = m_off(SMALL, gr, gc, a.n_pad);
+      if (m) *(f32x4*)(m + o) = v;
+      if (a.m2) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = a.g1 * v[q] + (gr == gc + q && gr < a.n ? a.g0 : 0.0f);
+        *(f32x4*)(a.m2 + o) = v;
+      }
+    }
+  }
+  if constexpr (PREC != kFP32) {
+    char* cp = a.c ? a.c + (size_t)k * a.sc : nullptr;
+    if (cp || a.c2) {
+      const int nst = a.n_pad / Fmt<PREC>::K;
+      const float sc2 = PREC == kSplitH ? ldexpf(1.0f, a.ec2) : 1.0f;
+#pragma unroll 2
+      for (int e = tid; e < (two ? 2 : 1) * TS * V8; e += NTH) {
+        const bool mir = e >= TS * V8;
+        const int g = mir ? e - TS * V8 : e, r = SMALL ? g % TS : g / V8, c = 8 * (SMALL ? g / TS : g % V8);
+        const int gr = (mir ? gc0 : gr0) + r, gc = (mir ? gr0 : gc0) + c;
+        float v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = at(mir, r, c + q);
+        if (cp) store_group8_t<PREC>(cp, nst, gr, gc, v, sc, SMALL);
+        if (a.c2) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) v[q] = a.g1 * v[q] + (gr == gc + q && gr < a.n ? a.g0 : 0.0f);
+          store_group8_t<PREC>(a.c2, nst, gr, gc, v, sc2, SMALL);
+        }
+      }
+    }
+  }
+  return sq;
+}
+
+// Scale of the product sums (undoes the copies' exponents) and exponent of V's
+// copy, for kSplitH; nrm: the norm behind `bound`.
+__device__ __forceinline__ float prod_scale(const ProdArgs& a, int k) {
+  const int ea = a.ma ? ((const MatMeta*)(a.ma + (size_t)k * a.sma))->scale : a.ea;
+  const int eb = a.mb ? ((const MatMeta*)(a.mb + (size_t)k * a.smb))->scale : a.eb;
+  return ldexpf(1.0f, -(ea + eb));
 }
 
 // The step controller's decision at launch k = a.step from the sums of the

@@ -1,24 +1,27 @@
-// Internal launchers of the finite-temperature path (dmpt_fermi.hip).  All
-// matrices are n_pad x n_pad row-major FP32 (zero padded beyond n).
+// Internal launchers of the finite-temperature path (dmpt_fermi.hip).
+// Matrices are n_pad x n_pad FP32, zero padded, row-major or (tiled) in the
+// small-size kernels' layout.
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 
+#include "dmpt_internal.h"
+
 namespace dmpt {
 
-// dst = scale (sym(src) - shift I_n), sym(S) = (S + S^T) / 2, src n x n (ld n).
-hipError_t launch_fermi_start(const float* src, int n, int n_pad, double scale, double shift, float* dst,
-                              hipStream_t s);
-// z = a x + b y + d I_nd (y may be NULL; I_nd: ones on the first nd diagonal entries).
-hipError_t launch_axpby(float* z, const float* x, float a, const float* y, float b, float d, int nd, int n_pad,
-                        hipStream_t s);
-// out = alpha (in + in^T) + beta x (x may be NULL); out must not alias in.
-hipError_t launch_symm(const float* in, float alpha, const float* x, float beta, float* out, int n_pad,
-                       hipStream_t s);
-// FP64 per-row-block partials over the leading n x n block: part[2b] = trace,
-// part[2b + 1] = sum of squares, b = 0 .. n_pad / 4 - 1 (four rows per block).
-hipError_t launch_trace_sq(const float* m, int n, int n_pad, double* part, hipStream_t s);
-int trace_sq_blocks(int n_pad);
+// FP64 partials of (Tr M, ||M||_F^2) of nmat matrices (`stride` floats apart):
+// part[2 (k nblk + b)], part[2 (k nblk + b) + 1] for block b of matrix k.
+hipError_t launch_trace_sq(const float* m, size_t stride, int nmat, int n, int n_pad, int tiled, double* part, int nblk,
+                           hipStream_t s);
+// Shift of each observable: chi'_k = Y_k + g_k (I/4 - E^2).
+struct FermiShift {
+  float g[kMaxObs];
+};
+// D = I/2 + E, chi_k = scale chi'_k (n x n, row-major; either may be NULL) and the
+// FP64 partials of Tr[A_k D] (nblk per observable).
+hipError_t launch_fermi_output(const float* e, const float* e2, const float* y, size_t ystride, const float* a, int n,
+                               int n_pad, int nobs, int tiled, FermiShift shift, double scale, float* d_out,
+                               float* chi_out, double* a0_part, int nblk, hipStream_t s);
 
 }  // namespace dmpt

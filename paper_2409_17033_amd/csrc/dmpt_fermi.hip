@@ -1,155 +1,114 @@
-// Elementwise and reduction kernels of the finite-temperature path (Sec. V.B).
-// The products of the recursion run on k_gemm_nt (FP32 MFMA); these kernels
-// form the start matrices, linear combinations, symmetrisations and traces.
+// Reductions and outputs of the finite-temperature path (Sec. V.B).  The products
+// of the recursion and everything elementwise between them run in the general
+// product kernels (ProdArgs).
 #include <hip/hip_runtime.h>
 
+#include "dmpt_device.h"
 #include "dmpt_fermi.h"
 
 namespace dmpt {
 
 namespace {
 
-__device__ __forceinline__ double wave_sum64(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
-// One 64 x 64 output block per workgroup; the block and its transpose are
-// staged through LDS so both are read row-wise.
-__global__ __launch_bounds__(256) void k_fermi_start(const float* src, int n, int n_pad, double scale, double shift,
-                                                     float* dst) {
-  __shared__ float t[64][65];
-  __shared__ float tt[64][65];
-  const int bi = blockIdx.y, bj = blockIdx.x;
-  for (int e = threadIdx.x; e < 64 * 64; e += 256) {
-    const int r = e >> 6, c = e & 63;
-    const int gi = bi * 64 + r, gj = bj * 64 + c;
-    const int hi = bj * 64 + r, hj = bi * 64 + c;
-    t[r][c] = (gi < n && gj < n) ? src[(size_t)gi * n + gj] : 0.0f;
-    tt[r][c] = (hi < n && hj < n) ? src[(size_t)hi * n + hj] : 0.0f;
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < 64 * 64; e += 256) {
-    const int r = e >> 6, c = e & 63;
-    const int gi = bi * 64 + r, gj = bj * 64 + c;
-    double v = 0.5 * ((double)t[r][c] + (double)tt[c][r]);
-    if (gi == gj && gi < n) v -= shift;
-    dst[(size_t)gi * n_pad + gj] = (gi < n && gj < n) ? (float)(scale * v) : 0.0f;
-  }
-}
-
-// One row per block iteration (coalesced, no index division).
-__global__ __launch_bounds__(256) void k_axpby(float* z, const float* x, float a, const float* y, float b, float d,
-                                               int nd, int n_pad) {
-  for (int i = blockIdx.x; i < n_pad; i += gridDim.x) {
-    const size_t row = (size_t)i * n_pad;
-    for (int j = threadIdx.x; j < n_pad; j += 256) {
-      float v = a * x[row + j];
-      if (y) v += b * y[row + j];
-      if (i == j && i < nd) v += d;
-      z[row + j] = v;
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void k_symm(const float* in, float alpha, const float* x, float beta, float* out,
-                                              int n_pad) {
-  __shared__ float t[64][65];
-  __shared__ float tt[64][65];
-  const int bi = blockIdx.y, bj = blockIdx.x;
-  for (int e = threadIdx.x; e < 64 * 64; e += 256) {
-    const int r = e >> 6, c = e & 63;
-    t[r][c] = in[(size_t)(bi * 64 + r) * n_pad + bj * 64 + c];
-    tt[r][c] = in[(size_t)(bj * 64 + r) * n_pad + bi * 64 + c];
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < 64 * 64; e += 256) {
-    const int r = e >> 6, c = e & 63;
-    const size_t o = (size_t)(bi * 64 + r) * n_pad + bj * 64 + c;
-    float v = alpha * (t[r][c] + tt[c][r]);
-    if (x) v += beta * x[o];
-    out[o] = v;
-  }
-}
-
-// Block b sums rows 64b .. 64b + 63 of the leading n x n block, one wave per
-// 16 rows, in a fixed order.
-// (Tr M, ||M||_F^2) over the leading n x n block of an n_pad-strided matrix:
-// one wave per row, 16-byte loads when the rows allow it (n % 4 == 0 and M
-// 16-byte aligned), two accumulators per lane; block b adds its four rows in
-// order into part[2b], part[2b + 1] (the host sums the blocks in order).
-__global__ __launch_bounds__(256) void k_trace_sq(const float* m, int n, int n_pad, double* part) {
+// Block b of matrix k sums the squares of its share of the 16-byte pieces, in a
+// fixed order, and the diagonal entries i = b (mod nblk).  Padding is zero, so
+// the layout does not matter for the squares.
+__global__ __launch_bounds__(256) void k_trace_sq(const float* m, size_t stride, int n, int n_pad, int tiled, double* part) {
   __shared__ double s_tr[4], s_sq[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int i = blockIdx.x * 4 + wave;
-  double tr = 0.0, sq0 = 0.0, sq1 = 0.0;
-  if (i < n) {
-    const float* row = m + (size_t)i * n_pad;
-    if ((n & 3) == 0 && ((uintptr_t)m & 15) == 0) {
-      typedef float f4 __attribute__((ext_vector_type(4)));
-      const f4* row4 = (const f4*)row;
-      const int n4 = n >> 2;
-      int q = lane;
-      for (; q + 64 < n4; q += 128) {
-        const f4 x0 = row4[q], x1 = row4[q + 64];
+  const float* mk = m + (size_t)blockIdx.y * stride;
+  const f32x4* m4 = (const f32x4*)mk;
+  const size_t n4 = (size_t)n_pad * n_pad / 4;
+  double sq[2] = {0.0, 0.0}, tr = 0.0;
+  const size_t step = (size_t)gridDim.x * 256;
+  size_t q = (size_t)blockIdx.x * 256 + threadIdx.x;
+  for (; q + step < n4; q += 2 * step) {
+    const f32x4 x0 = m4[q], x1 = m4[q + step];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          sq0 += (double)x0[e] * (double)x0[e];
-          sq1 += (double)x1[e] * (double)x1[e];
-        }
-      }
-      if (q < n4) {
-        const f4 x0 = row4[q];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sq0 += (double)x0[e] * (double)x0[e];
-      }
-    } else {
-      for (int j = lane; j < n; j += 64) {
-        const double v = row[j];
-        sq0 += v * v;
-      }
+    for (int e = 0; e < 4; ++e) {
+      sq[0] += (double)x0[e] * (double)x0[e];
+      sq[1] += (double)x1[e] * (double)x1[e];
     }
-    if (lane == 0) tr = row[i];
   }
-  const double sq = wave_sum64(sq0 + sq1);
-  if (lane == 0) {
-    s_tr[wave] = tr;
-    s_sq[wave] = sq;
+  if (q < n4) {
+    const f32x4 x0 = m4[q];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sq[0] += (double)x0[e] * (double)x0[e];
+  }
+  for (int i = blockIdx.x + (int)threadIdx.x * gridDim.x; i < n; i += 256 * gridDim.x) tr += mk[m_off(tiled, i, i, n_pad)];
+  const double s = wave_sum(sq[0] + sq[1]), t = wave_sum(tr);
+  if ((threadIdx.x & 63) == 0) {
+    s_tr[threadIdx.x >> 6] = t;
+    s_sq[threadIdx.x >> 6] = s;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = s_tr[0] + s_tr[1] + s_tr[2] + s_tr[3];
-    part[2 * blockIdx.x + 1] = s_sq[0] + s_sq[1] + s_sq[2] + s_sq[3];
+    double* o = part + 2 * ((size_t)blockIdx.y * gridDim.x + blockIdx.x);
+    o[0] = s_tr[0] + s_tr[1] + s_tr[2] + s_tr[3];
+    o[1] = s_sq[0] + s_sq[1] + s_sq[2] + s_sq[3];
+  }
+}
+
+// A wave takes 16 x 16 pieces: 4 columns of a row per lane, 16 lanes down the
+// rows of a tiled matrix (256-byte reads) or along a row-major one's.
+__global__ __launch_bounds__(256) void k_fermi_output(const float* em, const float* e2, const float* y, size_t ystride,
+                                                      const float* a, int n, int n_pad, int nobs, int tiled,
+                                                      FermiShift shift, double scale, float* d_out, float* chi_out,
+                                                      double* a0_part) {
+  __shared__ double s_red[4];
+  const size_t n2 = (size_t)n * n;
+  const int k = blockIdx.y, lane = threadIdx.x & 63;
+  // row-major: 4 rows x 64 columns a piece
+  const int pr = tiled ? 16 : 4, pc = tiled ? 16 : 64;
+  const int cg = (n + pc - 1) / pc, rg = (n + pr - 1) / pr;
+  const size_t pieces = (size_t)rg * cg;
+  double acc = 0.0;
+  for (size_t p = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6); p < pieces; p += (size_t)gridDim.x * 4) {
+    const int i = (int)(p / cg) * pr + (tiled ? lane & 15 : lane >> 4);
+    const int j = (int)(p % cg) * pc + 4 * (tiled ? lane >> 4 : lane & 15);
+    if (i >= n || j >= n) continue;
+    const size_t o = m_off(tiled, i, j, n_pad), e = (size_t)i * n + j;
+    f32x4 dv = *(const f32x4*)(em + o);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (i == j + q) dv[q] += 0.5f;
+    if (k == 0 && d_out)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (j + q < n) d_out[e + q] = dv[q];
+    if (nobs > 0) {
+      f32x4 yv = *(const f32x4*)(y + (size_t)k * ystride + o);
+      const float g = shift.g[k];
+      const f32x4 ev = *(const f32x4*)(e2 + o);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (j + q >= n) break;
+        const float v = yv[q] - g * ev[q] + (i == j + q ? 0.25f * g : 0.0f);
+        if (chi_out) chi_out[(size_t)k * n2 + e + q] = (float)(scale * (double)v);
+        acc += (double)dv[q] * (double)a[(size_t)k * n2 + e + q];
+      }
+    }
+  }
+  if (nobs > 0) {
+    acc = wave_sum(acc);
+    if (lane == 0) s_red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) a0_part[(size_t)k * gridDim.x + blockIdx.x] = s_red[0] + s_red[1] + s_red[2] + s_red[3];
   }
 }
 
 }  // namespace
 
-hipError_t launch_fermi_start(const float* src, int n, int n_pad, double scale, double shift, float* dst,
-                              hipStream_t s) {
-  const int nb = n_pad / 64;
-  hipLaunchKernelGGL(k_fermi_start, dim3(nb, nb), dim3(256), 0, s, src, n, n_pad, scale, shift, dst);
+hipError_t launch_trace_sq(const float* m, size_t stride, int nmat, int n, int n_pad, int tiled, double* part, int nblk,
+                           hipStream_t s) {
+  hipLaunchKernelGGL(k_trace_sq, dim3(nblk, nmat), dim3(256), 0, s, m, stride, n, n_pad, tiled, part);
   return hipGetLastError();
 }
 
-hipError_t launch_axpby(float* z, const float* x, float a, const float* y, float b, float d, int nd, int n_pad,
-                        hipStream_t s) {
-  hipLaunchKernelGGL(k_axpby, dim3(2048), dim3(256), 0, s, z, x, a, y, b, d, nd, n_pad);
-  return hipGetLastError();
-}
-
-hipError_t launch_symm(const float* in, float alpha, const float* x, float beta, float* out, int n_pad,
-                       hipStream_t s) {
-  const int nb = n_pad / 64;
-  hipLaunchKernelGGL(k_symm, dim3(nb, nb), dim3(256), 0, s, in, alpha, x, beta, out, n_pad);
-  return hipGetLastError();
-}
-
-int trace_sq_blocks(int n_pad) { return n_pad / 4; }   // one row per wave, four per block
-
-hipError_t launch_trace_sq(const float* m, int n, int n_pad, double* part, hipStream_t s) {
-  hipLaunchKernelGGL(k_trace_sq, dim3(trace_sq_blocks(n_pad)), dim3(256), 0, s, m, n, n_pad, part);
+hipError_t launch_fermi_output(const float* e, const float* e2, const float* y, size_t ystride, const float* a, int n,
+                               int n_pad, int nobs, int tiled, FermiShift shift, double scale, float* d_out,
+                               float* chi_out, double* a0_part, int nblk, hipStream_t s) {
+  hipLaunchKernelGGL(k_fermi_output, dim3(nblk, nobs > 0 ? nobs : 1), dim3(256), 0, s, e, e2, y, ystride, a, n, n_pad, nobs,
+                     tiled, shift, scale, d_out, chi_out, a0_part);
   return hipGetLastError();
 }
 

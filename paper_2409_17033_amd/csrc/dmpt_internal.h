@@ -121,6 +121,7 @@ struct MatRef {
   size_t stride_f32;   // elements
   size_t stride_op;    // bytes
   char* meta;
+  size_t stride_meta = 0;   // bytes between observables' metadata (0: stride_op)
   void* op2 = nullptr; // kSplit3 matrices of the kSplit32 option: their two-term (kSplit2) copy,
                        // written next to the three-term one (same (hi, lo = RNE(x - hi)) terms)
 };
@@ -169,6 +170,8 @@ size_t lanczos_doubles(int n);
 hipError_t launch_lanczos(const float* h, int n, double* vec, double* ab, int k, hipStream_t s);
 // Bounds (ctl's alpha, beta) from k Lanczos coefficients and the Gershgorin interval.
 hipError_t launch_ritz_bounds(const double* ab, int k, Ctl* ctl, hipStream_t s);
+// ctl's alpha and beta (launch_init forms alpha I + beta H).
+hipError_t launch_set_affine(Ctl* ctl, double alpha, double beta, hipStream_t s);
 hipError_t launch_set_bounds(Ctl* ctl, double emin, double emax, hipStream_t s);
 // tiled (here and below): the padded FP32 matrices and the operand copies are
 // in the small-size kernels' layouts (m_off, op_off in dmpt_device.h).
@@ -197,10 +200,7 @@ hipError_t launch_step_combine(int prec, StepArgs args, const uint32_t* cjobs, i
 // n_pad a multiple of 64.  One step launch over nz observables' Z tiles and,
 // with with_p, the P tiles (the controller runs with the P tiles only).
 hipError_t launch_step_small(int prec, int ts, const StepArgs& args, int nz, int with_p, hipStream_t s);
-// C = alpha A B^T; FP32 operands and C tiled, split copies as launch_gemm_op's;
-// sym: both triangles are stored.
-hipError_t launch_gemm_small(int prec, int ts, const void* A, const void* B, float* C, int n_pad, float alpha, int flush,
-                             int sym, hipStream_t s);
+hipError_t launch_prod_small(int prec, int ts, const struct ProdArgs& args, hipStream_t s);
 inline int small_tile_count(int n_pad, int ts) { const int t = n_pad / ts; return t * (t + 1) / 2; }
 // Upper bound of the norm partials a producer writes for one matrix.
 __host__ __device__ inline int meta_entries(int n_pad) { return (n_pad / 32) * (n_pad / 32); }
@@ -222,21 +222,53 @@ hipError_t launch_response(const float* chi, int nobs, const float* h1, int nper
                            double* part, int nblk, double* out_dev, int ld, hipStream_t s);
 int response_blocks(size_t n2);
 hipError_t launch_copy_out(const float* src, int n, int n_pad, float* dst, int tiled, hipStream_t s);
-// Non-orthonormal basis: C = alpha A B^T (n_pad x n_pad, n_pad % 256 == 0,
-// FP32 MFMA) and zero-padded (optionally transposed) copies.
-hipError_t launch_gemm_nt(const float* A, const float* B, float* C, int n_pad, float alpha, int flush,
-                          hipStream_t s);
-// The same for a product known to be symmetric: upper-triangle tiles only,
-// then the lower triangle mirrored (exactly symmetric result).
-hipError_t launch_gemm_nt_sym(const float* A, const float* B, float* C, int n_pad, float alpha, int flush,
-                              hipStream_t s);
-// General form: operands FP32 row-major (prec = kFP32) or tiled FP16 split
-// copies (prec = kSplitH, written by launch_split_copy); sym as above.
-hipError_t launch_gemm_op(int prec, const void* A, const void* B, float* C, int n_pad, float alpha, int flush,
-                          int sym, hipStream_t s);
-// Tiled FP16 split copy (the kSplitH operand format) of an n_pad x n_pad FP32
-// matrix scaled by 2^e.
-hipError_t launch_split_copy(const float* src, void* dst, int n_pad, int e, hipStream_t s);
+// General products of n_pad x n_pad matrices with a fused epilogue, for a batch
+// of `nb` matrices (strides in bytes of operands and copies, in elements of
+// FP32 matrices; 0: shared by the batch):
+//   V = alpha P + beta X + delta I_n,  P = A B^T (all tiles, or kProdSym: known
+//   to be symmetric, upper triangle and its mirror) or kProdAnti: A B^T + B A^T.
+// Operands: FP32 matrices (kFP32) or operand copies; for kSplitH the copies'
+// exponents ea, eb (ma, mb set: the matrix's own, from its metadata).  Outputs
+// (each may be NULL): V as FP32 (m) and as an operand copy (c; kSplitH: at 2^ec,
+// or with mn set at the exponent that bounds `bound` x the Frobenius norm in the
+// metadata mn; mo then receives that exponent and, of a symmetric V, its norm
+// partials), and g0 I_n + g1 V likewise (m2, c2 at 2^ec2).  V must not overlap the
+// operands; X may be V's own FP32 matrix.
+enum ProdKind : int { kProdFull = 0, kProdSym = 1, kProdAnti = 2 };
+struct ProdArgs {
+  int n, n_pad, nb, kind, flush;
+  const char *a, *b;
+  size_t sa, sb;
+  int ea, eb;
+  const char *ma, *mb;
+  size_t sma, smb;
+  float alpha, beta, delta;
+  const float* x;
+  size_t sx;
+  float* m;
+  size_t sm;
+  char* c;
+  size_t sc;
+  int ec;
+  const char* mn;
+  size_t smn;
+  double bound;
+  char* mo;
+  size_t smo;
+  float g0, g1;
+  float* m2;
+  char* c2;
+  int ec2;
+};
+// Large-size kernel: one workgroup per entry of a job list (dmpt_lists.h,
+// ProdJob); the last tiles of a list run in pieces of their K range, whose sums
+// go to `pieces` and are added by a second launch.
+struct ProdJob {
+  uint32_t tile;    // row block (256) | column block (128) << 16
+  uint32_t part;    // piece | pieces << 4 | batch index << 8 | first slot << 16
+};
+hipError_t launch_prod_large(int prec, const ProdArgs& args, const ProdJob* jobs, int njobs, const ProdJob* split,
+                             int nsplit, float* pieces, hipStream_t s);
 hipError_t launch_pad(const float* src, int n, int n_pad, float* dst, int transpose, int tiled, hipStream_t s);
 // Residual refinement helpers.
 //   launch_copy_src: tiled operand copy (prec kSplitH at scale 2^e, kSplit3 or

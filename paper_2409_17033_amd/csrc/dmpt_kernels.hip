@@ -1302,46 +1302,101 @@ hipError_t launch_queue_reset(Ctl* ctl, hipStream_t s) {
 
 // ---------------------------------------------------------------- general products
 
-// C = alpha A B^T over all 256 x 128 tiles of an n_pad x n_pad result (or,
-// with sym, only the tiles (I, J >= 2I) that cover the upper triangle, for a
-// product known to be symmetric); C is n_pad x n_pad row-major FP32 (zero
-// padded).  The operands are FP32 row-major (PREC = kFP32) or tiled FP16
-// split copies (PREC = kSplitH; alpha then carries the 2^-(s_a + s_b) that
-// undoes their scales).  Used for the congruences of the non-orthonormal
-// basis (Sec. V.A: Z^T H Z, Z^T A Z, Z D Z^T, two NT products each) and the
-// products of the finite-temperature recursion (Sec. V.B).  Same operand
-// pipeline as the step kernel (DMA into the four-slot LDS ring, MFMA,
-// two-level accumulation every `flush` groups of 4 stages); the epilogue
-// stores the tile as is.
+// Large-size kernel of the general products (ProdArgs): the congruences of the
+// non-orthonormal basis (Sec. V.A), the residual of the correction, and the
+// finite-temperature recursion (Sec. V.B).  One 256 x 128 tile, or a piece of its
+// K range, per workgroup, from a job list; the step kernel's operand pipeline
+// (DMA into the four-slot LDS ring, MFMA, two-level accumulation every `flush`
+// groups of 4 stages).
+//
+// A list of tiles that does not fill its last round is what bounds these
+// products at many sizes: at n = 4096 a symmetric product has 272 tiles on 256
+// CUs and took as long as a full one with 512.  The last tiles of a list
+// therefore run in pieces of their K range (build_prod_list); a piece stores
+// its sums (FP32, coalesced) and k_prod_combine adds the pieces in FP64 and
+// runs the epilogue.  The epilogue (linear combination, mirror, operand copies,
+// norm) is fused: separate passes for them took a quarter of a
+// finite-temperature solve.
+// n = 4096, FP16 split: symmetric product 325 us unsplit (and a mirror pass), now
+// 184 us with the pieces and 24 us for the combine launch; a full product 309 us
+// (1.33 PFLOP/s executed), bound by the MFMAs.  Whole solve, one observable, 170 ms
+// before, 79 ms now.  Of that 5 ms are from the epilogue's loads (X, the norm
+// partials) being in flight together.
+__device__ __forceinline__ int prod_ti(uint32_t t) { return (int)(t & 0xffff); }
+__device__ __forceinline__ int prod_tj(uint32_t t) { return (int)(t >> 16); }
+
+// The region of V that wave w of the tile's eight owns, 64 x 64 at (w / 2, w % 2),
+// from the sums `tot`, staged in T.
 template <int PREC>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_nt(
-    const void* A, const void* B, float* C, int n_pad, float alpha, int flush, int sym) {
-  using P = Pipe<PREC>;
-  __shared__ __attribute__((aligned(1024))) char ring0[P::SLOT];
-  __shared__ __attribute__((aligned(1024))) char ring1[P::SLOT];
-  __shared__ __attribute__((aligned(1024))) char ring2[P::SLOT];
-  __shared__ __attribute__((aligned(1024))) char ring3[P::SLOT];
-  const int tcols = n_pad / TN;
-  int ti, tj;
-  if (sym) {   // row-major order over the triangle tiles
-    int b = blockIdx.x;
-    ti = 0;
-    while (b >= tcols - 2 * ti) {
-      b -= tcols - 2 * ti;
-      ++ti;
+__device__ __forceinline__ double prod_wave(const ProdArgs& a, int k, const f32x16 (&tot)[BR][BC], LDS_AS float* T,
+                                            int ti, int tj, int wave, int lane, float alpha, float sc) {
+  const int h = lane >> 5, l32 = lane & 31;
+  const int gr0 = ti * TM + (wave >> 1) * 64, gc0 = tj * TN + (wave & 1) * 64;
+  const bool sym = a.kind != kProdFull;
+  if (sym && gr0 > gc0) return 0.0;   // below the diagonal: the mirror of another region
+#pragma unroll
+  for (int bi = 0; bi < BR; ++bi)
+#pragma unroll
+    for (int bj = 0; bj < BC; ++bj)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) T[(bi * 32 + 8 * g + 4 * h + e) * kLS + bj * 32 + l32] = tot[bi][bj][4 * g + e];
+  region_sync<false>();
+  return prod_region<PREC, 64, kLS, 64, false, 0>(a, k, T, lane, gr0, gc0, sym, alpha, sc);
+}
+
+// Exponent of V's copy (kSplitH): every workgroup finds the same one.
+template <int PREC>
+__device__ __forceinline__ int prod_exp(const ProdArgs& a, int k, double* s_nrm) {
+  if constexpr (PREC == kSplitH) {
+    if (a.mn) {
+      const int nb = a.n_pad / 64;
+      return yscale_exp(meta_norm((const MatMeta*)(a.mn + (size_t)k * a.smn), nb * nb, s_nrm), a.bound);
     }
-    tj = 2 * ti + b;
-  } else {
-    ti = blockIdx.x / tcols;
-    tj = blockIdx.x % tcols;
   }
+  return a.ec;
+}
+
+// Norm partials of a symmetric V: one per wave of each tile.
+__device__ __forceinline__ void prod_norm(const ProdArgs& a, int k, double sq, int ti, int tj, int wave, int lane, int ec) {
+  if (!a.mo) return;
+  MatMeta* mo = (MatMeta*)(a.mo + (size_t)k * a.smo);
+  const bool full = a.kind == kProdFull;   // the exponent only
+  const int idx = full ? ti | tj | wave : NW * tile_index(ti, tj, a.n_pad / TN) + wave;
+  if (!full) sq = wave_sum(sq);
+  if (lane != 0) return;
+  if (!full) mo->nrm[idx] = sq;
+  if (idx == 0) {
+    mo->scale = ec;
+    mo->count = full ? 0 : NW * (a.n_pad / TM) * (a.n_pad / TM + 1);
+  }
+}
+
+template <int PREC>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_prod_large(ProdArgs a, const ProdJob* jobs,
+                                                                                               float* pieces) {
+  using P = Pipe<PREC>;
+  constexpr int RSZ = P::SLOT > 2 * kStageBytes ? P::SLOT : 2 * kStageBytes;
+  __shared__ __attribute__((aligned(1024))) char ring0[RSZ];
+  __shared__ __attribute__((aligned(1024))) char ring1[RSZ];
+  __shared__ __attribute__((aligned(1024))) char ring2[RSZ];
+  __shared__ __attribute__((aligned(1024))) char ring3[RSZ];
+  __shared__ double s_nrm;
+  const ProdJob job = jobs[blockIdx.x];
+  const int ti = prod_ti(job.tile), tj = prod_tj(job.tile);
+  const int piece = job.part & 15, npc = (job.part >> 4) & 15, k = (job.part >> 8) & 255, slot0 = job.part >> 16;
   // row block I / J starts at the same byte offset in the row-major and the
   // tiled layouts (rows * ldb, or row blocks * nst chunks of 128 rows)
-  const size_t ldb = (size_t)n_pad * operand_bytes(PREC);
+  const size_t ldb = (size_t)a.n_pad * operand_bytes(PREC);
   const uint32_t ldb32 = (uint32_t)ldb;
-  const int nst = n_pad / Fmt<PREC>::K;
-  const char* a0 = (const char*)A + (size_t)ti * TM * ldb;
-  const char* b0 = (const char*)B + (size_t)tj * TN * ldb;
+  const int spass = a.n_pad / Fmt<PREC>::K;
+  const int nst = a.kind == kProdAnti ? 2 * spass : spass;
+  // this piece's stages [sb, se): whole groups of 4
+  const int n4 = nst / 4, sb = n4 * piece / npc * 4, se = n4 * (piece + 1) / npc * 4;
+  const char* pa = a.a + (size_t)k * a.sa;
+  const char* pb = a.b + (size_t)k * a.sb;
+  const size_t rI = (size_t)ti * TM * ldb, rJ = (size_t)tj * TN * ldb;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = wave >> 1, wc = wave & 1;
@@ -1355,47 +1410,52 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
       acc[i][j] = f32x16{0};
       tot[i][j] = f32x16{0};
     }
-  // stages past the end re-fetch stage 0 into a slot that is never read again
-  auto dma = [&](LDS_AS char* slot, int s) {
-    const int st = s < nst ? s : 0;
-    if constexpr (P::TILED) {
-      const char* ca = a0 + (size_t)st * P::CHUNK;
-      dma_stage_tiled<PREC>(slot, ca, ca + (size_t)nst * P::CHUNK, b0 + (size_t)st * P::CHUNK, wave, lane);
-    } else {
-      const size_t kb = (size_t)st * P::RB;
-      dma_stage_rows<PREC>(slot, a0 + kb, b0 + kb, ldb32, wave, lane);
-    }
+  // the stages in order (kProdAnti: A_I B_J^T, then B_I A_J^T); past the end
+  // the piece's first again, into a slot that is never read
+  const size_t step_b = P::TILED ? (size_t)P::CHUNK : (size_t)P::RB, a_hi = (size_t)spass * P::CHUNK;
+  const char *a0 = pa + rI, *b0 = pb + rJ, *a1 = pb + rI, *b1 = pa + rJ;
+  const char* fA = sb < spass ? a0 + (size_t)sb * step_b : a1 + (size_t)(sb - spass) * step_b;
+  const char* fB = sb < spass ? b0 + (size_t)sb * step_b : b1 + (size_t)(sb - spass) * step_b;
+  const char *cA = fA, *cB = fB;
+  int cs = sb;
+  auto dma = [&](LDS_AS char* slot) {
+    if constexpr (P::TILED) dma_stage_tiled<PREC>(slot, cA, cA + a_hi, cB, wave, lane);
+    else dma_stage_rows<PREC>(slot, cA, cB, ldb32, wave, lane);
+    ++cs;
+    const bool wrap = cs >= se, second = cs == spass;
+    cA = wrap ? fA : second ? a1 : cA + step_b;
+    cB = wrap ? fB : second ? b1 : cB + step_b;
   };
   LDS_AS char* R0 = (LDS_AS char*)ring0;
   LDS_AS char* R1 = (LDS_AS char*)ring1;
   LDS_AS char* R2 = (LDS_AS char*)ring2;
   LDS_AS char* R3 = (LDS_AS char*)ring3;
   Ops<PREC> o0, o1;
-  dma(R0, 0);
-  dma(R1, 1);
-  dma(R2, 2);
+  dma(R0);
+  dma(R1);
+  dma(R2);
   wait_vm<2 * P::L, false>();
   barrier_nofence();
-  dma(R3, 3);
+  dma(R3);
   __builtin_amdgcn_sched_barrier(0);
   read_ops<PREC>(R0, o0, rowA, rowB, h);
-#define DMPT_GITER(S_, NEXT, REFILL, OC, ON)              \
+#define DMPT_GITER(NEXT, REFILL, OC, ON)                  \
   {                                                       \
     wait_vm<2 * P::L, true>();                            \
     barrier_nofence();                                    \
-    dma(REFILL, (S_) + 4);                                \
+    dma(REFILL);                                          \
     __builtin_amdgcn_sched_barrier(0);                    \
     read_ops<PREC>(NEXT, ON, rowA, rowB, h);              \
     mma_ops<PREC>(OC, acc);                               \
     stage_order<PREC>();                                  \
   }
-  const int fl4 = flush > 0 ? flush : 1 << 30;
+  const int fl4 = a.flush > 0 ? a.flush : 1 << 30;
   int since = 0;
-  for (int s = 0; s < nst; s += 4) {
-    DMPT_GITER(s + 0, R1, R0, o0, o1)
-    DMPT_GITER(s + 1, R2, R1, o1, o0)
-    DMPT_GITER(s + 2, R3, R2, o0, o1)
-    DMPT_GITER(s + 3, R0, R3, o1, o0)
+  for (int s = sb; s < se; s += 4) {
+    DMPT_GITER(R1, R0, o0, o1)
+    DMPT_GITER(R2, R1, o1, o0)
+    DMPT_GITER(R3, R2, o0, o1)
+    DMPT_GITER(R0, R3, o1, o0)
     if (++since == fl4) {
       since = 0;
 #pragma unroll
@@ -1409,70 +1469,100 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   }
 #undef DMPT_GITER
   wait_vm<0, true>();
-  // 32x32 MFMA output layout: lane l, register 4g+e holds row 8g + 4(l/32) + e, column l%32.
 #pragma unroll
-  for (int bi = 0; bi < BR; ++bi)
+  for (int i = 0; i < BR; ++i)
 #pragma unroll
-    for (int bj = 0; bj < BC; ++bj) {
-      const f32x16 v = tot[bi][bj] + acc[bi][bj];
-      const int col = tj * TN + wc * 64 + bj * 32 + l32;
+    for (int j = 0; j < BC; ++j) tot[i][j] += acc[i][j];
+  if (npc > 1) {
+    float* out = pieces + (size_t)(slot0 + piece) * kSplitTileFloats;
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
+    for (int q = 0; q < BR * BC; ++q)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = ti * TM + wr * 64 + bi * 32 + 8 * g + 4 * h + e;
-          C[(size_t)r * n_pad + col] = alpha * v[4 * g + e];
-        }
-    }
-}
-
-hipError_t launch_gemm_nt(const float* A, const float* B, float* C, int n_pad, float alpha, int flush,
-                          hipStream_t s) {
-  if (n_pad <= 0 || n_pad % TM != 0) return hipErrorInvalidValue;
-  const int tiles = (n_pad / TM) * (n_pad / TN);
-  hipLaunchKernelGGL(k_gemm_nt<kFP32>, dim3(tiles), dim3(NT), 0, s, A, B, C, n_pad, alpha, flush, 0);
-  return hipGetLastError();
-}
-
-// Strictly lower triangle of C := transpose of the upper one (64 x 64 blocks
-// through LDS; blocks above the diagonal are read, never written).
-__global__ __launch_bounds__(256) void k_mirror_lower(float* C, int n_pad) {
-  __shared__ float t[64][65];
-  const int bi = blockIdx.y, bj = blockIdx.x;   // destination block (bi >= bj)
-  if (bi < bj) return;
-  for (int e = threadIdx.x; e < 64 * 64; e += 256) {
-    const int r = e >> 6, c = e & 63;
-    t[r][c] = C[(size_t)(bj * 64 + r) * n_pad + bi * 64 + c];   // source block (bj, bi)
+      for (int e4 = 0; e4 < 4; ++e4) {
+        const f32x16& t = tot[q / BC][q % BC];
+        *(f32x4*)(out + ((size_t)((q * 4 + e4) * NW + wave) * 64 + lane) * 4) =
+            f32x4{t[4 * e4], t[4 * e4 + 1], t[4 * e4 + 2], t[4 * e4 + 3]};
+      }
+    return;
   }
-  __syncthreads();
-  for (int e = threadIdx.x; e < 64 * 64; e += 256) {
-    const int r = e >> 6, c = e & 63;
-    if (bi == bj && r <= c) continue;
-    C[(size_t)(bi * 64 + r) * n_pad + bj * 64 + c] = t[c][r];
+  const int ec = prod_exp<PREC>(a, k, &s_nrm);
+  const float alpha = PREC == kSplitH ? a.alpha * prod_scale(a, k) : a.alpha;
+  const float sc = PREC == kSplitH ? ldexpf(1.0f, ec) : 1.0f;
+  __syncthreads();   // every wave is past its last ring read
+  LDS_AS char* rb = (wave >> 1) == 0 ? R0 : (wave >> 1) == 1 ? R1 : (wave >> 1) == 2 ? R2 : R3;
+  const double sq = prod_wave<PREC>(a, k, tot, (LDS_AS float*)(rb + (wave & 1) * kStageBytes), ti, tj, wave, lane, alpha, sc);
+  prod_norm(a, k, sq, ti, tj, wave, lane, ec);
+}
+
+// A tile in pieces: eight workgroups of one wave, workgroup 8 q + w the region of
+// wave w in the list's q-th such tile.  All 16 loads of 16 bytes of four pieces are
+// in flight at once (a wave alone on its SIMD may hold 512 registers).
+constexpr int kCombPieces = 4;
+template <int PREC>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_prod_combine(ProdArgs a,
+                                                                                                 const ProdJob* split,
+                                                                                                 const float* pieces) {
+  __shared__ __attribute__((aligned(1024))) char stage[kStageBytes];
+  __shared__ double s_nrm;
+  const int wave = blockIdx.x % NW, lane = threadIdx.x;
+  const ProdJob job = split[blockIdx.x / NW];
+  const int ti = prod_ti(job.tile), tj = prod_tj(job.tile);
+  const int npc = (job.part >> 4) & 15, k = (job.part >> 8) & 255, slot0 = job.part >> 16;
+  double v[BR * BC][16];
+#pragma unroll
+  for (int q = 0; q < BR * BC; ++q)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) v[q][e] = 0.0;
+  const float* src = pieces + (size_t)slot0 * kSplitTileFloats + ((size_t)wave * 64 + lane) * 4;
+  for (int p = 0; p < npc; p += kCombPieces) {
+    f32x4 u[kCombPieces][BR * BC][4];
+#pragma unroll
+    for (int z = 0; z < kCombPieces; ++z)
+#pragma unroll
+      for (int q = 0; q < BR * BC; ++q)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4)
+          u[z][q][e4] = *(const f32x4*)(src + (size_t)min(p + z, npc - 1) * kSplitTileFloats +
+                                        (size_t)(q * 4 + e4) * NW * 64 * 4);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int z = 0; z < kCombPieces; ++z)
+      if (p + z < npc) {
+#pragma unroll
+        for (int q = 0; q < BR * BC; ++q)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) v[q][e] += (double)u[z][q][e >> 2][e & 3];
+      }
   }
+  f32x16 tot[BR][BC];
+#pragma unroll
+  for (int q = 0; q < BR * BC; ++q)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) tot[q / BC][q % BC][e] = (float)v[q][e];
+  const int ec = prod_exp<PREC>(a, k, &s_nrm);
+  const float alpha = PREC == kSplitH ? a.alpha * prod_scale(a, k) : a.alpha;
+  const float sc = PREC == kSplitH ? ldexpf(1.0f, ec) : 1.0f;
+  const double sq = prod_wave<PREC>(a, k, tot, (LDS_AS float*)((LDS_AS char*)stage), ti, tj, wave, lane, alpha, sc);
+  prod_norm(a, k, sq, ti, tj, wave, lane, ec);
 }
 
-hipError_t launch_gemm_nt_sym(const float* A, const float* B, float* C, int n_pad, float alpha, int flush,
-                              hipStream_t s) {
-  return launch_gemm_op(kFP32, A, B, C, n_pad, alpha, flush, 1, s);
-}
-
-hipError_t launch_gemm_op(int prec, const void* A, const void* B, float* C, int n_pad, float alpha, int flush,
-                          int sym, hipStream_t s) {
-  if (n_pad <= 0 || n_pad % TM != 0) return hipErrorInvalidValue;
-  const int tr = n_pad / TM;
-  const int tiles = sym ? tr * (tr + 1) : (n_pad / TM) * (n_pad / TN);
+hipError_t launch_prod_large(int prec, const ProdArgs& a, const ProdJob* jobs, int njobs, const ProdJob* split, int nsplit,
+                             float* pieces, hipStream_t s) {
+  if (a.n_pad <= 0 || a.n_pad % TM != 0 || njobs < 1 || (nsplit > 0 && !pieces)) return hipErrorInvalidValue;
+#define DMPT_PLARGE(P)                                                                                            \
+  case P:                                                                                                         \
+    hipLaunchKernelGGL(k_prod_large<P>, dim3(njobs), dim3(NT), 0, s, a, jobs, pieces);                            \
+    if (nsplit > 0)                                                                                               \
+      hipLaunchKernelGGL(k_prod_combine<P>, dim3(nsplit * NW), dim3(64), 0, s, a, split, pieces);               \
+    break;
   switch (prec) {
-    case kFP32: hipLaunchKernelGGL(k_gemm_nt<kFP32>, dim3(tiles), dim3(NT), 0, s, A, B, C, n_pad, alpha, flush, sym); break;
-    case kSplitH: hipLaunchKernelGGL(k_gemm_nt<kSplitH>, dim3(tiles), dim3(NT), 0, s, A, B, C, n_pad, alpha, flush, sym); break;
-    case kSplit3: hipLaunchKernelGGL(k_gemm_nt<kSplit3>, dim3(tiles), dim3(NT), 0, s, A, B, C, n_pad, alpha, flush, sym); break;
-    case kSplit2: hipLaunchKernelGGL(k_gemm_nt<kSplit2>, dim3(tiles), dim3(NT), 0, s, A, B, C, n_pad, alpha, flush, sym); break;
+    DMPT_PLARGE(kFP32)
+    DMPT_PLARGE(kSplitH)
+    DMPT_PLARGE(kSplit3)
+    DMPT_PLARGE(kSplit2)
     default: return hipErrorInvalidValue;
   }
-  if (sym) {
-    const int nb = n_pad / 64;
-    hipLaunchKernelGGL(k_mirror_lower, dim3(nb, nb), dim3(256), 0, s, C, n_pad);
-  }
+#undef DMPT_PLARGE
   return hipGetLastError();
 }
 
@@ -1528,6 +1618,18 @@ __device__ void set_coeffs(Ctl* c, double emin, double emax) {
   const double w = emax - emin;
   c->alpha = emax / w;   // Eq. DM0: X_1 = alpha I + beta H maps [emin, emax] onto [1, 0]
   c->beta = -1.0 / w;
+}
+
+__global__ void k_set_affine(Ctl* c, double alpha, double beta) {
+  if (threadIdx.x == 0) {
+    c->alpha = alpha;
+    c->beta = beta;
+  }
+}
+
+hipError_t launch_set_affine(Ctl* ctl, double alpha, double beta, hipStream_t s) {
+  hipLaunchKernelGGL(k_set_affine, dim3(1), dim3(64), 0, s, ctl, alpha, beta);
+  return hipGetLastError();
 }
 
 __global__ void k_set_bounds(Ctl* c, double emin, double emax) {
@@ -2101,7 +2203,7 @@ __global__ __launch_bounds__(256) void k_resplit(int prec, MatRef m, int n_pad, 
   char* dst = (char*)m.op + (size_t)z * m.stride_op;
   float sc = 1.0f;
   if (prec == kSplitH) {
-    MatMeta* mm = (MatMeta*)(m.meta + (size_t)z * m.stride_op);
+    MatMeta* mm = (MatMeta*)(m.meta + (size_t)z * (m.stride_meta ? m.stride_meta : m.stride_op));
     const int e = yscale_exp(meta_norm(mm, (n_pad / 64) * (n_pad / 64), &s_nrm), 1.0);
     sc = ldexpf(1.0f, e);
     if (blockIdx.x == 0 && threadIdx.x == 0) mm->scale = e;
@@ -2116,24 +2218,6 @@ __global__ __launch_bounds__(256) void k_resplit(int prec, MatRef m, int n_pad, 
     const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
     store_group8(prec, dst, n_pad, r, c0, v, sc, tiled);
   }
-}
-
-// Tiled FP16 split copy of one n_pad x n_pad FP32 matrix at the scale 2^e.
-__global__ __launch_bounds__(256) void k_split_copy(const float* src, char* dst, int n_pad, float sc) {
-  const size_t ngroups = (size_t)n_pad * n_pad / 8;
-  for (size_t g = (size_t)blockIdx.x * 256 + threadIdx.x; g < ngroups; g += (size_t)gridDim.x * 256) {
-    const size_t r = g / (n_pad / 8);
-    const int c0 = (int)(g % (n_pad / 8)) * 8;
-    const f32x4 a = *(const f32x4*)(src + r * n_pad + c0);
-    const f32x4 b = *(const f32x4*)(src + r * n_pad + c0 + 4);
-    const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-    store_group8_t<kSplitH>(dst, n_pad / Fmt<kSplitH>::K, (int)r, c0, v, sc);
-  }
-}
-
-hipError_t launch_split_copy(const float* src, void* dst, int n_pad, int e, hipStream_t s) {
-  hipLaunchKernelGGL(k_split_copy, dim3(2048), dim3(256), 0, s, src, (char*)dst, n_pad, ldexpf(1.0f, e));
-  return hipGetLastError();
 }
 
 // Tiled operand copy (format F) of the n_pad x n_pad zero padding of an
@@ -2366,7 +2450,7 @@ __device__ __forceinline__ void init_block(int prec, const float (*p)[65], const
     if ((t & 63) == 0) s_red[t >> 6] = sq;
     __syncthreads();
     if (t == 0) {
-      MatMeta* mm = (MatMeta*)(m.meta + (size_t)(z - 1) * m.stride_op);
+      MatMeta* mm = (MatMeta*)(m.meta + (size_t)(z - 1) * (m.stride_meta ? m.stride_meta : m.stride_op));
       mm->nrm[bi * nb + bj] = s_red[0] + s_red[1] + s_red[2] + s_red[3];
       if (bi == 0 && bj == 0) mm->count = nb * nb;
     }

@@ -234,4 +234,100 @@ inline const JobList& cached_wide_list(int n_pad, int nobs, bool with_p, int cus
   return it->second;
 }
 
+// Job list of a general product (k_prod_large): the tiles of nb matrices (all
+// of them, or those of the upper triangle) in the groups of the step lists, the
+// last k tiles of each matrix in s pieces of their K range.  k and s minimise the
+// modelled makespan of one matrix on `cus` workgroups, in tile times: a piece
+// costs 1 / s and a fixed part (its start, the partial sums), the combine launch
+// its own fixed part and the sums it reads.  They do not depend on nb, so that a
+// batch gives the bits of single products; the pieces come after the whole tiles
+// of all matrices.  n = 4096, symmetric (272 tiles, 256 CUs): the last 16 tiles
+// in 8 pieces each.
+constexpr int kMaxPieces = 512;   // slots of partial sums a matrix (128 KB each)
+struct ProdList {
+  std::vector<ProdJob> jobs, split;
+};
+
+inline std::vector<std::vector<std::pair<int, int>>> full_groups(int n_pad) {
+  const int tr = n_pad / kStepTM, tc = n_pad / kStepTN;
+  std::vector<std::vector<std::pair<int, int>>> out;
+  for (int gi = 0; gi < tr; gi += kGroupI)
+    for (int gj = 0; gj < tc; gj += kGroupJ) {
+      std::vector<std::pair<int, int>> g;
+      for (int i = gi; i < std::min(tr, gi + kGroupI); ++i)
+        for (int j = gj; j < std::min(tc, gj + kGroupJ); ++j) g.emplace_back(i, j);
+      out.push_back(std::move(g));
+    }
+  return out;
+}
+
+inline ProdList build_prod_list(int n_pad, bool full, int nb, int cus, bool long_k) {
+  const auto groups = full ? full_groups(n_pad) : tile_groups(n_pad);
+  std::vector<uint32_t> tiles;    // row block << 13 | column block, in XCD order
+  {
+    std::vector<std::vector<uint32_t>> kg;
+    for (const auto& g : groups) {
+      std::vector<uint32_t> t;
+      for (const auto& x : g) t.push_back((uint32_t)x.first << 13 | (uint32_t)x.second);
+      kg.push_back(std::move(t));
+    }
+    append_xcd_ordered(tiles, kg);
+  }
+  const int total = (int)tiles.size();
+  // a tile of twice the K range halves the fixed parts
+  const double over = long_k ? 0.05 : 0.1, comb = long_k ? 0.05 : 0.1;
+  auto makespan = [&](int k, int s) {   // total - k whole tiles, then k s pieces
+    const int whole = total - k, rounds = whole / cus, rest = whole % cus;
+    if (k == 0) return (double)((total + cus - 1) / cus);
+    // pieces fill the CUs that the last whole round leaves idle, then all of them
+    const double p = 1.0 / s + over;
+    int left = k * s;
+    double end = rounds + (rest ? 1.0 : 0.0), t = rounds;
+    if (rest) {
+      const int per = (int)(1.0 / p);                    // pieces a CU takes beside a whole tile
+      left -= (cus - rest) * per;
+      t = rounds + 1.0;
+      if (left > 0) end = t;
+    }
+    if (left > 0) end = std::max(end, t + p * ((left + cus - 1) / cus));
+    return end + comb + 0.0002 * k * s;
+  };
+  int bk = 0, bs = 1;
+  double best = makespan(0, 1);
+  for (int s = 2; s <= 8; ++s)
+    for (int k = 1; k <= std::min(total, kMaxPieces / s); ++k) {
+      const double t = makespan(k, s);
+      if (t < best - 1e-9) { best = t; bk = k; bs = s; }
+    }
+  ProdList L;
+  auto job = [](uint32_t t, int k, int piece, int pieces, int slot) {
+    return ProdJob{t >> 13 | (t & 0x1fff) << 16,
+                   (uint32_t)piece | (uint32_t)pieces << 4 | (uint32_t)k << 8 | (uint32_t)slot << 16};
+  };
+  for (int k = 0; k < nb; ++k)
+    for (int q = 0; q < total - bk; ++q) L.jobs.push_back(job(tiles[q], k, 0, 1, 0));
+  int slot = 0;
+  for (int k = 0; k < nb; ++k)
+    for (int q = total - bk; q < total; ++q, slot += bs) {
+      for (int p = 0; p < bs; ++p) L.jobs.push_back(job(tiles[q], k, p, bs, slot));
+      L.split.push_back(job(tiles[q], k, 0, bs, slot));
+    }
+  return L;
+}
+
+// Entries (jobs, then split tiles) a list may take in the workspace.
+inline size_t prod_list_entries(int n_pad, int nb) {
+  return ((size_t)(n_pad / kStepTM) * (n_pad / kStepTN) + 2 * kMaxPieces) * nb;
+}
+
+inline const ProdList& cached_prod_list(int n_pad, bool full, int nb, int cus, bool long_k) {
+  static std::mutex mu;
+  static std::map<std::tuple<int, bool, int, int, bool>, ProdList> cache;
+  std::lock_guard<std::mutex> lock(mu);
+  const auto key = std::make_tuple(n_pad, full, nb, cus, long_k);
+  auto it = cache.find(key);
+  if (it == cache.end()) it = cache.emplace(key, build_prod_list(n_pad, full, nb, cus, long_k)).first;
+  return it->second;
+}
+
 }  // namespace dmpt

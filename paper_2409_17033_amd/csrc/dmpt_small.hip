@@ -562,65 +562,98 @@ hipError_t launch_step_small(int prec, int ts, const StepArgs& args, int nz, int
 
 // ---------------------------------------------------------------- general product
 
-// C = alpha A B^T over the TS x TS tiles (sym: the upper triangle of a product
-// known to be symmetric, with the mirror tile stored from the same sums).
+// One tile of a general product (ProdArgs) per workgroup.
 namespace {
 template <int PREC, int B, int W>
 __global__ __launch_bounds__((W * 64)) __attribute__((amdgpu_waves_per_eu((B == 1 ? 4 : 2), (B == 1 ? 4 : 2))))
-void k_gemm_small(const char* A, const char* Bm, float* C, int n_pad, float alpha, int flush, int sym) {
+void k_prod_small(ProdArgs a) {
   using G = SGeo<PREC, B, W>;
-  constexpr int TS = G::TS, LS = G::LS, NTH = G::NTH, V4 = TS / 4;
+  constexpr int TS = G::TS, NTH = G::NTH;
   __shared__ __attribute__((aligned(1024))) char part[G::PART];
-  LDS_AS float* T = (LDS_AS float*)part;
+  __shared__ double s_red[8], s_nrm[8];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nt = n_pad / TS;
-  const int t = xcd_order(blockIdx.x, gridDim.x);
+  const int nt = a.n_pad / TS, tiles = a.kind == kProdFull ? nt * nt : nt * (nt + 1) / 2;
+  const int k = blockIdx.x / tiles, t = xcd_order(blockIdx.x - k * tiles, tiles);
   int ti, tj;
-  if (sym) tri_tile(t, nt, &ti, &tj);
-  else full_tile(t, nt, &ti, &tj);
-  const int nst = n_pad / Fmt<PREC>::K;
-  const char* pa = A + panel_off<PREC>(ti * TS, n_pad);
-  const char* pb = Bm + panel_off<PREC>(tj * TS, n_pad);
-  tile_sum<PREC, B, W>(pa, pb, pa, pb, nst, nst, n_pad, flush, alpha, 1.0f, (LDS_AS char*)part, wave, lane,
-                       [] { return true; }, [] {});
+  if (a.kind == kProdFull) full_tile(t, nt, &ti, &tj);
+  else tri_tile(t, nt, &ti, &tj);
+  const int spass = a.n_pad / Fmt<PREC>::K, nst = a.kind == kProdAnti ? 2 * spass : spass;
+  const char* pa = a.a + (size_t)k * a.sa;
+  const char* pb = a.b + (size_t)k * a.sb;
+  const size_t rI = panel_off<PREC>(ti * TS, a.n_pad), rJ = panel_off<PREC>(tj * TS, a.n_pad);
+  float usc = 1.0f;
+  auto ov = [&]() {   // while the first operands are on their way: the norm behind the copy's exponent
+    if constexpr (PREC == kSplitH) {
+      usc = prod_scale(a, k);
+      if (a.mn) {
+        const MatMeta* mi = (const MatMeta*)(a.mn + (size_t)k * a.smn);
+        const int cap = meta_entries(a.n_pad), cnt = mi->count < cap ? mi->count : cap;
+        double v = 0.0;
+        for (int q = tid; q < cnt; q += NTH) v += mi->nrm[q];
+        v = wave_sum(v);
+        if (lane == 0) s_nrm[wave] = v;
+      }
+    }
+    return true;
+  };
+  tile_sum<PREC, B, W>(pa + rI, pb + rJ, pb + rI, pa + rJ, spass, nst, a.n_pad, a.flush, 1.0f, 1.0f, (LDS_AS char*)part,
+                       wave, lane, ov, [] {});
+  int ec = a.ec;
+  if constexpr (PREC == kSplitH) {
+    if (a.mn) {
+      double v = 0.0;
+      for (int w = 0; w < G::NWV; ++w) v += s_nrm[w];
+      ec = yscale_exp(sqrt(v), a.bound);
+    }
+  }
   __syncthreads();
-  const bool diag = sym && ti == tj;
-  for (int e = tid; e < TS * V4; e += NTH) {
-    const int r = e % TS, c = 4 * (e / TS);
-    f32x4 v;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = diag && r > c + k ? T[(c + k) * LS + r] : T[r * LS + c + k];
-    *(f32x4*)(C + m_off(1, ti * TS + r, tj * TS + c, n_pad)) = v;
-    if (sym && !diag) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) v[k] = T[(c + k) * LS + r];
-      *(f32x4*)(C + m_off(1, tj * TS + r, ti * TS + c, n_pad)) = v;
+  double sq = prod_region<PREC, TS, G::LS, NTH, true, 1>(a, k, (LDS_AS float*)part, tid, ti * TS, tj * TS,
+                                                         a.kind != kProdFull, a.alpha * usc,
+                                                         PREC == kSplitH ? ldexpf(1.0f, ec) : 1.0f);
+  if (a.mo && a.kind == kProdFull) {   // the exponent only
+    if (t == 0 && tid == 0) {
+      MatMeta* mo = (MatMeta*)(a.mo + (size_t)k * a.smo);
+      mo->scale = ec;
+      mo->count = 0;
+    }
+  } else if (a.mo) {
+    sq = wave_sum(sq);
+    if (lane == 0) s_red[wave] = sq;
+    __syncthreads();
+    if (tid == 0) {
+      double v = 0.0;
+      for (int w = 0; w < G::NWV; ++w) v += s_red[w];
+      MatMeta* mo = (MatMeta*)(a.mo + (size_t)k * a.smo);
+      mo->nrm[t] = v;
+      if (t == 0) {
+        mo->scale = ec;
+        mo->count = tiles;
+      }
     }
   }
 }
 }  // namespace
 
-hipError_t launch_gemm_small(int prec, int ts, const void* A, const void* B, float* C, int n_pad, float alpha, int flush,
-                             int sym, hipStream_t s) {
-  if (n_pad <= 0 || n_pad % 64 != 0 || (ts != 32 && ts != 64)) return hipErrorInvalidValue;
-  const int nt = n_pad / ts, grid = sym ? nt * (nt + 1) / 2 : nt * nt;
-#define DMPT_GSMALL(P)                                                                                              \
-  if (ts == 32) hipLaunchKernelGGL((k_gemm_small<P, 1, 8>), dim3(grid), dim3(512), 0, s, (const char*)A,       \
-                                   (const char*)B, C, n_pad, alpha, flush, sym);                               \
-  else if (eight_waves(grid)) hipLaunchKernelGGL((k_gemm_small<P, 2, 8>), dim3(grid), dim3(512), 0, s, (const char*)A, \
-                                                 (const char*)B, C, n_pad, alpha, flush, sym);                 \
-  else hipLaunchKernelGGL((k_gemm_small<P, 2, 4>), dim3(grid), dim3(256), 0, s, (const char*)A, (const char*)B, C, \
-                          n_pad, alpha, flush, sym);                                                           \
+hipError_t launch_prod_small(int prec, int ts, const ProdArgs& a, hipStream_t s) {
+  if (a.n_pad <= 0 || a.n_pad % 64 != 0 || (ts != 32 && ts != 64) || a.nb < 1) return hipErrorInvalidValue;
+  const int nt = a.n_pad / ts, grid = a.nb * (a.kind == kProdFull ? nt * nt : nt * (nt + 1) / 2);
+  // The observables' products (kProdFull, kProdAnti) keep four waves whatever the
+  // batch, so that an observable's sums do not depend on how many share a launch.
+  const bool w8 = a.kind == kProdSym && eight_waves(grid);
+#define DMPT_PSMALL(P)                                                                                         \
+  if (ts == 32) hipLaunchKernelGGL((k_prod_small<P, 1, 8>), dim3(grid), dim3(512), 0, s, a);                   \
+  else if (w8) hipLaunchKernelGGL((k_prod_small<P, 2, 8>), dim3(grid), dim3(512), 0, s, a);     \
+  else hipLaunchKernelGGL((k_prod_small<P, 2, 4>), dim3(grid), dim3(256), 0, s, a);                            \
   break;
   switch (prec) {
-    case kFP32: DMPT_GSMALL(kFP32)
-    case kSplit2: DMPT_GSMALL(kSplit2)
-    case kSplit3: DMPT_GSMALL(kSplit3)
-    case kSplitH: DMPT_GSMALL(kSplitH)
+    case kFP32: DMPT_PSMALL(kFP32)
+    case kSplit2: DMPT_PSMALL(kSplit2)
+    case kSplit3: DMPT_PSMALL(kSplit3)
+    case kSplitH: DMPT_PSMALL(kSplitH)
     default: return hipErrorInvalidValue;
   }
-#undef DMPT_GSMALL
+#undef DMPT_PSMALL
   return hipGetLastError();
 }
 
