@@ -156,6 +156,25 @@ int flush_interval(int prec, int n_pad) {
   return std::max(1, (int)std::lround(f));
 }
 
+// Tile edge, 32 or 64, of the small-size kernels for a launch of `matrices` products.
+// 32 x 32 tiles while all of them are resident at once, where the K loop of one tile
+// is what a launch takes, and later than that where 64 x 64 tiles would fill the chip
+// once and a bit.  64 x 64 tiles read half the operands.  Whole solves, ms, 32 / 64
+// (32 x 32 tiles of a launch): FP16 split n = 700 0.84 / 1.03 (506), n = 850 1.13 / 1.13
+// (812), n = 1000 1.32 / 1.45 (1056; 272 of 64 x 64), n = 1100 1.50 / 1.49 (1332), n =
+// 1250 1.92 / 1.69 (1640); finite temperature n = 1000 5.9 / 6.3 (528), n = 1250 9.9 /
+// 8.6 (820), n = 1500 8.8 / 10.3 (1176).  FP32, whose tiles have four times the MFMA
+// time: n = 700 1.03 / 1.48, n = 850 1.64 / 1.64, n = 1100 2.57 / 2.67, n = 1250 3.48 /
+// 3.03; four observables n = 512 1.13 / 1.29 (680), n = 850 2.96 / 2.85 (2030); and with
+// eight waves a 64 x 64 tile (eight_waves) n = 1000 2.07 / 1.99, n = 1050 2.48 / 2.23.
+int square_tile(int prec, int n, int matrices) {
+  const int t = (n + 63) / 64, jobs64 = t * (t + 1) / 2 * matrices, jobs32 = t * (2 * t + 1) * matrices;
+  const bool fp32 = prec == kFP32;
+  if (jobs64 <= 256) return jobs32 <= (fp32 ? 700 : 560) ? 32 : 64;
+  if (fp32 && matrices > 1 && jobs64 <= 320) return 64;
+  return jobs32 <= (fp32 ? 1400 : 1200) ? 32 : 64;
+}
+
 // Tile edge of the small-size kernels (dmpt_small.hip) for a problem with z
 // sweep products a launch and with_p = 1 if the launch forms X^2 too; 0: the
 // large-size kernels.  All times are whole solves in ms, small / large.
@@ -168,16 +187,7 @@ int flush_interval(int prec, int n_pad) {
 //  * Corrected runs of the three-term-X^2 option have wide sweep tiles and
 //    K-split tails in the large-size lists: those take over at n = 2048
 //    already (6.1 / 8.3; z = 4: 15.0 / 14.6).
-//  * 32 x 32 tiles while all of them are resident at once (two workgroups a
-//    CU), where the K loop of one tile is what a launch takes: z = 1, FP16
-//    split: n = 700 1.04 against 1.15 with 64 x 64 tiles, n = 850 1.47 against
-//    1.32.  FP32 tiles have four times the MFMA time, and the finer grain
-//    balances it up to five rounds: n = 700 1.27 against 1.61, z = 4 2.15
-//    against 2.48, n = 1000 2.19 against 2.15.
-int square_tile(int prec, int n, int matrices) {
-  const int t32 = (n + 63) / 64 * 2, jobs32 = t32 * (t32 + 1) / 2 * matrices;
-  return jobs32 <= (prec == kFP32 ? 1280 : 512) ? 32 : 64;
-}
+//  * 32 or 64: see square_tile.
 int small_tile(int prec, bool wide_lists, int n, int z, int with_p) {
   const int nmax = wide_lists ? 1984 : prec == kFP32 ? (z <= 1 ? 4608 : z <= 4 ? 2560 : 2048)
                                                      : (z <= 1 ? 2600 : z <= 4 ? 2048 : 1536);
@@ -190,8 +200,7 @@ int small_tile(int prec, bool wide_lists, int n, int z, int with_p) {
 // 25.2, n = 2600 29.1 / 36.4, n = 3000 40.7 / 40.6, n = 3500 62.9 / 51.5; FP32, where
 // the padding to 256 and the number of tiles move the large side more, n = 2048
 // 55.1 / 49.9, n = 2300 51.6 / 60.3, n = 3000 107 / 128, n = 3500 171 / 162, n = 4096
-// 324 / 270.  32 x 32 tiles, four observables: FP16 split n = 1000 9.4 against 8.6
-// with 64 x 64, FP32 14.4 against 15.9.
+// 324 / 270.
 int product_tile(int prec, int n) {
   return n > (prec == kFP32 ? 3328 : 2944) ? 0 : square_tile(prec, n, 1);
 }

@@ -15,8 +15,11 @@
 // What bounds it, and what it measured (one step of one observable, us; the
 // 256 x 128 tiles before): n = 128 FP32 77 -> 7.8, of which the chain of a few
 // dependent memory round trips (operands and partials, the current matrix, the
-// stores) and the launch; n = 1000 FP32 248 -> 51, FP16 split 86 -> 29; n = 2048
-// FP32 562 -> 276, FP16 split 162 -> 114.  From n = 1000 on the operand loads
+// stores) and the launch; n = 1000 FP32 248 -> 51, FP16 split 86 -> 27; n = 2048
+// FP32 562 -> 276, FP16 split 162 -> 114.  At n = 128 the controller's sums and its
+// decision took 2.3 of them; with the sums inside the vector unit (wave_sum) and the
+// decision beside the main loop the whole solve went from 0.65 to 0.58 ms (four waves
+// a workgroup included).  From n = 1000 on the operand loads
 // bound the split formats (n = 2048: 0.9 GB of operands a launch; the same loop
 // without its MFMAs takes as long) and the FP32 MFMAs the FP32 ones (0.6 of
 // their peak at n = 2048).  Loads in the order of the 128-row chunks of the
@@ -282,6 +285,21 @@ __device__ __forceinline__ int xcd_order(int p, int cnt) {
   return x * per + (x < rest ? x : rest) + (p >> 3);
 }
 
+// This thread's part of the sum of a matrix's norm partials, four loads in flight.
+template <int NTH>
+__device__ __forceinline__ double meta_part(const MatMeta* m, int cap, int tid) {
+  const int cnt = m->count < cap ? m->count : cap;
+  double s = 0.0;
+  for (int q = tid; q < cnt; q += 4 * NTH) {
+    double u[4];
+#pragma unroll
+    for (int z = 0; z < 4; ++z) u[z] = q + z * NTH < cnt ? m->nrm[q + z * NTH] : 0.0;
+#pragma unroll
+    for (int z = 0; z < 4; ++z) s += u[z];
+  }
+  return s;
+}
+
 // ---------------------------------------------------------------- step kernel
 
 // One SP2 / sweep step (see the step kernel of dmpt_kernels.hip): workgroup =
@@ -319,40 +337,55 @@ __device__ __forceinline__ void small_job(const StepArgs& a, const int kind, con
   }
   // while the first operands are on their way: leave after the stop, and the
   // FP64 sums (lane-strided, fixed order) of the controller's partials and of ||Y_n||^2
-  CtlIn ci = {};
   auto ov = [&]() {
-    if (a.decide) {
-      // everything the decision reads is asked for at once
-      ci = ctl_read(a);
-      const int done = a.ctl->done;
-      double tr = 0.0, sq = 0.0, eps = 0.0;
-      for (int q = tid; q < a.nparts; q += NTH) {
-        const Part p = a.part_in[q];
-        tr += p.tr;
-        sq += p.sq;
-        eps += p.eps;
-      }
-      // sweep stop (ytol2): recorded by an earlier launch, or by this one,
-      // whose Z tiles are then dropped either way
-      if (done || (zk && a.ytol2 > 0.0 && ci.ystop != 0)) return false;
-      tr = wave_sum(tr);
-      sq = wave_sum(sq);
-      eps = wave_sum(eps);
-      if (lane == 0) {
-        s_ctl[3 * wave] = tr;
-        s_ctl[3 * wave + 1] = sq;
-        s_ctl[3 * wave + 2] = eps;
-      }
-    }
     if constexpr (PREC == kSplitH) {
       if (zk) {
         const MatMeta* mi = (const MatMeta*)(a.y_in.meta + obs * a.y_in.stride_op);
-        const int cap = meta_entries(a.n_pad), cnt = mi->count < cap ? mi->count : cap;
-        double s = 0.0;
-        for (int q = tid; q < cnt; q += NTH) s += mi->nrm[q];
-        s = wave_sum(s);
+        const double s = wave_sum(meta_part<NTH>(mi, meta_entries(a.n_pad), tid));
         if (lane == 0) s_red[wave] = s;
       }
+    }
+    if (!a.decide) return true;
+    // everything the decision reads is asked for at once
+    const CtlIn ci = ctl_read(a);
+    const int done = a.ctl->done;
+    double tr = 0.0, sq = 0.0, eps = 0.0;
+    for (int q = tid; q < a.nparts; q += 4 * NTH) {
+      Part p[4];
+#pragma unroll
+      for (int z = 0; z < 4; ++z) p[z] = q + z * NTH < a.nparts ? a.part_in[q + z * NTH] : Part{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int z = 0; z < 4; ++z) {
+        tr += p[z].tr;
+        sq += p[z].sq;
+        eps += p[z].eps;
+      }
+    }
+    tr = wave_sum(tr);
+    sq = wave_sum(sq);
+    eps = wave_sum(eps);
+    if (lane == 0) {
+      s_ctl[3 * wave] = tr;
+      s_ctl[3 * wave + 1] = sq;
+      s_ctl[3 * wave + 2] = eps;
+    }
+    // sweep stop (ytol2): recorded by an earlier launch, or by this one, whose Z
+    // tiles are then dropped either way.  One thread's reading counts, so that the
+    // workgroup leaves as a whole.
+    if (tid == 0) s_code[2] = done || (zk && a.ytol2 > 0.0 && ci.ystop != 0) ? 1 : 0;
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the operand loads stay in flight
+    if (s_code[2]) return false;
+    // the first wave decides while the others start their loop
+    if (tid == 0) {
+      tr = sq = eps = 0.0;
+      for (int w = 0; w < G::NWV; ++w) {
+        tr += s_ctl[3 * w];
+        sq += s_ctl[3 * w + 1];
+        eps += s_ctl[3 * w + 2];
+      }
+      int zs = 0;
+      s_code[0] = step_decide(a, ci, tr, sq, eps, blockIdx.x == gridDim.x - 1, &zs);
+      s_code[1] = zs;
     }
     return true;
   };
@@ -380,18 +413,6 @@ __device__ __forceinline__ void small_job(const StepArgs& a, const int kind, con
       s_out = yscale_exp(sqrt(s), kYBound);
     }
     sc_out = ldexpf(1.0f, s_out);
-  }
-  if (a.decide && tid == 0) {
-    double tr = 0.0, sq = 0.0, eps = 0.0;
-    for (int w = 0; w < G::NWV; ++w) {
-      tr += s_ctl[3 * w];
-      sq += s_ctl[3 * w + 1];
-      eps += s_ctl[3 * w + 2];
-    }
-    int zs = 0;
-    const int code = step_decide(a, ci, tr, sq, eps, blockIdx.x == gridDim.x - 1, &zs);
-    s_code[0] = code;
-    s_code[1] = zs;
   }
   __syncthreads();
   int sigma;
@@ -513,7 +534,7 @@ void k_step_small(StepArgs a, int nz) {
   __shared__ __attribute__((aligned(1024))) char part[PART];
   __shared__ double s_ctl[3 * 8];
   __shared__ double s_red[8];
-  __shared__ int s_code[2];
+  __shared__ int s_code[3];
   const int nt = a.n_pad / G::TS, tri = nt * (nt + 1) / 2;
   int b = blockIdx.x;
   if (b < nz * tri) {
@@ -526,14 +547,16 @@ void k_step_small(StepArgs a, int nz) {
   }
 }
 
-// Waves of a 64 x 64 tile's workgroup.  Four (64 KB of sums, so that two
-// workgroups share a CU and one's epilogue runs under the other's loop) except
-// where the tiles fill the chip once and a bit: there the few extra ones
-// would double up on some CUs for the whole launch, while eight waves (one
-// workgroup a CU) leave them to the CUs that finish first.  Step, us, four /
-// eight waves: n = 850 (210 tiles) FP32 42.2 / 44.9; n = 1000 (272) FP32
-// 70.7 / 57.2, FP16 split 35.6 / 34.4; n = 2048 (1056) 275 / 300, 114 / 137.
-inline bool eight_waves(int grid) { return grid > 256 && grid <= 384; }
+// Waves of a tile's workgroup: four, so that several workgroups share a CU (64 KB of
+// sums at most, two to four of them) and one's prologue and epilogue run under the
+// other's loop.  With eight a tile's own loop is shorter, but the sums cost more:
+// whole solve, ms, eight / four waves on 32 x 32 tiles: n = 128 FP32 0.61 / 0.58, n =
+// 700 1.14 / 1.03, n = 1000 FP16 split 1.44 / 1.32.  Eight on 64 x 64 tiles in FP32
+// only where the tiles fill the chip once and a bit: there the few extra ones would
+// double up on some CUs for the whole launch, while one workgroup a CU leaves them to
+// the CUs that finish first: n = 1000 (272 tiles) 1.99 against 2.41 with four, n =
+// 1050 (306) 2.23 / 2.76, n = 1100 (342) 2.74 / 2.67.
+inline bool eight_waves(int grid) { return grid > 256 && grid <= 320; }
 
 }  // namespace
 
@@ -543,12 +566,16 @@ hipError_t launch_step_small(int prec, int ts, const StepArgs& args, int nz, int
   const int nt = args.n_pad / ts, grid = (nz + (with_p ? 1 : 0)) * (nt * (nt + 1) / 2);
   if (grid <= 0) return hipSuccess;
 #define DMPT_SMALL(PP, PZ)                                                                                          \
-  if (ts == 32) hipLaunchKernelGGL((k_step_small<PP, PZ, 1, 8>), dim3(grid), dim3(512), 0, s, args, nz);       \
-  else if (eight_waves(grid)) hipLaunchKernelGGL((k_step_small<PP, PZ, 2, 8>), dim3(grid), dim3(512), 0, s, args, nz); \
-  else hipLaunchKernelGGL((k_step_small<PP, PZ, 2, 4>), dim3(grid), dim3(256), 0, s, args, nz);                \
+  if (ts == 32) hipLaunchKernelGGL((k_step_small<PP, PZ, 1, 4>), dim3(grid), dim3(256), 0, s, args, nz);            \
+  else hipLaunchKernelGGL((k_step_small<PP, PZ, 2, 4>), dim3(grid), dim3(256), 0, s, args, nz);                     \
   break;
   switch (prec) {
-    case kFP32: DMPT_SMALL(kFP32, kFP32)
+    case kFP32:
+      if (ts == 64 && eight_waves(grid)) {
+        hipLaunchKernelGGL((k_step_small<kFP32, kFP32, 2, 8>), dim3(grid), dim3(512), 0, s, args, nz);
+        break;
+      }
+      DMPT_SMALL(kFP32, kFP32)
     case kSplit2: DMPT_SMALL(kSplit2, kSplit2)
     case kSplit3: DMPT_SMALL(kSplit3, kSplit3)
     case kSplit32: DMPT_SMALL(kSplit3, kSplit2)
@@ -588,10 +615,7 @@ void k_prod_small(ProdArgs a) {
       usc = prod_scale(a, k);
       if (a.mn) {
         const MatMeta* mi = (const MatMeta*)(a.mn + (size_t)k * a.smn);
-        const int cap = meta_entries(a.n_pad), cnt = mi->count < cap ? mi->count : cap;
-        double v = 0.0;
-        for (int q = tid; q < cnt; q += NTH) v += mi->nrm[q];
-        v = wave_sum(v);
+        const double v = wave_sum(meta_part<NTH>(mi, meta_entries(a.n_pad), tid));
         if (lane == 0) s_nrm[wave] = v;
       }
     }
@@ -638,12 +662,9 @@ void k_prod_small(ProdArgs a) {
 hipError_t launch_prod_small(int prec, int ts, const ProdArgs& a, hipStream_t s) {
   if (a.n_pad <= 0 || a.n_pad % 64 != 0 || (ts != 32 && ts != 64) || a.nb < 1) return hipErrorInvalidValue;
   const int nt = a.n_pad / ts, grid = a.nb * (a.kind == kProdFull ? nt * nt : nt * (nt + 1) / 2);
-  // The observables' products (kProdFull, kProdAnti) keep four waves whatever the
-  // batch, so that an observable's sums do not depend on how many share a launch.
-  const bool w8 = a.kind == kProdSym && eight_waves(grid);
+  // Always four waves, so that an observable's sums do not depend on how many share a launch.
 #define DMPT_PSMALL(P)                                                                                         \
-  if (ts == 32) hipLaunchKernelGGL((k_prod_small<P, 1, 8>), dim3(grid), dim3(512), 0, s, a);                   \
-  else if (w8) hipLaunchKernelGGL((k_prod_small<P, 2, 8>), dim3(grid), dim3(512), 0, s, a);     \
+  if (ts == 32) hipLaunchKernelGGL((k_prod_small<P, 1, 4>), dim3(grid), dim3(256), 0, s, a);                   \
   else hipLaunchKernelGGL((k_prod_small<P, 2, 4>), dim3(grid), dim3(256), 0, s, a);                            \
   break;
   switch (prec) {

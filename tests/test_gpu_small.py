@@ -54,6 +54,26 @@ def test_partial_recursion_at_tile_edges(gpu, inputs, n, prec):
         assert np.array_equal(c, c.T)
 
 
+@pytest.mark.parametrize("prec,n,tile", [("fp32", 800, 64), ("split_fp16", 800, 32), ("split_fp16", 850, 64),
+                                         ("fp32", 900, 32), ("fp32", 960, 32), ("fp32", 961, 64)])
+def test_tile_choice_around_one_round(gpu, inputs, prec, n, tile):
+    """The sizes where the tile edge and the waves of a workgroup change (two
+    observables; FP32 at n = 800: eight waves)."""
+    import torch
+
+    import paper_2409_17033_amd as dm
+    wl = inputs(n)
+    H, A = torch.from_numpy(wl.H).to(gpu), torch.from_numpy(wl.A).to(gpu)
+    chi, D, _, info = dm.susceptibility(H, A, wl.nocc, precision=prec, bounds="gershgorin", max_iter=STEPS,
+                                        min_iter=STEPS + 1, project=False, spin=1.0, raise_on_error=False)
+    assert info["m"] == STEPS and info["tile"] == tile
+    xs, beta = sp2.sp2_sequence(wl.H.astype(np.float64), info["sigma"], info["emin"], info["emax"])
+    assert cf.rel_frobenius(D.double().cpu().numpy(), xs[-1]) < 2e-6 * STEPS
+    for k in range(2):
+        y = sp2.forward_sweep(xs, info["sigma"], beta, wl.A[k].astype(np.float64))
+        assert cf.rel_frobenius(chi[k].double().cpu().numpy(), y) < 2e-6 * STEPS
+
+
 @pytest.mark.parametrize("n,tile", [(1984, 64), (1985, 256)])
 def test_wide_list_runs_keep_the_large_tiles(gpu, n, tile):
     """Corrected runs of the three-term-X^2 option change to the large-size
