@@ -218,7 +218,7 @@ void make_plan(const Opts& o, int nobs, Plan* p, bool products = false) {
   p->ntile = p->n_pad / kStepTN;                       // 128-column blocks
   p->nb64 = p->n_pad / 64;
   p->nparts_cap = p->ts ? small_tile_count(p->n_pad, 32) : step_tile_count(p->n_pad);
-  p->nparts_step = p->ts ? small_tile_count(p->n_pad, p->ts) : step_tile_count(p->n_pad);
+  p->nparts_step = p->ts ? small_parts(o.prec == kFP32, p->n_pad, p->ts, adjoint ? 0 : nobs) : step_tile_count(p->n_pad);
   // The adjoint keeps X_1 .. X_{max_iter+2} (slot n = X_n; the last launch may
   // write one iterate past the result before the stop is seen), or with a
   // checkpoint interval k: two working slots, one slot per X_n with
@@ -232,7 +232,7 @@ void make_plan(const Opts& o, int nobs, Plan* p, bool products = false) {
   p->mat_op2 = np2 * operand2_bytes(o.prec);
   // norm partials: one per 64 x 64 block (initialisation), or one per step tile
   // (the FP16 split's sweep launches)
-  p->mat_meta = meta_bytes(o.prec == kSplitH ? std::max(p->nb64 * p->nb64, p->nparts_step) : p->nb64 * p->nb64);
+  p->mat_meta = meta_bytes(o.prec == kSplitH ? std::max(p->nb64 * p->nb64, p->nparts_cap) : p->nb64 * p->nb64);
   p->lz_steps = o.lanczos_steps;
   const int ut = p->nparts_cap;                        // step tiles covering the upper triangle
   p->njobs_max = ut * (1 + std::max(nobs, 0)) + kMaxSplit;

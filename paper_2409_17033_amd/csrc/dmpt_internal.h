@@ -202,6 +202,40 @@ hipError_t launch_step_combine(int prec, StepArgs args, const uint32_t* cjobs, i
 hipError_t launch_step_small(int prec, int ts, const StepArgs& args, int nz, int with_p, hipStream_t s);
 hipError_t launch_prod_small(int prec, int ts, const struct ProdArgs& args, hipStream_t s);
 inline int small_tile_count(int n_pad, int ts) { const int t = n_pad / ts; return t * (t + 1) / 2; }
+// Whole 64 x 64 tiles of a launch; the ones after them run as four 32 x 32 quarters.
+// 512 tiles are resident at once (two workgroups a CU), so that a few tiles more than
+// whole rounds of them keep most of the chip waiting: 528 at n = 2048, whose 16 extra
+// ones took 0.6 of a round.  In quarters (a quarter takes about a third of a tile) they
+// spread over the CUs; the more rounds there are, the more a remainder is absorbed by
+// itself, hence the limit on rounds x remainder.  Only FP32 tiles, which the MFMAs bound,
+// gain in launches of both kinds and with larger remainders: quarters read twice the
+// operands.  Whole solves, ms, without / with: X^2 alone (density) FP32 n = 2048 4.73 /
+// 3.65, n = 2240 (118 extra) 4.67 / 4.14, n = 4096 (4 rounds and 32) 22.1 / 20.7, n = 3000
+// (2 rounds and 104, over the limit) 9.7 / 10.2; FP16 split n = 2048 2.04 / 1.79, n = 2112
+// (49) 2.06 / 1.85, n = 2240 2.23 / 2.23; sweep alone (adjoint solve) FP32 n = 2048 12.5 /
+// 9.5; both kinds FP32 n = 2048 10.0 / 8.4, n = 2112 9.5 / 8.7, two observables n = 1440 (40)
+// 6.8 / 6.3, FP16 split n = 2112 4.0 / 4.25.
+struct SmallSplit { int zw, pw; };
+inline SmallSplit small_split(bool fp32, int n_pad, int ts, int nz, int with_p) {
+  constexpr int S = 512;
+  const int tri = small_tile_count(n_pad, ts), Z = nz * tri, P = with_p ? tri : 0;
+  const int T = Z > 0 ? Z : P, k = T / S, rest = T - k * S;
+  SmallSplit r = {Z, P};
+  if (ts != 64 || k < 1 || rest < 1 || 2 * rest > tri) return r;
+  if (Z == 0 || P == 0) {
+    if (rest * k <= (fp32 ? 128 : 64)) (Z > 0 ? r.zw : r.pw) -= rest;
+  } else if (fp32 && rest * k <= 64) {
+    r.zw -= rest;
+    const int prest = (P + rest * 8 / 3) % S;   // a Z quarter: two thirds of a P tile
+    if (prest <= 192 && 2 * prest <= tri) r.pw -= prest;
+  }
+  return r;
+}
+// Entries of the P partials such a launch writes.
+inline int small_parts(bool fp32, int n_pad, int ts, int nz) {
+  const int tri = small_tile_count(n_pad, ts), pw = small_split(fp32, n_pad, ts, nz, 1).pw;
+  return pw + 4 * (tri - pw);
+}
 // Upper bound of the norm partials a producer writes for one matrix.
 __host__ __device__ inline int meta_entries(int n_pad) { return (n_pad / 32) * (n_pad / 32); }
 // Step tiles are 256 rows x 128 columns; tile (I, J) with J >= 2I covers the

@@ -306,18 +306,17 @@ __device__ __forceinline__ double meta_part(const MatMeta* m, int cap, int tid) 
 // one tile of Z = Y_n X_n + X_n Y_n (nz observables, first: twice the work) or
 // of P = X_n X_n (with_p).  The controller's reduction of the previous
 // launch's partials overlaps the main loop; the decision is needed only by
-// the epilogue, which every workgroup reaches or leaves together.
+// the epilogue, which every workgroup reaches or leaves together.  The tile's
+// partials go to entry `slot` of its matrix's `slots` (next: the one after it is 0).
 template <int PREC, int B, int W, bool MIX>
-__device__ __forceinline__ void small_job(const StepArgs& a, const int kind, const int obs, const int t, LDS_AS char* part,
+__device__ __forceinline__ void small_job(const StepArgs& a, const int kind, const int obs, const int ti, const int tj,
+                                          const int slot, const bool next, const int slots, LDS_AS char* part,
                                           double* s_ctl, double* s_red, int* s_code) {
   using G = SGeo<PREC, B, W>;
   LDS_AS float* T = (LDS_AS float*)part;
   constexpr int TS = G::TS, LS = G::LS, NTH = G::NTH, V4 = TS / 4;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nt = a.n_pad / TS;
-  int ti, tj;
-  tri_tile(t, nt, &ti, &tj);
   const int spass = a.n_pad / Fmt<PREC>::K;
   const bool zk = kind == kJobZ;
   const int nst = zk ? 2 * spass : spass;
@@ -513,37 +512,68 @@ __device__ __forceinline__ void small_job(const StepArgs& a, const int kind, con
         p.eps += s_ctl[3 * w + 2];
       }
       if (!zk) {
-        a.part_out[t] = p;
+        a.part_out[slot] = p;
+        if (next) a.part_out[slot + 1] = Part{0.0, 0.0, 0.0, 0.0};
       } else {
         MatMeta* mo = (MatMeta*)(a.y_out.meta + obs * a.y_out.stride_op);
-        mo->nrm[t] = p.sq;
-        if (t == 0) {
+        mo->nrm[slot] = p.sq;
+        if (next) mo->nrm[slot + 1] = 0.0;
+        if (slot == 0) {
           mo->scale = s_out;
-          mo->count = nt * (nt + 1) / 2;
+          mo->count = slots;
         }
       }
     }
   }
 }
 
+// Tiles of one kind (Z of nz observables, or P): job b of the `whole` whole tiles, or
+// with B = 1 quarter b of the tiles after them.
+template <int PREC, int B, int W, bool MIX>
+__device__ __forceinline__ void small_jobs(const StepArgs& a, const int kind, int b, const int whole, const bool quarter,
+                                           LDS_AS char* part, double* s_ctl, double* s_red, int* s_code) {
+  const int nt = a.n_pad / (quarter ? 64 : 32 * B), tri = nt * (nt + 1) / 2;
+  const int f = quarter ? whole + (b >> 2) : b, obs = f / tri;
+  const int left = whole - obs * tri, cw = left < 0 ? 0 : left < tri ? left : tri;   // the observable's whole tiles
+  int t = f - obs * tri, ti, tj, slot = t;
+  bool next = false;
+  if (!quarter) slot = t = xcd_order(t, cw);
+  tri_tile(t, nt, &ti, &tj);
+  if (quarter) {
+    const int q = b & 3;
+    slot = cw + 4 * (t - cw) + q;
+    if (ti == tj) {
+      if (q == 2) return;   // below the diagonal: the mirror of quarter 1, which clears its entry
+      next = q == 1;
+    }
+    ti = 2 * ti + (q >> 1);
+    tj = 2 * tj + (q & 1);
+  }
+  small_job<PREC, B, W, MIX>(a, kind, obs, ti, tj, slot, next, cw + 4 * (tri - cw), part, s_ctl, s_red, s_code);
+}
+
+// Workgroups: the first zw of the nz observables' Z tiles, the others in quarters, the
+// first pw of the P tiles, the others in quarters (B = 2; small_split).
 template <int PP, int PZ, int B, int W>
 __global__ __launch_bounds__((W * 64)) __attribute__((amdgpu_waves_per_eu((B == 1 ? 4 : 2), (B == 1 ? 4 : 2))))
-void k_step_small(StepArgs a, int nz) {
+void k_step_small(StepArgs a, int nz, int zw, int pw) {
   using G = SGeo<PP, B, W>;
   constexpr int PART = G::PART > SGeo<PZ, B, W>::PART ? G::PART : SGeo<PZ, B, W>::PART;
-  __shared__ __attribute__((aligned(1024))) char part[PART];
+  __shared__ __attribute__((aligned(1024))) char part_[PART];
   __shared__ double s_ctl[3 * 8];
   __shared__ double s_red[8];
   __shared__ int s_code[3];
-  const int nt = a.n_pad / G::TS, tri = nt * (nt + 1) / 2;
-  int b = blockIdx.x;
-  if (b < nz * tri) {
-    const int obs = b / tri;
-    b = xcd_order(b - obs * tri, tri);
-    small_job<PZ, B, W, PP != PZ>(a, kJobZ, obs, b, (LDS_AS char*)part, s_ctl, s_red, s_code);
-  } else {
-    b = xcd_order(b - nz * tri, tri);
-    small_job<PP, B, W, PP != PZ>(a, kJobP, 0, b, (LDS_AS char*)part, s_ctl, s_red, s_code);
+  LDS_AS char* part = (LDS_AS char*)part_;
+  const int nt = a.n_pad / G::TS, zt = nz * (nt * (nt + 1) / 2);
+  const int zq = 4 * (zt - zw);
+  const int b = blockIdx.x;
+  constexpr bool MIX = PP != PZ;
+  if (b < zw) small_jobs<PZ, B, W, MIX>(a, kJobZ, b, zw, false, part, s_ctl, s_red, s_code);
+  else if (b >= zw + zq && b < zw + zq + pw)
+    small_jobs<PP, B, W, MIX>(a, kJobP, b - zw - zq, pw, false, part, s_ctl, s_red, s_code);
+  else if constexpr (B == 2 && W == 4) {
+    if (b < zw + zq) small_jobs<PZ, 1, W, MIX>(a, kJobZ, b - zw, zw, true, part, s_ctl, s_red, s_code);
+    else small_jobs<PP, 1, W, MIX>(a, kJobP, b - zw - zq - pw, pw, true, part, s_ctl, s_red, s_code);
   }
 }
 
@@ -563,16 +593,18 @@ inline bool eight_waves(int grid) { return grid > 256 && grid <= 320; }
 hipError_t launch_step_small(int prec, int ts, const StepArgs& args, int nz, int with_p, hipStream_t s) {
   if (args.n_pad <= 0 || args.n_pad % 64 != 0 || (ts != 32 && ts != 64) || (args.decide && !with_p))
     return hipErrorInvalidValue;
-  const int nt = args.n_pad / ts, grid = (nz + (with_p ? 1 : 0)) * (nt * (nt + 1) / 2);
+  const SmallSplit sp = small_split(prec == kFP32, args.n_pad, ts, nz, with_p);
+  const int tri = small_tile_count(args.n_pad, ts);
+  const int grid = sp.zw + 4 * (nz * tri - sp.zw) + (with_p ? sp.pw + 4 * (tri - sp.pw) : 0);
   if (grid <= 0) return hipSuccess;
 #define DMPT_SMALL(PP, PZ)                                                                                          \
-  if (ts == 32) hipLaunchKernelGGL((k_step_small<PP, PZ, 1, 4>), dim3(grid), dim3(256), 0, s, args, nz);            \
-  else hipLaunchKernelGGL((k_step_small<PP, PZ, 2, 4>), dim3(grid), dim3(256), 0, s, args, nz);                     \
+  if (ts == 32) hipLaunchKernelGGL((k_step_small<PP, PZ, 1, 4>), dim3(grid), dim3(256), 0, s, args, nz, sp.zw, sp.pw);            \
+  else hipLaunchKernelGGL((k_step_small<PP, PZ, 2, 4>), dim3(grid), dim3(256), 0, s, args, nz, sp.zw, sp.pw);                     \
   break;
   switch (prec) {
     case kFP32:
       if (ts == 64 && eight_waves(grid)) {
-        hipLaunchKernelGGL((k_step_small<kFP32, kFP32, 2, 8>), dim3(grid), dim3(512), 0, s, args, nz);
+        hipLaunchKernelGGL((k_step_small<kFP32, kFP32, 2, 8>), dim3(grid), dim3(512), 0, s, args, nz, sp.zw, sp.pw);
         break;
       }
       DMPT_SMALL(kFP32, kFP32)

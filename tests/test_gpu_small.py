@@ -74,6 +74,44 @@ def test_tile_choice_around_one_round(gpu, inputs, prec, n, tile):
         assert cf.rel_frobenius(chi[k].double().cpu().numpy(), y) < 2e-6 * STEPS
 
 
+@pytest.mark.parametrize("prec,n,nobs", [("fp32", 1985, 1), ("fp32", 2048, 1), ("fp32", 2112, 1), ("fp32", 2240, 1),
+                                         ("split_fp16", 2048, 1), ("split_fp16", 2112, 1), ("split3_bf16", 2048, 1),
+                                         ("fp32", 1440, 2)])
+def test_tiles_in_quarters(gpu, inputs, prec, n, nobs):
+    """Sizes whose last tiles run as quarters in the launches of one kind (the
+    adjoint solve, which sweeps only after a converged recursion) or of both (the
+    partial forward recursion), against the FP64 recursion on the device."""
+    import torch
+
+    import paper_2409_17033_amd as dm
+    wl = inputs(n)
+    H, A = torch.from_numpy(wl.H).to(gpu), torch.from_numpy(wl.A[:nobs]).to(gpu)
+    eye = torch.eye(n, dtype=torch.float64, device=gpu)
+
+    def step(y, x, s):
+        z = torch.stack([yk @ x for yk in y])
+        z = z + z.transpose(1, 2)
+        return z if s > 0 else 2 * y - z
+
+    for kw in ({"max_iter": STEPS, "min_iter": STEPS + 1, "raise_on_error": False}, {"sweep": "adjoint"}):
+        chi, D, _, info = dm.susceptibility(H, A, wl.nocc, precision=prec, bounds="gershgorin", project=False, spin=1.0,
+                                            **kw)
+        assert info["tile"] == 64
+        m = info["m"]
+        beta = 1.0 / (info["emax"] - info["emin"])
+        xs = [beta * (info["emax"] * eye - H.double())]
+        for s in info["sigma"][:m]:
+            xs.append(xs[-1] @ xs[-1] if s > 0 else 2 * xs[-1] - xs[-1] @ xs[-1])
+        y = -beta * A.double()
+        order = range(m) if "max_iter" in kw else range(m - 1, -1, -1)
+        for q in order:
+            y = step(y, xs[q], info["sigma"][q])
+        assert float((D.double() - xs[m]).norm() / xs[m].norm()) < 2e-6 * m
+        for k in range(nobs):
+            assert float((chi[k].double() - y[k]).norm() / y[k].norm()) < 2e-6 * m
+            assert torch.equal(chi[k], chi[k].T)
+
+
 @pytest.mark.parametrize("n,tile", [(1984, 64), (1985, 256)])
 def test_wide_list_runs_keep_the_large_tiles(gpu, n, tile):
     """Corrected runs of the three-term-X^2 option change to the large-size
