@@ -285,6 +285,39 @@ __device__ __forceinline__ int xcd_order(int p, int cnt) {
   return x * per + (x < rest ? x : rest) + (p >> 3);
 }
 
+// Tiles of the upper triangle in the order of a step launch: the first diagonal tiles
+// (a multiple of 8 up to half of them), those above the diagonal, the other
+// diagonal tiles.  Z's diagonal tiles take half as long as its others: spread over the
+// XCDs and over both ends of the launch they even out the CUs that take one tile more:
+// n = 1024, FP32, 528 tiles of 32 x 32 on 256 CUs: the self-consistent loop, whose
+// launches are sweeps, 21.8 -> 16.8 ms (with the diagonal tiles in one run, which goes to
+// one XCD, no gain).
+// Launches over several observables keep the bands' own order and whole diagonal
+// tiles: n = 1500, four of them, FP16 split 4.3 ms, spread 4.6; n = 1000 2.1, and 2.3 with
+// the shorter diagonal tiles in the bands' order.
+struct StepOrder {
+  int nt, first, off;
+  bool spread;
+  __device__ __forceinline__ StepOrder(int nt_, bool spread_)
+      : nt(nt_), first((nt_ / 2) & ~7), off(nt_ * (nt_ - 1) / 2), spread(spread_) {}
+  // workgroup b of the first cw tiles: its tile
+  __device__ __forceinline__ int at(int b, int cw) const {
+    if (!spread) return xcd_order(b, cw);
+    const int w = cw - first < 0 ? 0 : cw - first < off ? cw - first : off;   // of those above the diagonal
+    return b >= first && b < first + w ? first + xcd_order(b - first, w) : b;
+  }
+  __device__ __forceinline__ void tile(int t, int* ti, int* tj) const {
+    if (!spread) {
+      tri_tile(t, nt, ti, tj);
+    } else if (t >= first && t < first + off) {
+      tri_tile(t - first, nt - 1, ti, tj);
+      ++*tj;
+    } else {
+      *ti = *tj = t < first ? t : t - off;
+    }
+  }
+};
+
 // This thread's part of the sum of a matrix's norm partials, four loads in flight.
 template <int NTH>
 __device__ __forceinline__ double meta_part(const MatMeta* m, int cap, int tid) {
@@ -310,7 +343,8 @@ __device__ __forceinline__ double meta_part(const MatMeta* m, int cap, int tid) 
 // partials go to entry `slot` of its matrix's `slots` (next: the one after it is 0).
 template <int PREC, int B, int W, bool MIX>
 __device__ __forceinline__ void small_job(const StepArgs& a, const int kind, const int obs, const int ti, const int tj,
-                                          const int slot, const bool next, const int slots, LDS_AS char* part,
+                                          const int slot, const bool next, const int slots, const bool halve,
+                                          LDS_AS char* part,
                                           double* s_ctl, double* s_red, int* s_code) {
   using G = SGeo<PREC, B, W>;
   LDS_AS float* T = (LDS_AS float*)part;
@@ -319,7 +353,9 @@ __device__ __forceinline__ void small_job(const StepArgs& a, const int kind, con
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int spass = a.n_pad / Fmt<PREC>::K;
   const bool zk = kind == kJobZ;
-  const int nst = zk ? 2 * spass : spass;
+  const bool diag = ti == tj;
+  const bool fold = zk && diag && halve;   // Z's diagonal tile as Y X and its transpose
+  const int nst = zk && !fold ? 2 * spass : spass;
 
   const char* xop = (const char*)(MIX && zk ? a.x_in.op2 : a.x_in.op);
   const char* yop = (const char*)a.y_in.op + obs * a.y_in.stride_op;
@@ -432,7 +468,6 @@ __device__ __forceinline__ void small_job(const StepArgs& a, const int kind, con
   }
   char* hop = !zk && a.hist ? a.hist + (size_t)(a.step + 1) * a.hist_stride : nullptr;
   const bool wsplit = a.write_split && PREC != kFP32;
-  const bool diag = ti == tj;
   double tr = 0.0, sq = 0.0, ep = 0.0;
 #pragma unroll
   for (int q = 0; q < G::VX; ++q) {
@@ -443,7 +478,8 @@ __device__ __forceinline__ void small_job(const StepArgs& a, const int kind, con
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       if (diag && r > c + k) continue;   // a diagonal tile keeps its upper triangle and mirrors it
-      const float p = T[r * LS + c + k];
+      float p = T[r * LS + c + k];
+      if (fold) p += T[(c + k) * LS + r];   // below the diagonal nothing is overwritten
       const float v = sigma > 0 ? p : 2.0f * x[k] - p;
       T[r * LS + c + k] = v;
       const double w = diag && r == c + k ? 1.0 : 2.0;
@@ -530,15 +566,16 @@ __device__ __forceinline__ void small_job(const StepArgs& a, const int kind, con
 // Tiles of one kind (Z of nz observables, or P): job b of the `whole` whole tiles, or
 // with B = 1 quarter b of the tiles after them.
 template <int PREC, int B, int W, bool MIX>
-__device__ __forceinline__ void small_jobs(const StepArgs& a, const int kind, int b, const int whole, const bool quarter,
+__device__ __forceinline__ void small_jobs(const StepArgs& a, const int kind, int b, const int whole, const bool quarter, const bool spread,
                                            LDS_AS char* part, double* s_ctl, double* s_red, int* s_code) {
   const int nt = a.n_pad / (quarter ? 64 : 32 * B), tri = nt * (nt + 1) / 2;
-  const int f = quarter ? whole + (b >> 2) : b, obs = f / tri;
+  const StepOrder order(nt, spread);
+  const int f = quarter ? whole + (b >> 2) : b, obs = f < tri ? 0 : f / tri;
   const int left = whole - obs * tri, cw = left < 0 ? 0 : left < tri ? left : tri;   // the observable's whole tiles
   int t = f - obs * tri, ti, tj, slot = t;
   bool next = false;
-  if (!quarter) slot = t = xcd_order(t, cw);
-  tri_tile(t, nt, &ti, &tj);
+  if (!quarter) slot = t = order.at(t, cw);
+  order.tile(t, &ti, &tj);
   if (quarter) {
     const int q = b & 3;
     slot = cw + 4 * (t - cw) + q;
@@ -549,7 +586,7 @@ __device__ __forceinline__ void small_jobs(const StepArgs& a, const int kind, in
     ti = 2 * ti + (q >> 1);
     tj = 2 * tj + (q & 1);
   }
-  small_job<PREC, B, W, MIX>(a, kind, obs, ti, tj, slot, next, cw + 4 * (tri - cw), part, s_ctl, s_red, s_code);
+  small_job<PREC, B, W, MIX>(a, kind, obs, ti, tj, slot, next, cw + 4 * (tri - cw), spread, part, s_ctl, s_red, s_code);
 }
 
 // Workgroups: the first zw of the nz observables' Z tiles, the others in quarters, the
@@ -568,12 +605,12 @@ void k_step_small(StepArgs a, int nz, int zw, int pw) {
   const int zq = 4 * (zt - zw);
   const int b = blockIdx.x;
   constexpr bool MIX = PP != PZ;
-  if (b < zw) small_jobs<PZ, B, W, MIX>(a, kJobZ, b, zw, false, part, s_ctl, s_red, s_code);
+  if (b < zw) small_jobs<PZ, B, W, MIX>(a, kJobZ, b, zw, false, nz <= 1, part, s_ctl, s_red, s_code);
   else if (b >= zw + zq && b < zw + zq + pw)
-    small_jobs<PP, B, W, MIX>(a, kJobP, b - zw - zq, pw, false, part, s_ctl, s_red, s_code);
+    small_jobs<PP, B, W, MIX>(a, kJobP, b - zw - zq, pw, false, nz <= 1, part, s_ctl, s_red, s_code);
   else if constexpr (B == 2 && W == 4) {
-    if (b < zw + zq) small_jobs<PZ, 1, W, MIX>(a, kJobZ, b - zw, zw, true, part, s_ctl, s_red, s_code);
-    else small_jobs<PP, 1, W, MIX>(a, kJobP, b - zw - zq - pw, pw, true, part, s_ctl, s_red, s_code);
+    if (b < zw + zq) small_jobs<PZ, 1, W, MIX>(a, kJobZ, b - zw, zw, true, nz <= 1, part, s_ctl, s_red, s_code);
+    else small_jobs<PP, 1, W, MIX>(a, kJobP, b - zw - zq - pw, pw, true, nz <= 1, part, s_ctl, s_red, s_code);
   }
 }
 

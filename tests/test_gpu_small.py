@@ -112,6 +112,27 @@ def test_tiles_in_quarters(gpu, inputs, prec, n, nobs):
             assert torch.equal(chi[k], chi[k].T)
 
 
+@pytest.mark.parametrize("prec", ["fp32", "split_fp16", "split3x_bf16"])
+@pytest.mark.parametrize("n", [31, 64, 100, 500, 512, 700, 1000, 1024])
+def test_diagonal_tiles_of_one_observable(gpu, inputs, n, prec):
+    """One observable: Z's diagonal tiles from one product and its transpose, in
+    the order that spreads them (fewer than 16 tile rows: all of them last)."""
+    import torch
+
+    import paper_2409_17033_amd as dm
+    wl = inputs(n)
+    H, A = torch.from_numpy(wl.H).to(gpu), torch.from_numpy(wl.A[0]).to(gpu)
+    chi, D, _, info = dm.susceptibility(H, A, wl.nocc, precision=prec, bounds="gershgorin", max_iter=STEPS,
+                                        min_iter=STEPS + 1, project=False, spin=1.0, raise_on_error=False)
+    assert info["m"] == STEPS and info["tile"] in (32, 64)
+    xs, beta = sp2.sp2_sequence(wl.H.astype(np.float64), info["sigma"], info["emin"], info["emax"])
+    tol = 6e-5 * STEPS if prec == "split3x_bf16" else 2e-6 * STEPS
+    c = chi.double().cpu().numpy()
+    y = sp2.forward_sweep(xs, info["sigma"], beta, wl.A[0].astype(np.float64))
+    assert cf.rel_frobenius(D.double().cpu().numpy(), xs[-1]) < tol
+    assert cf.rel_frobenius(c, y) < tol and np.array_equal(c, c.T)
+
+
 @pytest.mark.parametrize("n,tile", [(1984, 64), (1985, 256)])
 def test_wide_list_runs_keep_the_large_tiles(gpu, n, tile):
     """Corrected runs of the three-term-X^2 option change to the large-size
