@@ -271,7 +271,7 @@ inline int fused_groups(int n, int B) {
   return (B + per - 1) / per;
 }
 
-template <int FB, bool BWD>
+template <int FB, bool BWD, bool TAIL>
 __global__ __launch_bounds__(512) void k_mixer_fused(const uint16_t* p16, int w, int h, const float* u, const float* en,
                                                      int n, const float* x, const float* t, int B, int per, float* y,
                                                      double* loss_part, float* gpart, double scale) {
@@ -279,13 +279,14 @@ __global__ __launch_bounds__(512) void k_mixer_fused(const uint16_t* p16, int w,
   constexpr int XS = kFusedSites + KM + 32;
   __shared__ uint16_t wx[KM * kFusedHidden];       // W1's x columns, [f][unit]
   __shared__ uint16_t we[KM * kFusedHidden];       // its E columns
-  __shared__ float xs[XS], es[XS], us[kFusedSites];
+  __shared__ float xs[XS], es[XS], us[kFusedSites], zeros[TAIL ? 32 * FB + 1 : 1];
   __shared__ float ysum[8][kFusedSites];
   __shared__ __attribute__((aligned(16))) float dys[kFusedSites];
   const int m = 2 * w + 1, k = 2 * m + 1, km = m + 1;
   const int tid = threadIdx.x, nth = blockDim.x, lane = tid & 63, wave = tid >> 6;
   const int hf = lane >> 5, l32 = lane & 31, unit = wave * 32 + l32, hp = (nth >> 6) * 32;
-  const int i0 = blockIdx.x * kFusedSites;
+  // the last block ends with the last site and passes over rows of the block before it
+  const int own = blockIdx.x * kFusedSites, i0 = min(own, max(n - kFusedSites, 0));
   const uint16_t* b1 = p16 + (size_t)h * k;
   const uint16_t* w2 = b1 + h;
   const int b0 = blockIdx.y * per, be = b0 + per < B ? b0 + per : B;
@@ -299,6 +300,8 @@ __global__ __launch_bounds__(512) void k_mixer_fused(const uint16_t* p16, int w,
     const int j = i0 + q - w;
     es[q] = j >= 0 && j < n ? en[j] : 0.0f;
   }
+  if (TAIL)
+    for (int q = tid; q < 32 * FB + 1; q += nth) zeros[q] = 0.0f;
   for (int q = tid; q < kFusedSites; q += nth) us[q] = i0 + q < n ? u[i0 + q] : 0.0f;
   const float w2c = unit < h ? ld(w2, unit) : 0.0f, b1c = unit < h ? ld(b1, unit) : 0.0f;
   const float wuc = unit < h ? ld(p16, (size_t)unit * k + 2 * m) : 0.0f, b2 = ld(w2 + h, 0);
@@ -311,12 +314,16 @@ __global__ __launch_bounds__(512) void k_mixer_fused(const uint16_t* p16, int w,
     for (int e = 0; e < 16; ++e) site[bi][e] = b1c + us[32 * bi + 8 * (e >> 2) + 4 * hf + (e & 3)] * wuc;
   auto forward = [&](const float* v, const uint16_t* wt, f16v (&acc)[2]) {
 #pragma unroll 4
-    for (int s = 0; s < km / 2; ++s) {
+    for (int s = 0; s < km / 2 - 1; ++s) {
       const int f = 2 * s + hf;
       const float bv = ld(wt, f * hp + unit);
       acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[l32 + f], bv, acc[0], 0, 0, 0);
       acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[32 + l32 + f], bv, acc[1], 0, 0, 0);
     }
+    // columns m - 1 and m: the padding one's input lies outside the window (zero times Inf or NaN is NaN)
+    const float bv = ld(wt, (m - 1 + hf) * hp + unit);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(hf ? 0.0f : v[l32 + m - 1], bv, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(hf ? 0.0f : v[32 + l32 + m - 1], bv, acc[1], 0, 0, 0);
   };
   forward(es, we, site);
   constexpr int GB = FB > 0 ? FB : 1;
@@ -329,17 +336,25 @@ __global__ __launch_bounds__(512) void k_mixer_fused(const uint16_t* p16, int w,
   sdz[1] = f16v{0};
   double loss = 0.0;
   float gb2 = 0.0f;
-  // g[fb] += (dZ rows of this wave's units)^T (window columns of v); rem: column 32 FB
+  // g[fb] += (dZ rows of this wave's units)^T (window columns of v); rem: column 32 FB.
+  // TAIL (fewer sites than a block): rows past the last site read zeros, so that an
+  // Inf or NaN near the end does not meet their zero gradients.  Rows that a last
+  // block shares with the one before it need no such care: what a zero gradient
+  // meets there, the site's own row meets too.
+  const int left = n - i0;
   auto backward = [&](const f16v (&dz)[2], const float* v, float& rem) {
+    int lf = left;
+    if (TAIL) asm volatile("" : "+s"(lf));   // the 32 row addresses are formed here, not kept in registers
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int row = 32 * bi + 8 * (e >> 2) + 4 * hf + (e & 3);
+        const float* vr = !TAIL || row < lf ? v + row : zeros;
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb)
-          g[fb] = __builtin_amdgcn_mfma_f32_32x32x2f32(dz[bi][e], v[row + 32 * fb + l32], g[fb], 0, 0, 0);
-        rem += dz[bi][e] * v[row + 32 * FB];
+          g[fb] = __builtin_amdgcn_mfma_f32_32x32x2f32(dz[bi][e], vr[32 * fb + l32], g[fb], 0, 0, 0);
+        rem += dz[bi][e] * vr[32 * FB];
       }
   };
   for (int b = b0; b < be; ++b) {
@@ -355,6 +370,15 @@ __global__ __launch_bounds__(512) void k_mixer_fused(const uint16_t* p16, int w,
     for (int q = 0; q < 32; ++q) {
       a[q >> 4][q & 15] = tanhf(a[q >> 4][q & 15]);
       v[q] = a[q >> 4][q & 15] * w2c;
+    }
+    if (hp != h) {   // padding units add nothing, whatever their zero weights met
+#pragma unroll
+      for (int q = 0; q < 32; ++q) v[q] = unit < h ? v[q] : 0.0f;
+    }
+    if (TAIL) {
+#pragma unroll
+      for (int q = 0; q < 32; ++q)
+        if (32 * (q >> 4) + 8 * ((q & 15) >> 2) + 4 * hf + (q & 3) >= left) a[q >> 4][q & 15] = 0.0f;
     }
     // sums over the 32 units: halve the values a lane holds with each exchange;
     // lane l32 ends with value l32.  The steps have constant indices: in a loop over
@@ -380,7 +404,7 @@ __global__ __launch_bounds__(512) void k_mixer_fused(const uint16_t* p16, int w,
       float yv = 0.0f;
       for (int q = 0; q < (nth >> 6); ++q) yv += ysum[q][tid];
       yv += b2;
-      const bool in = i0 + tid < n;
+      const bool in = i0 + tid >= own && i0 + tid < n;
       const size_t row = (size_t)b * n + i0 + tid;
       if (!BWD) {
         if (in) y[row] = yv;
@@ -485,9 +509,11 @@ hipError_t launch_fused(const uint16_t* p16, int w, int h, const float* u, const
   const double scale = 2.0 / ((double)B * n);
 #define DMPT_FUSED(FB)                                                                                              \
   case FB:                                                                                                          \
-    if (t) hipLaunchKernelGGL((k_mixer_fused<FB, true>), grid, block, 0, s, p16, w, h, u, en, n, x, t, B, per, y,      \
-                              loss_part, gpart, scale);                                                             \
-    else hipLaunchKernelGGL((k_mixer_fused<FB, false>), grid, block, 0, s, p16, w, h, u, en, n, x, t, B, per, y,       \
+    if (!t) hipLaunchKernelGGL((k_mixer_fused<FB, false, false>), grid, block, 0, s, p16, w, h, u, en, n, x, t, B, per, y, \
+                               loss_part, gpart, scale);                                                            \
+    else if (n >= kFusedSites) hipLaunchKernelGGL((k_mixer_fused<FB, true, false>), grid, block, 0, s, p16, w, h, u, en, n, \
+                                                      x, t, B, per, y, loss_part, gpart, scale);                    \
+    else hipLaunchKernelGGL((k_mixer_fused<FB, true, true>), grid, block, 0, s, p16, w, h, u, en, n, x, t, B, per, y,  \
                             loss_part, gpart, scale);                                                               \
     break;
   switch (fused_blocks(w)) {
