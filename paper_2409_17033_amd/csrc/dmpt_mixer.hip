@@ -542,9 +542,12 @@ size_t mixer_scratch_floats(int n, int w, int h, int B) {
   // z, a, y, da, split partials of the weight gradients
   const size_t general = rows * k + rows * h + rows + rows * h + (size_t)kSplits * (h * k + h + 1);
   if (!fused_shape(w, h)) return general;
-  // the fused pass: one gradient per workgroup
-  const size_t wgs = (size_t)((n + kFusedSites - 1) / kFusedSites) * fused_groups(n, B);
-  return std::max(general, wgs * mixer_param_count(w, h));
+  // the fused pass: one gradient per workgroup.  A bound on fused_groups that does not
+  // fall with B (the groups themselves do: 256 for B = 256, 129 for B = 257), since a
+  // workspace sized for a batch serves the smaller ones too.
+  const size_t ib = (n + kFusedSites - 1) / kFusedSites;
+  const size_t groups = std::min<size_t>(B, std::max<size_t>(1, kFusedWGs / ib));
+  return std::max(general, ib * groups * mixer_param_count(w, h));
 }
 
 // forward: y (B x n) for states x (B x n).  scratch: mixer_scratch_floats.
