@@ -262,6 +262,15 @@ constexpr int kFusedSites = 64, kFusedHidden = 256, kFusedWGs = 256;
 
 inline int fused_blocks(int w) { return (2 * w + 1) / 32 + ((2 * w + 1) % 32 > 1 ? 1 : 0); }   // FB (0: one column)
 inline bool fused_shape(int w, int h) { return h <= kFusedHidden && fused_blocks(w) <= 4; }
+// Few sites fill little of a block, whose rows cost the same: with several states a
+// workgroup the general products, whose rows run on through the batch, win.  us,
+// general / fused, w = 8, h = 64: forward n = 8 16384 states 131 / 241, n = 16 1024
+// states 51 / 42, n = 8 64 states 41 / 31; gradient 16384 states n = 1 275 / 405, n = 3
+// 533 / 414 (w = 2, h = 16: 351 / 383), n = 8 1180 / 427.
+inline bool use_fused(int n, int w, int h, int B, bool grad) {
+  const bool sparse = grad ? n < kFusedSites / 16 && B > 4 * kFusedWGs : n < kFusedSites / 4 && B > kFusedWGs;
+  return fused_shape(w, h) && !sparse;
+}
 // Batch groups a 64-site block is cut into: about one workgroup per CU.
 inline int fused_groups(int n, int B) {
   const int ib = (n + kFusedSites - 1) / kFusedSites;
@@ -553,7 +562,7 @@ size_t mixer_scratch_floats(int n, int w, int h, int B) {
 // forward: y (B x n) for states x (B x n).  scratch: mixer_scratch_floats.
 hipError_t mixer_forward(const uint16_t* p16, int w, int h, const float* u, const float* en, int n, const float* x,
                          int B, float* y, float* scratch, hipStream_t s) {
-  if (fused_shape(w, h)) return launch_fused(p16, w, h, u, en, n, x, nullptr, B, y, nullptr, nullptr, s);
+  if (use_fused(n, w, h, B, false)) return launch_fused(p16, w, h, u, en, n, x, nullptr, B, y, nullptr, nullptr, s);
   const int k = mixer_features(w);
   const size_t rows = (size_t)B * n;
   const uint16_t* w1 = p16;
@@ -580,7 +589,7 @@ hipError_t mixer_loss_grad(const uint16_t* p16, int w, int h, const float* u, co
                            int idx, hipStream_t s) {
   const int k = mixer_features(w);
   const size_t rows = (size_t)B * n;
-  if (fused_shape(w, h)) {
+  if (use_fused(n, w, h, B, true)) {
     const int nwg = (n + kFusedSites - 1) / kFusedSites * fused_groups(n, B);
     hipError_t e = launch_fused(p16, w, h, u, en, n, x, t, B, nullptr, part, scratch, s);
     if (e != hipSuccess) return e;
