@@ -2026,7 +2026,6 @@ __global__ __launch_bounds__(128) void k_ritz_bounds(const double* ab, int k, Ct
   for (int i = threadIdx.x; i < k; i += 128) {
     sa[i] = ab[2 * i];
     sb[i] = ab[2 * i + 1];
-    sb2[i] = sb[i] * sb[i];
   }
   for (int i = k + threadIdx.x; i < k + 8; i += 128) sa[i] = sb2[i] = 0.0;   // read, not used
   __syncthreads();
@@ -2046,6 +2045,17 @@ __global__ __launch_bounds__(128) void k_ritz_bounds(const double* ab, int k, Ct
   for (int i = lane; i < k; i += 64)
     if (sb[i] <= 1e-12 * scale) kk = kk < i + 1 ? kk : i + 1;
   for (int o = 32; o > 0; o >>= 1) kk = min(kk, __shfl_xor(kk, o, 64));
+  // T in units of a power of two near its largest entry (exact), so that the leading
+  // minors, products of up to nine of its entries, stay in range for any finite H
+  const int ex = ilogb(scale);
+  const double one = ldexp(1.0, -ex);   // 1 in these units
+  __syncthreads();
+  for (int i = threadIdx.x; i < k; i += 128) {
+    sa[i] = ldexp(sa[i], -ex);
+    sb[i] = ldexp(sb[i], -ex);
+    sb2[i] = sb[i] * sb[i];
+  }
+  __syncthreads();
   const double beta_last = kk < k ? 0.0 : sb[k - 1];
   double lo = 1e300, hi = -1e300;
   for (int i = lane; i < kk; i += 64) {
@@ -2056,7 +2066,7 @@ __global__ __launch_bounds__(128) void k_ritz_bounds(const double* ab, int k, Ct
   lo = -wmax(-lo);
   hi = wmax(hi);
   const int want = wave == 0 ? 0 : kk - 1;   // the want-th smallest eigenvalue
-  for (int it = 0; it < 16 && hi - lo > 1e-15 * fmax(1.0, fabs(hi) + fabs(lo)); ++it) {
+  for (int it = 0; it < 16 && hi - lo > 1e-15 * fmax(one, fabs(hi) + fabs(lo)); ++it) {
     const double x = lo + (hi - lo) * ((lane + 1) / 65.0);
     // eigenvalues below x: sign changes of the leading minors p_i of T - x
     int cnt = 0;
@@ -2074,9 +2084,9 @@ __global__ __launch_bounds__(128) void k_ritz_bounds(const double* ab, int k, Ct
         cnt += in && (p < 0.0) != (pm < 0.0);
       }
       // keep both in range (a power of two)
-      const int ex = -ilogb(fmax(fabs(p), fabs(pm)));
-      p = ldexp(p, ex);
-      pm = ldexp(pm, ex);
+      const int down = -ilogb(fmax(fabs(p), fabs(pm)));
+      p = ldexp(p, down);
+      pm = ldexp(pm, down);
     }
     const unsigned long long above = __ballot(cnt > want);   // points above the eigenvalue
     const int first = above ? __ffsll((long long)above) - 1 : 64;
@@ -2091,7 +2101,7 @@ __global__ __launch_bounds__(128) void k_ritz_bounds(const double* ab, int k, Ct
   if (lane == 0) ritz[wave] = theta;
   __syncthreads();
   const double tmin = ritz[0], tmax = ritz[1];
-  const double width = fmax(tmax - tmin, 1e-12 * fmax(1.0, fabs(tmax)));
+  const double width = fmax(tmax - tmin, 1e-12 * fmax(one, fabs(tmax)));
   // |last component| of the extreme Ritz vectors: three steps of inverse
   // iteration with the shift just outside the spectrum (T - shift is definite
   // and its LDL^T solve stable)
@@ -2135,8 +2145,8 @@ __global__ __launch_bounds__(128) void k_ritz_bounds(const double* ab, int k, Ct
   __syncthreads();
   if (threadIdx.x == 0) {
     const double rmin = beta_last * comp[0], rmax = beta_last * comp[1];
-    double emin = fmax(tmin - fmax(rmin, 0.01 * width), ctl->gmin);
-    double emax = fmin(tmax + fmax(rmax, 0.01 * width), ctl->gmax);
+    double emin = fmax(ldexp(tmin - fmax(rmin, 0.01 * width), ex), ctl->gmin);
+    double emax = fmin(ldexp(tmax + fmax(rmax, 0.01 * width), ex), ctl->gmax);
     if (!(emax > emin)) {
       emin = ctl->gmin;
       emax = ctl->gmax;
