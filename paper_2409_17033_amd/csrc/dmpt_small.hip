@@ -115,7 +115,7 @@ template <int PREC, int B, int W> struct SGeo {
   static constexpr int TS = 32 * B, LS = TS + 1;
   using P = typename std::conditional<PREC == kFP32, double, float>::type;
   static constexpr int SUMS = KP * B * B * 16 * 64 * (int)sizeof(P);
-  static constexpr int PART = SUMS > TS * LS * 4 ? SUMS : TS * LS * 4;   // the tile takes the sums' place
+  static constexpr int PART = SUMS > TS * LS * 8 ? SUMS : TS * LS * 8;   // the tile (FP64 in a fold) takes the sums' place
   static constexpr int VX = (TS * TS / 4 + NTH - 1) / NTH;   // 16-byte pieces of the tile per thread
 };
 
@@ -125,12 +125,13 @@ template <int PREC, int B, int W> struct SGeo {
 // Two-level accumulation as in the large-size kernels: FP32 operands go into
 // FP64 sums every 4 stages, the split formats into a second FP32 level every
 // 4 x flush stages (within the wave's range); the waves' sums add in FP64.
+// fold: the tile of P + P^T (a diagonal tile of Z from Y X alone), still in FP64.
 // ov runs while the first loads are in flight (false: leave, in every thread
 // alike); pre runs before the partial sums are exchanged.
 template <int PREC, int B, int W, class Ov, class Pre>
 __device__ __forceinline__ bool tile_sum(const char* a0, const char* b0, const char* a1, const char* b1, int spass,
-                                         int nst, int n_pad, int flush, float scale, float scale2, LDS_AS char* part_,
-                                         int wave, int lane, Ov ov, Pre pre) {
+                                         int nst, int n_pad, int flush, float scale, float scale2, bool fold,
+                                         LDS_AS char* part_, int wave, int lane, Ov ov, Pre pre) {
   using G = SGeo<PREC, B, W>;
   constexpr int D = SFmt<PREC>::D, BA = G::BA, NB = BA * B;
   const int h = lane >> 5, l32 = lane & 31;
@@ -223,23 +224,33 @@ __device__ __forceinline__ bool tile_sum(const char* a0, const char* b0, const c
   __syncthreads();
   // register e of a 32 x 32 block: row 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32
   constexpr int PER = B * B * 16 / G::NWV;
-  float f[PER];
+  auto row = [&](int idx) { return ((idx >> 4) / B) * 32 + 8 * ((idx & 15) >> 2) + 4 * h + (idx & 3); };
+  auto col = [&](int idx) { return ((idx >> 4) % B) * 32 + l32; };
+  double v[PER];
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int idx = wave * PER + k;
-    double v = 0.0;
+    v[k] = 0.0;
 #pragma unroll
-    for (int w = 0; w < G::KP; ++w) v += (double)part[(w * B * B * 16 + idx) * 64 + lane];
-    f[k] = (float)v;
-    f[k] *= scale;
-    f[k] *= scale2;
+    for (int w = 0; w < G::KP; ++w) v[k] += (double)part[(w * B * B * 16 + idx) * 64 + lane];
   }
   __syncthreads();   // the sums are read: the tile takes their place
+  if (fold) {
+    LDS_AS double* T = (LDS_AS double*)part_;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) T[row(wave * PER + k) * G::LS + col(wave * PER + k)] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) v[k] += T[col(wave * PER + k) * G::LS + row(wave * PER + k)];
+    __syncthreads();
+  }
   LDS_AS float* T = (LDS_AS float*)part_;
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int idx = wave * PER + k, q = idx >> 4, e = idx & 15;
-    T[((q / B) * 32 + 8 * (e >> 2) + 4 * h + (e & 3)) * G::LS + (q % B) * 32 + l32] = f[k];
+    float f = (float)v[k];
+    f *= scale;
+    f *= scale2;
+    T[row(wave * PER + k) * G::LS + col(wave * PER + k)] = f;
   }
   return true;
 }
@@ -439,7 +450,7 @@ __device__ __forceinline__ void small_job(const StepArgs& a, const int kind, con
   const size_t rI = panel_off<PREC>(ti * TS, a.n_pad), rJ = panel_off<PREC>(tj * TS, a.n_pad);
   const int fl = MIX && zk && a.flush_z > 0 ? a.flush_z : a.flush;
   if (!tile_sum<PREC, B, W>((zk ? yop : xop) + rI, xop + rJ, xop + rI, yop + rJ, spass, nst, a.n_pad, fl, usc,
-                         a.oscale != 0.0f ? a.oscale : 1.0f, part, wave, lane, ov, pre))
+                         a.oscale != 0.0f ? a.oscale : 1.0f, fold, part, wave, lane, ov, pre))
     return;
   if constexpr (PREC == kSplitH) {
     if (zk) {   // s_red was written before tile_sum's barrier
@@ -478,8 +489,7 @@ __device__ __forceinline__ void small_job(const StepArgs& a, const int kind, con
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       if (diag && r > c + k) continue;   // a diagonal tile keeps its upper triangle and mirrors it
-      float p = T[r * LS + c + k];
-      if (fold) p += T[(c + k) * LS + r];   // below the diagonal nothing is overwritten
+      const float p = T[r * LS + c + k];
       const float v = sigma > 0 ? p : 2.0f * x[k] - p;
       T[r * LS + c + k] = v;
       const double w = diag && r == c + k ? 1.0 : 2.0;
@@ -690,7 +700,7 @@ void k_prod_small(ProdArgs a) {
     }
     return true;
   };
-  tile_sum<PREC, B, W>(pa + rI, pb + rJ, pb + rI, pa + rJ, spass, nst, a.n_pad, a.flush, 1.0f, 1.0f, (LDS_AS char*)part,
+  tile_sum<PREC, B, W>(pa + rI, pb + rJ, pb + rI, pa + rJ, spass, nst, a.n_pad, a.flush, 1.0f, 1.0f, false, (LDS_AS char*)part,
                        wave, lane, ov, [] {});
   int ec = a.ec;
   if constexpr (PREC == kSplitH) {
