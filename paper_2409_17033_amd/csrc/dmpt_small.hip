@@ -125,12 +125,13 @@ template <int PREC, int B, int W> struct SGeo {
 // Two-level accumulation as in the large-size kernels: FP32 operands go into
 // FP64 sums every 4 stages, the split formats into a second FP32 level every
 // 4 x flush stages (within the wave's range); the waves' sums add in FP64.
+// kr, kc: the tile's rows and columns in units of 32 (32 x 32 tiles).
 // fold: the tile of P + P^T (a diagonal tile of Z from Y X alone), still in FP64.
 // ov runs while the first loads are in flight (false: leave, in every thread
 // alike); pre runs before the partial sums are exchanged.
 template <int PREC, int B, int W, class Ov, class Pre>
 __device__ __forceinline__ bool tile_sum(const char* a0, const char* b0, const char* a1, const char* b1, int spass,
-                                         int nst, int n_pad, int flush, float scale, float scale2, bool fold,
+                                         int nst, int n_pad, int flush, int kr, int kc, float scale, float scale2, bool fold,
                                          LDS_AS char* part_, int wave, int lane, Ov ov, Pre pre) {
   using G = SGeo<PREC, B, W>;
   constexpr int D = SFmt<PREC>::D, BA = G::BA, NB = BA * B;
@@ -152,8 +153,9 @@ __device__ __forceinline__ bool tile_sum(const char* a0, const char* b0, const c
   f32x16 acc[BA][B];
 #pragma unroll
   for (int q = 0; q < NB; ++q) acc[q / B][q % B] = f32x16{0};
+  const int skip = PREC == kFP32 ? s0 & 3 : 0, t0 = s0 - skip;
 #pragma unroll
-  for (int d = 0; d < D - 1; ++d) load(o[d], s0 + d);
+  for (int d = 0; d < D - 1; ++d) load(o[d], t0 + d);
   __builtin_amdgcn_sched_barrier(0);
   if (!ov()) return false;
   LDS_AS typename G::P* part = (LDS_AS typename G::P*)part_;
@@ -164,22 +166,36 @@ __device__ __forceinline__ bool tile_sum(const char* a0, const char* b0, const c
     for (int q = 0; q < NB; ++q)
 #pragma unroll
       for (int e = 0; e < 16; ++e) td[q][e] = 0.0;
-    // each block goes into its FP64 sum once in 4 stages, the blocks at different ones:
-    // no FP32 chain is longer than 4 stages
+    // Each block goes into its FP64 sum once in 4 stages, so that no FP32 chain is longer
+    // (64 columns).  Where the chains end matters: X and Y have their largest entries
+    // on and near the diagonal, so a tile's largest terms are those of its own rows'
+    // and columns' k range, and every addition after them in their chain rounds at
+    // their size.  So the chains end at fixed columns, whatever stage a wave's range begins
+    // with (the loop begins with the stage below that is a multiple of 4).  Two blocks
+    // of columns a wave: each after its own 32 columns.  One (32 x 32 tiles): after every
+    // other 32 columns, the tile's own among them, and after its rows'.  Ended every 4
+    // stages of a wave's range instead, errors in D and chi were 1.1 - 1.5 times these
+    // (FP32, n = 128 - 1100).
+    static_assert(NB == 1 || NB == 2, "FP32 waves take one or two blocks");
 #define DMPT_SSTAGE(K)                                                              \
   {                                                                                 \
-    load(o[((K) + D - 1) % D], s0 + s + (K) + D - 1);                               \
+    load(o[((K) + D - 1) % D], t0 + s + (K) + D - 1);                               \
     __builtin_amdgcn_sched_barrier(0);                                              \
-    if (s + (K) < cnt) {                                                            \
+    if (s + (K) >= skip && s + (K) < cnt + skip) {                                  \
       constexpr int blk = (K) * NB / 4;                                             \
       s_mma<PREC, BA, B, blk>(o[K], acc);                                           \
-      if ((K) % (4 / NB) == 4 / NB - 1) {                                                 \
+      bool end = ((K) & 1) != 0;                                                    \
+      if constexpr (NB == 1 && ((K) & 1) != 0) {                                    \
+        const int t = t0 + s + (K), c = (t < spass ? t : t - spass) >> 1;           \
+        end = ((c ^ kc) & 1) == 0 || c == kr;                                       \
+      }                                                                             \
+      if (end) {                                                                    \
         _Pragma("unroll") for (int e = 0; e < 16; ++e) td[blk][e] += (double)acc[blk / B][blk % B][e]; \
         acc[blk / B][blk % B] = f32x16{0};                                          \
       }                                                                             \
     }                                                                               \
   }
-    for (int s = 0; s < cnt; s += 4) {
+    for (int s = 0; s < cnt + skip; s += 4) {
       DMPT_SSTAGE(0)
       DMPT_SSTAGE(1)
       DMPT_SSTAGE(2)
@@ -449,7 +465,7 @@ __device__ __forceinline__ void small_job(const StepArgs& a, const int kind, con
   };
   const size_t rI = panel_off<PREC>(ti * TS, a.n_pad), rJ = panel_off<PREC>(tj * TS, a.n_pad);
   const int fl = MIX && zk && a.flush_z > 0 ? a.flush_z : a.flush;
-  if (!tile_sum<PREC, B, W>((zk ? yop : xop) + rI, xop + rJ, xop + rI, yop + rJ, spass, nst, a.n_pad, fl, usc,
+  if (!tile_sum<PREC, B, W>((zk ? yop : xop) + rI, xop + rJ, xop + rI, yop + rJ, spass, nst, a.n_pad, fl, ti, tj, usc,
                          a.oscale != 0.0f ? a.oscale : 1.0f, fold, part, wave, lane, ov, pre))
     return;
   if constexpr (PREC == kSplitH) {
@@ -700,7 +716,7 @@ void k_prod_small(ProdArgs a) {
     }
     return true;
   };
-  tile_sum<PREC, B, W>(pa + rI, pb + rJ, pb + rI, pa + rJ, spass, nst, a.n_pad, a.flush, 1.0f, 1.0f, false, (LDS_AS char*)part,
+  tile_sum<PREC, B, W>(pa + rI, pb + rJ, pb + rI, pa + rJ, spass, nst, a.n_pad, a.flush, ti, tj, 1.0f, 1.0f, false, (LDS_AS char*)part,
                        wave, lane, ov, [] {});
   int ec = a.ec;
   if constexpr (PREC == kSplitH) {
