@@ -1387,7 +1387,7 @@ struct FMat {
 };
 
 // Fixed exponents of the FP16 copies (entry bounds x 2^e <= 2^14..2^15):
-// |E| <= 1/2 (E = D - I/2; its start at kXScaleExp), |E^2| <= 1/4, |R| and |T|
+// |E| <= 1/2 (E = D - I/2), |E^2| <= 1/4, |R| and |T|
 // near 1 (spectra in [1/2, 1] and about 1).  Y, S and W take the exponent that
 // bounds a multiple of ||Y||_F: ||S||_2 <= 2 ||E||_2 ||Y||_F <= ||Y||_F,
 // ||W|| <= (2 + 4 ||E'||_2) ||Y||_F <= 4 ||Y||_F, ||Y'|| <= ||W||, each with a margin.
@@ -1526,9 +1526,10 @@ dmpt_status dmpt_susceptibility_fermi(const float* H, const float* A, int32_t no
       r.stride_meta = smeta;
       return r;
     };
-    E[0].e = cprec == kSplitH ? kXScaleExp : 0;
+    E[0].e = cprec == kSplitH ? kExpE : 0;
     const MatRef yr = ref(Y, ymeta[0], w.meta);
-    DMPT_HIP(launch_init(cprec, tl, H, A, n, np, ny, ref(E[0], ymeta[0], 0), yr, -c, (Part*)(ws + p.off_part[0]), ctl, s));
+    DMPT_HIP(launch_init(cprec, tl, H, A, n, np, ny, ref(E[0], ymeta[0], 0), yr, -c, (Part*)(ws + p.off_part[0]), ctl, s,
+                         kExpE));
     if (cprec == kSplitH && ny > 0) DMPT_HIP(launch_resplit(cprec, yr, np, ny, tl, s));
     for (int step = 0; step < m; ++step) {
       FMat &Ec = E[cur], &En = E[cur ^ 1];

@@ -175,8 +175,9 @@ hipError_t launch_set_affine(Ctl* ctl, double alpha, double beta, hipStream_t s)
 hipError_t launch_set_bounds(Ctl* ctl, double emin, double emax, hipStream_t s);
 // tiled (here and below): the padded FP32 matrices and the operand copies are
 // in the small-size kernels' layouts (m_off, op_off in dmpt_device.h).
+// x_exp: exponent of X_1's copy (kSplitH).
 hipError_t launch_init(int prec, int tiled, const float* h, const float* a, int n, int n_pad, int nobs, MatRef x,
-                       MatRef y, double y_scale_mode, Part* part, Ctl* ctl, hipStream_t s);
+                       MatRef y, double y_scale_mode, Part* part, Ctl* ctl, hipStream_t s, int x_exp = kXScaleExp);
 // Workgroups of a persistent step launch over njobs jobs (one per CU at most).
 int persistent_grid(int njobs);
 // Step launch: a persistent grid of at most one workgroup per CU working

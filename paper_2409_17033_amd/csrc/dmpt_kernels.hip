@@ -2412,7 +2412,7 @@ hipError_t launch_resplit(int prec, MatRef m, int n_pad, int nmat, int tiled, hi
 // block its own in a fixed order.
 __device__ __forceinline__ void init_block(int prec, const float (*p)[65], const float (*q)[65], int bi, int bj,
                                            int nb, int n, int n_pad, int z, const MatRef& x, const MatRef& y,
-                                           double y_scale_mode, Part* part, const Ctl* ctl, double* s_red, int tiled) {
+                                           double y_scale_mode, Part* part, const Ctl* ctl, double* s_red, int tiled, int x_exp) {
   // output block (bi, bj): element (r, c) = (p[r][c] + q[c][r]) / 2, p the
   // source block (bi, bj), q the source block (bj, bi)
   const int t = threadIdx.x;
@@ -2421,14 +2421,14 @@ __device__ __forceinline__ void init_block(int prec, const float (*p)[65], const
   const MatRef& m = z == 0 ? x : y;
   float* o32 = m.f32 + (z == 0 ? 0 : (size_t)(z - 1) * m.stride_f32);
   char* oop = (char*)m.op + (z == 0 ? 0 : (size_t)(z - 1) * m.stride_op);
-  // kSplitH: X_1's copy at the fixed 2^14; a Y copy needs the matrix's norm
+  // kSplitH: X_1's copy at 2^x_exp; a Y copy needs the matrix's norm
   // first, so here Y gets only its master and norm partials (k_resplit
   // writes the copy)
   const bool ycopy_later = prec == kSplitH && z != 0;
   // three-term-X^2 option: X_1 gets its three- and two-term copies, Y_1 the two-term one
   const int fmt = prec == kSplit32 ? (z == 0 ? kSplit3 : kSplit2) : prec;
   char* oop2 = prec == kSplit32 && z == 0 ? (char*)x.op2 : nullptr;
-  const float sc = prec == kSplitH ? ldexpf(1.0f, kXScaleExp) : 1.0f;
+  const float sc = prec == kSplitH ? ldexpf(1.0f, x_exp) : 1.0f;
   double tr = 0.0, sq = 0.0;
   // each thread: 2 groups of 8 consecutive columns
   for (int gidx = t; gidx < 64 * 8; gidx += 256) {
@@ -2488,7 +2488,7 @@ __device__ __forceinline__ void init_block(int prec, const float (*p)[65], const
 
 __global__ __launch_bounds__(256) void k_init(int prec, const float* h, const float* a, int n,
                                               int n_pad, int zoff, MatRef x, MatRef y,
-                                              double y_scale_mode, Part* part, Ctl* ctl, int tiled) {
+                                              double y_scale_mode, Part* part, Ctl* ctl, int tiled, int x_exp) {
   __shared__ float tile[64][65];    // block (bi, bj) of the source
   __shared__ float tileT[64][65];   // block (bj, bi) of the source
   __shared__ double s_red[8];
@@ -2520,21 +2520,21 @@ __global__ __launch_bounds__(256) void k_init(int prec, const float* h, const fl
   if (bad) ctl->nonfinite = 1;
   __syncthreads();
   if (bi == bj) {
-    init_block(prec, tile, tile, bi, bj, nb, n, n_pad, z, x, y, y_scale_mode, part, ctl, s_red, tiled);
+    init_block(prec, tile, tile, bi, bj, nb, n, n_pad, z, x, y, y_scale_mode, part, ctl, s_red, tiled, x_exp);
   } else {
-    init_block(prec, tile, tileT, bi, bj, nb, n, n_pad, z, x, y, y_scale_mode, part, ctl, s_red, tiled);
-    init_block(prec, tileT, tile, bj, bi, nb, n, n_pad, z, x, y, y_scale_mode, part, ctl, s_red, tiled);
+    init_block(prec, tile, tileT, bi, bj, nb, n, n_pad, z, x, y, y_scale_mode, part, ctl, s_red, tiled, x_exp);
+    init_block(prec, tileT, tile, bj, bi, nb, n, n_pad, z, x, y, y_scale_mode, part, ctl, s_red, tiled, x_exp);
   }
 }
 
 // nobs >= 0: X_1 and nobs observables; nobs < 0: only the -nobs observables.
 hipError_t launch_init(int prec, int tiled, const float* h, const float* a, int n, int n_pad, int nobs, MatRef x,
-                       MatRef y, double y_scale_mode, Part* part, Ctl* ctl, hipStream_t s) {
+                       MatRef y, double y_scale_mode, Part* part, Ctl* ctl, hipStream_t s, int x_exp) {
   const int nb = n_pad / 64;
   const int zoff = nobs < 0 ? 1 : 0;
   const int nz = nobs < 0 ? -nobs : 1 + nobs;
   hipLaunchKernelGGL(k_init, dim3(nb, nb, nz), dim3(256), 0, s, prec, h, a, n, n_pad, zoff, x, y,
-                     y_scale_mode, part, ctl, tiled);
+                     y_scale_mode, part, ctl, tiled, x_exp);
   return hipGetLastError();
 }
 
