@@ -32,6 +32,7 @@
 
 #include "dmpt_device.h"
 #include "dmpt_internal.h"
+#include "dmpt_tiles.h"
 #include "sp2_rule.h"
 
 namespace dmpt {
@@ -270,80 +271,6 @@ __device__ __forceinline__ bool tile_sum(const char* a0, const char* b0, const c
   }
   return true;
 }
-
-// Tile t of the upper triangle (J >= I) of an nt x nt grid: bands of 4 tile
-// rows, first the band's own triangle, then its columns from left to right,
-// so that a run of tiles shares few row panels.
-__device__ __forceinline__ void tri_tile(int t, int nt, int* ti, int* tj) {
-  const float m = (float)nt + 0.5f;
-  int i = (int)(m - sqrtf(m * m - 2.0f * (float)t));
-  i = i < 0 ? 0 : i > nt - 1 ? nt - 1 : i;
-  while (i > 0 && i * nt - i * (i - 1) / 2 > t) --i;
-  while (i + 1 < nt && (i + 1) * nt - (i + 1) * i / 2 <= t) ++i;
-  const int r0 = i & ~3, hb = nt - r0 < 4 ? nt - r0 : 4;   // the band's first row and height
-  int local = t - (r0 * nt - r0 * (r0 - 1) / 2);
-  if (local < hb * (hb + 1) / 2) {
-    int r = 0;
-    while (local >= hb - r) {
-      local -= hb - r;
-      ++r;
-    }
-    *ti = r0 + r;
-    *tj = r0 + r + local;
-  } else {
-    local -= hb * (hb + 1) / 2;
-    *ti = r0 + local % hb;
-    *tj = r0 + hb + local / hb;
-  }
-}
-
-// Tile t of a whole nt x nt grid in the same bands.
-__device__ __forceinline__ void full_tile(int t, int nt, int* ti, int* tj) {
-  const int r0 = t / (4 * nt) * 4, hb = nt - r0 < 4 ? nt - r0 : 4;
-  const int local = t - r0 * nt;
-  *ti = r0 + local % hb;
-  *tj = local / hb;
-}
-
-// Position p of cnt tiles as workgroups are dealt to the XCDs in turn: each
-// XCD takes a contiguous run of tiles, which share row panels in its L2.
-__device__ __forceinline__ int xcd_order(int p, int cnt) {
-  const int x = p & 7, per = cnt >> 3, rest = cnt & 7;
-  return x * per + (x < rest ? x : rest) + (p >> 3);
-}
-
-// Tiles of the upper triangle in the order of a step launch: the first diagonal tiles
-// (a multiple of 8 up to half of them), those above the diagonal, the other
-// diagonal tiles.  Z's diagonal tiles take half as long as its others: spread over the
-// XCDs and over both ends of the launch they even out the CUs that take one tile more:
-// n = 1024, FP32, 528 tiles of 32 x 32 on 256 CUs: the self-consistent loop, whose
-// launches are sweeps, 21.8 -> 16.8 ms (with the diagonal tiles in one run, which goes to
-// one XCD, no gain).
-// Launches over several observables keep the bands' own order and whole diagonal
-// tiles: n = 1500, four of them, FP16 split 4.3 ms, spread 4.6; n = 1000 2.1, and 2.3 with
-// the shorter diagonal tiles in the bands' order.
-struct StepOrder {
-  int nt, first, off;
-  bool spread;
-  __device__ __forceinline__ StepOrder(int nt_, bool spread_)
-      : nt(nt_), first((nt_ / 2) & ~7), off(nt_ * (nt_ - 1) / 2), spread(spread_) {}
-  // workgroup b of the first cw tiles: its tile
-  __device__ __forceinline__ int at(int b, int cw) const {
-    if (!spread) return xcd_order(b, cw);
-    const int w = cw - first < 0 ? 0 : cw - first < off ? cw - first : off;   // of those above the diagonal
-    return b >= first && b < first + w ? first + xcd_order(b - first, w) : b;
-  }
-  __device__ __forceinline__ void tile(int t, int* ti, int* tj) const {
-    if (!spread) {
-      tri_tile(t, nt, ti, tj);
-    } else if (t >= first && t < first + off) {
-      tri_tile(t - first, nt - 1, ti, tj);
-      ++*tj;
-    } else {
-      *ti = *tj = t < first ? t : t - off;
-    }
-  }
-};
 
 // This thread's part of the sum of a matrix's norm partials, four loads in flight.
 template <int NTH>
@@ -589,30 +516,13 @@ __device__ __forceinline__ void small_job(const StepArgs& a, const int kind, con
   }
 }
 
-// Tiles of one kind (Z of nz observables, or P): job b of the `whole` whole tiles, or
-// with B = 1 quarter b of the tiles after them.
+// Job b of a kind (small_place).
 template <int PREC, int B, int W, bool MIX>
 __device__ __forceinline__ void small_jobs(const StepArgs& a, const int kind, int b, const int whole, const bool quarter, const bool spread,
                                            LDS_AS char* part, double* s_ctl, double* s_red, int* s_code) {
-  const int nt = a.n_pad / (quarter ? 64 : 32 * B), tri = nt * (nt + 1) / 2;
-  const StepOrder order(nt, spread);
-  const int f = quarter ? whole + (b >> 2) : b, obs = f < tri ? 0 : f / tri;
-  const int left = whole - obs * tri, cw = left < 0 ? 0 : left < tri ? left : tri;   // the observable's whole tiles
-  int t = f - obs * tri, ti, tj, slot = t;
-  bool next = false;
-  if (!quarter) slot = t = order.at(t, cw);
-  order.tile(t, &ti, &tj);
-  if (quarter) {
-    const int q = b & 3;
-    slot = cw + 4 * (t - cw) + q;
-    if (ti == tj) {
-      if (q == 2) return;   // below the diagonal: the mirror of quarter 1, which clears its entry
-      next = q == 1;
-    }
-    ti = 2 * ti + (q >> 1);
-    tj = 2 * tj + (q & 1);
-  }
-  small_job<PREC, B, W, MIX>(a, kind, obs, ti, tj, slot, next, cw + 4 * (tri - cw), spread, part, s_ctl, s_red, s_code);
+  const SmallPlace p = small_place(a.n_pad, 32 * B, b, whole, quarter, spread);
+  if (p.none) return;
+  small_job<PREC, B, W, MIX>(a, kind, p.obs, p.ti, p.tj, p.slot, p.next, p.slots, spread, part, s_ctl, s_red, s_code);
 }
 
 // Workgroups: the first zw of the nz observables' Z tiles, the others in quarters, the
