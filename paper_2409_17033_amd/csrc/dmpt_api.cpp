@@ -1608,7 +1608,6 @@ dmpt_status dmpt_susceptibility_fermi(const float* H, const float* A, int32_t no
         q.m = Yk.m;
         q.sm = np2;
         if (step + 1 < m) scaled(&q, &Yk, kBoundW, ymeta[ym ^ 1] + (size_t)k0 * w.meta);
-        q.m = Yk.m;
         q.sc = mop;
         DMPT_HIP(prods.run(cprec, q));
       }

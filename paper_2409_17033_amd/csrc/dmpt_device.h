@@ -235,8 +235,7 @@ __device__ __forceinline__ double prod_region(const ProdArgs& a, int k, LDS_AS f
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       if (diag && r > c + q) continue;
-      float v = alpha * T[r * LS + c + q] + a.beta * xv[z][q];
-      if (gr0 + r == gc0 + c + q && gr0 + r < a.n) v += a.delta;
+      const float v = alpha * T[r * LS + c + q] + a.beta * xv[z][q];
       T[r * LS + c + q] = v;
       if (a.mo) sq += (sym && !(diag && r == c + q) ? 2.0 : 1.0) * (double)v * (double)v;
     }

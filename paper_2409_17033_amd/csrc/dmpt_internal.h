@@ -39,10 +39,11 @@ __host__ __device__ constexpr int operand_bytes(int prec) {
 // Bytes per element of the second (two-term) operand copy of the kSplit32 option.
 __host__ __device__ constexpr int operand2_bytes(int prec) { return prec == kSplit32 ? 4 : 0; }
 
-constexpr int kPadTo = 256;     // n is padded (with zeros in X-space) to a multiple of this
+constexpr int kPadTo = 256;     // n is padded (with zeros in X-space) to a multiple of this; on the small-size kernels of 64
 constexpr int kMaxObs = 64;
 
-// Per-step record written by workgroup 0 of the step kernel (step n, 1-based).
+// Per-step record written by one workgroup of the step launch, the first one or, on the
+// small-size kernels, the last one (step n, 1-based).
 struct StepRec {
   double tr;    // Tr X_n
   double sq;    // ||X_n||_F^2
@@ -260,7 +261,7 @@ hipError_t launch_copy_out(const float* src, int n, int n_pad, float* dst, int t
 // General products of n_pad x n_pad matrices with a fused epilogue, for a batch
 // of `nb` matrices (strides in bytes of operands and copies, in elements of
 // FP32 matrices; 0: shared by the batch):
-//   V = alpha P + beta X + delta I_n,  P = A B^T (all tiles, or kProdSym: known
+//   V = alpha P + beta X,  P = A B^T (all tiles, or kProdSym: known
 //   to be symmetric, upper triangle and its mirror) or kProdAnti: A B^T + B A^T.
 // Operands: FP32 matrices (kFP32) or operand copies; for kSplitH the copies'
 // exponents ea, eb (ma, mb set: the matrix's own, from its metadata).  Outputs
@@ -277,7 +278,7 @@ struct ProdArgs {
   int ea, eb;
   const char *ma, *mb;
   size_t sma, smb;
-  float alpha, beta, delta;
+  float alpha, beta;
   const float* x;
   size_t sx;
   float* m;

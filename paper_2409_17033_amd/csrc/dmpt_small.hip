@@ -7,9 +7,11 @@
 // and a launch then takes as long as one tile's serial K loop.  Here a
 // workgroup owns one TS x TS tile and each of its waves forms the whole tile
 // over its own part of the K range, so a tile's loop is NWV times shorter and
-// there are 8 times as many tiles.  Waves share no operand bytes (different k),
-// so operands go straight from memory to registers: no LDS ring, no barrier in
-// the loop, D stages in flight.  The partial sums meet in LDS (added in
+// there are 8 times as many tiles.  Such waves share no operand bytes (different
+// k), so operands go straight from memory to registers: no LDS ring, no barrier in
+// the loop, D stages in flight.  (FP32 64 x 64 tiles, whose waves keep FP64 sums
+// beside their accumulators: a wave forms half of the tile's rows, and two waves read
+// the same columns' operands.)  The partial sums meet in LDS (added in
 // FP64, in wave order), and the workgroup runs the tile's epilogue.
 //
 // What bounds it, and what it measured (one step of one observable, us; the
