@@ -185,8 +185,12 @@ int square_tile(int prec, int n, int matrices) {
 //    much longer: z = 1: n = 4600 83 / 91, n = 5000 111 / 103; z = 4: n = 2400
 //    37 / 43; z = 16: n = 1400 28 / 41, n = 2048 90 / 89.
 //  * Corrected runs of the three-term-X^2 option have wide sweep tiles and
-//    K-split tails in the large-size lists: those take over at n = 2048
-//    already (6.1 / 8.3; z = 4: 15.0 / 14.6).
+//    K-split tails in the large-size lists, which run from n = 1985 on.  That is
+//    below where the times cross for few observables, and no more than the size
+//    from which these lists are used and checked: z = 1: n = 1984 5.1 / 8.0, n = 2048
+//    5.6 / 8.2, n = 2560 10.3 / 11.4, n = 2900 15.1 / 15.7, n = 3072 16.7 / 16.0; z = 2:
+//    n = 2048 8.3 / 9.7, n = 2500 14.5 / 15.1, n = 2900 22.5 / 22.3; z = 4: n = 1984 13.0 /
+//    13.8, n = 2048 14.4 / 14.2, n = 2304 19.5 / 18.5; z = 8: n = 1984 23.7 / 23.8.
 //  * 32 or 64: see square_tile.
 int small_tile(int prec, bool wide_lists, int n, int z, int with_p) {
   const int nmax = wide_lists ? 1984 : prec == kFP32 ? (z <= 1 ? 4608 : z <= 4 ? 2560 : 2048)
@@ -196,11 +200,14 @@ int small_tile(int prec, bool wide_lists, int n, int z, int with_p) {
 
 // The same for a solve made of general products (the finite-temperature path; not
 // by the number of observables, whose batches give the bits of single ones).
-// Whole solves with one observable, ms, small / large: FP16 split n = 2048 22.3 /
-// 25.2, n = 2600 29.1 / 36.4, n = 3000 40.7 / 40.6, n = 3500 62.9 / 51.5; FP32, where
-// the padding to 256 and the number of tiles move the large side more, n = 2048
-// 55.1 / 49.9, n = 2300 51.6 / 60.3, n = 3000 107 / 128, n = 3500 171 / 162, n = 4096
-// 324 / 270.
+// The line is where the small side stops winning at most sizes; the large one also
+// wins by 5 - 13 % where n fills a multiple of 512 of its padding (n = 2048, 2560).
+// Whole solves with one observable (gapped, kT = 0.01), ms, small / large: FP16 split
+// n = 2048 38.8 / 46.1, n = 2304 44.9 / 53.9, n = 2560 66.2 / 63.0, n = 2816 74.9 / 84.5,
+// n = 3072 95.0 / 93.9, n = 3328 122 / 106; FP32 n = 1536 39.4 / 47.8, n = 2048 98.0 / 87.2,
+// n = 2304 113 / 129, n = 2560 163 / 143, n = 2816 182 / 264, n = 3072 243 / 289, n = 3328
+// 313 / 321; gapless: FP32 n = 3500 171 / 162, n = 4096 324 / 270, FP16 split n = 3500
+// 62.9 / 51.5.
 int product_tile(int prec, int n) {
   return n > (prec == kFP32 ? 3328 : 2944) ? 0 : square_tile(prec, n, 1);
 }
