@@ -39,6 +39,13 @@ PRODUCTS = {"split3_bf16": (6, 6), "split3x_bf16": (6, 3), "split_bf16": (3, 3),
             "fp32": (1, 1), "bf16": (1, 1)}
 
 
+def padded(n, info):
+    """The size the step launches run at: the small-size kernels (square tiles of
+    64 or 32, info["tile"]) pad to multiples of 64, the large ones of 256."""
+    to = 64 if info["tile"] <= 64 else 256
+    return -(-n // to) * to
+
+
 def step_flops(prec, n_pad, m, sweep_steps, nobs=1):
     """Executed MFMA flops of the m step launches on the upper-triangle
     tiles: X^2 as a symmetric rank-n product (n^3 per product) in every
@@ -103,19 +110,18 @@ def run_shapes(args, dm, torch, W, dev):
         wl = W.water_shaped(mol)
         log(f"water-shaped N={wl.n} generated in {time.perf_counter() - t:.1f} s")
         H, A, H1 = (torch.from_numpy(x).to(dev) for x in (wl.H, wl.A[0], wl.H1[0]))
-        n_pad = -(-wl.n // 256) * 256
-        row = {"molecules": mol, "n": wl.n, "nocc": wl.nocc, "n_pad": n_pad, "paths": {}}
+        row = {"molecules": mol, "n": wl.n, "nocc": wl.nocc, "paths": {}}
         for path in dict.fromkeys([args.precision, "split_fp16", "fp32"]):
             prec = path.partition("+")[0]
             ms, chi, D, a0, resp, infos = run_path(dm, torch, H, A, H1, wl.nocc, path, args.steps, args.warmup)
             info = infos[-1]
-            m = info["m"]
+            m, n_pad = info["m"], padded(wl.n, info)
             step_avg = info["step_ms"] / max(m, 1)
             executed = step_flops(prec, n_pad, m, info["sweep_steps"]) / (info["step_ms"] * 1e-3) / 1e12
             d1, _, _, info1 = dm.susceptibility(H, H1, wl.nocc, spin=1.0, want_density=False, **path_kw(path))
             r_d1 = 2.0 * float(dm.response(d1, A)[0, 0])
             row["paths"][path] = {
-                "ms": round(ms, 3), "m": m, "step_avg_ms": round(step_avg, 4),
+                "ms": round(ms, 3), "m": m, "n_pad": n_pad, "step_avg_ms": round(step_avg, 4),
                 "mfma_tflops": round(executed, 1), "mfma_tflops_fma1": round(executed / 2, 1),
                 "algorithmic_tflops": round(3.0 * float(wl.n) ** 3 * m / (ms * 1e-3) / 1e12, 1),
                 "tr_chi_h1": float(resp[0, 0]), "s_tr_a_d1": r_d1, "m_d1": info1["m"],
@@ -402,7 +408,7 @@ def main():
         info = infos[-1]
         props = property_errors(torch, H, A, D, chi, wl.nocc, 2.0)
         m = info["m"]
-        n_pad = -(-wl.n // 256) * 256
+        n_pad = padded(wl.n, info)
         flops = step_flops(prec, n_pad, m, info["sweep_steps"])   # executed MFMA flops of the m step launches
         step_avg_ms = info["step_ms"] / max(m, 1)
         results[path] = {

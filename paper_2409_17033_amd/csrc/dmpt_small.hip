@@ -142,7 +142,12 @@ __device__ __forceinline__ bool tile_sum(const char* a0, const char* b0, const c
   const int kp = wave / G::WR, wr = wave % G::WR;
   const size_t step_b = SFmt<PREC>::BLK, rstep = (size_t)32 * n_pad * operand_bytes(PREC);
   const uint32_t off = 16u * (uint32_t)lane;
-  const int per = (nst + G::KP - 1) / G::KP;
+  // FP32 ranges begin with a multiple of 4 stages (their chains end at fixed columns, see
+  // below): of two ranges the first takes the odd pair; four of them, of fewer stages
+  // each, may begin anywhere, and the loop passes over the stages before.
+  constexpr bool PASS = PREC == kFP32 && (NB == 1 || G::KP > 2);
+  int per = (nst + G::KP - 1) / G::KP;
+  if (PREC == kFP32 && !PASS) per = (per + 3) & ~3;
   const int s0 = kp * per;
   const int cnt = s0 >= nst ? 0 : (nst - s0 < per ? nst - s0 : per);
   const size_t arow = (size_t)(wr * BA) * rstep;
@@ -156,7 +161,7 @@ __device__ __forceinline__ bool tile_sum(const char* a0, const char* b0, const c
   f32x16 acc[BA][B];
 #pragma unroll
   for (int q = 0; q < NB; ++q) acc[q / B][q % B] = f32x16{0};
-  const int skip = PREC == kFP32 ? s0 & 3 : 0, t0 = s0 - skip;
+  const int skip = PASS ? s0 & 3 : 0, t0 = s0 - skip;
 #pragma unroll
   for (int d = 0; d < D - 1; ++d) load(o[d], t0 + d);
   __builtin_amdgcn_sched_barrier(0);
@@ -174,8 +179,7 @@ __device__ __forceinline__ bool tile_sum(const char* a0, const char* b0, const c
     // on and near the diagonal, so a tile's largest terms are those of its own rows'
     // and columns' k range, and every addition after them in their chain rounds at
     // their size.  So the chains end at fixed columns, whatever stage a wave's range begins
-    // with (the loop begins with the stage below that is a multiple of 4).  Two blocks
-    // of columns a wave: each after its own 32 columns.  One (32 x 32 tiles): after every
+    // with.  Two blocks of columns a wave: each after its own 32 columns.  One (32 x 32 tiles): after every
     // other 32 columns, the tile's own among them, and after its rows'.  Ended every 4
     // stages of a wave's range instead, errors in D and chi were 1.1 - 1.5 times these
     // (FP32, n = 128 - 1100).
@@ -184,7 +188,7 @@ __device__ __forceinline__ bool tile_sum(const char* a0, const char* b0, const c
   {                                                                                 \
     load(o[((K) + D - 1) % D], t0 + s + (K) + D - 1);                               \
     __builtin_amdgcn_sched_barrier(0);                                              \
-    if (s + (K) >= skip && s + (K) < cnt + skip) {                                  \
+    if ((!PASS || s + (K) >= skip) && s + (K) < cnt + skip) {                       \
       constexpr int blk = (K) * NB / 4;                                             \
       s_mma<PREC, BA, B, blk>(o[K], acc);                                           \
       bool end = ((K) & 1) != 0;                                                    \
