@@ -213,7 +213,10 @@ dmpt_status dmpt_sp2_density(const float* H, float* D, const dmpt_opts* opts, dm
  *   info host, optional.
  * The adjoint sweep stores every X_n in the workspace, or with opts.ckpt_interval = k
  * every k-th one plus k - 1 recomputation slots (the steps between checkpoints
- * are recomputed with the recorded sigma sequence before they are swept). */
+ * are recomputed with the recorded sigma sequence before they are swept).
+ * The same call gives the same bits.  A batch, its single observables and
+ * dmpt_sp2_density agree within rounding, not bit for bit: the tiles of a launch,
+ * and with them the order of its sums, depend on how many products share it. */
 dmpt_status dmpt_susceptibility(const float* H, const float* A, int32_t nobs, float* chi,
                                 float* D, double* a0, const dmpt_opts* opts, dmpt_info* info);
 

@@ -200,8 +200,8 @@ int small_tile(int prec, bool wide_lists, int n, int z, int with_p) {
 
 // The same for a solve made of general products (the finite-temperature path; not
 // by the number of observables, whose batches give the bits of single ones).
-// The line is where the small side stops winning at most sizes; the large one also
-// wins by 5 - 13 % where n fills a multiple of 512 of its padding (n = 2048, 2560).
+// The line is where the small side stops winning at most sizes; below it the large one
+// still wins by 5 - 14 % near n = 2048 (FP32) and n = 2560.
 // Whole solves with one observable (gapped, kT = 0.01), ms, small / large: FP16 split
 // n = 2048 38.8 / 46.1, n = 2304 44.9 / 53.9, n = 2560 66.2 / 63.0, n = 2816 74.9 / 84.5,
 // n = 3072 95.0 / 93.9, n = 3328 122 / 106; FP32 n = 1536 39.4 / 47.8, n = 2048 98.0 / 87.2,
